@@ -1224,6 +1224,7 @@ int xls_subdomain_tune(xls_subdomain_t s, int32_t prec, int32_t block, int32_t t
   return guarded([&]() -> int {
     if (!s) fail(XLS_ERR_INVALID_ARG, "NULL handle");
     if (prec != XLS_PREC_FP64 && prec != XLS_PREC_FP32) fail(XLS_ERR_INVALID_ARG, "prec must be FP64 or FP32");
+    if (tz < 0) fail(XLS_ERR_INVALID_ARG, "stencil tile sizes must be >= 0");
     StencilLaunch c;
     c.block = block;
     c.ty = ty;

@@ -823,6 +823,7 @@ int tune_batch(xls_batch_s* b, const char* cache_path, double* best_ms_out) {
           StencilLaunch cfg = cfg_of<TS>(s);
           cfg.block = block;
           cfg.ty = ty;
+          cfg.tz = 0;  // as xls_subdomain_tune applies it below
           cfg.nv = nv;
           try {
             stencil_validate(s->n[0], s->n[1], s->n[2], s->bc == XLS_BC_PERIODIC, sizeof(TS), s->nproj(), cfg);

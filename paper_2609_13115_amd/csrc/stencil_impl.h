@@ -741,40 +741,77 @@ struct TileChoice {
 };
 
 // Launch plan: one grid point per lane-slot, at most 2 slots per lane.
-inline int default_ty(int nx, int ny, int elem, int block, const StencilLaunch& cfg) {
+inline int default_ty(int nx, int ny, int block, const StencilLaunch& cfg, int per_lane) {
   // default tile: ~2 points per lane (measured best on the 64^3 box in both
   // precisions, and for the FP64 residual sweep of FP32 blocks: -16 %)
-  const int target = 2 * block;
-  (void)elem;
-  const int ty = cfg.ty > 0 ? cfg.ty : std::max(1, target / nx);
+  const int ty = cfg.ty > 0 ? cfg.ty : std::max(1, per_lane * block / nx);
   return std::max(1, std::min(ty, ny));
 }
 
-inline TileChoice choose_tiles(int nx, int ny, int nz, int elem, int nproj, int64_t ld, int periodic,
+// Workgroups a launch should have so that every CU holds its share: about
+// four 256-thread workgroups of one-vector tiles are resident per CU.
+constexpr int64_t kTileSlots = 1024;
+// Two vectors per tile pay (-6 to -10 %: V, the reverse-CSR words and the
+// projector payload are read once for both) only while the halved workgroup
+// count still fills the chip several times over: 1,920 workgroups (64^3, 480
+// columns) 403 against 426 us FP32, but 805 (53 x 61 x 47, 229 columns) 163
+// against 147 us.
+constexpr int64_t kTwoVecWgs = 1536;
+
+// Shape of a launch over `cols` columns (grouped launches pass the columns of
+// this size that would hold the whole group's points).  With cfg.tz < 0 the
+// z range is cut so that small launches fill the chip: a workgroup's time is
+// a fixed start (about 4 us: the first 13 planes load together) plus 0.6 to
+// 1.3 us per plane, whatever its neighbours do, so one column group on a
+// whole box leaves the chip idle.  Measured, whole box against cut (us per
+// launch): 24^3 x 20 columns FP64 55.8 -> 11.2, 17 x 21 x 14 x 31 37.6 ->
+// 9.9, one 64^3 column 128 -> 10.8 (FP64) and 90 -> 9.7 (FP32), 46^3 x 150
+// FP32 98.7 -> 67.3.  Cuts re-read 12 y planes each, so where the chip is
+// full they stay above 20 planes (53 x 61 x 47 x 229 FP32: 24 planes 140 us,
+// whole 147, 6 planes 159, 2 planes 258).
+inline TileChoice choose_tiles(int nx, int ny, int nz, int elem, int nproj, int64_t cols, int periodic,
                                const StencilLaunch& cfg) {
   TileChoice tc{};
-  if (cfg.block == 0) {  // 256 threads when their halo budget covers the tile's halo, else 512
-    const int ty = default_ty(nx, ny, elem, 256, cfg);
-    tc.block = (2 * R * nx + (periodic ? 2 * R * ty : 0) <= HMAX * 256) ? 256 : 512;
-  } else {
-    tc.block = cfg.block == 256 ? 256 : 512;
+  const bool fit = cfg.tz < 0;
+  auto block_of = [&](int per_lane) {
+    if (cfg.block != 0) return cfg.block == 256 ? 256 : 512;
+    // 256 threads when their halo budget covers the tile's halo, else 512
+    const int ty = default_ty(nx, ny, 256, cfg, per_lane);
+    return (2 * R * nx + (periodic ? 2 * R * ty : 0) <= HMAX * 256) ? 256 : 512;
+  };
+  int per_lane = 2;
+  tc.block = block_of(per_lane);
+  int ty = default_ty(nx, ny, tc.block, cfg, per_lane);
+  if (fit && cfg.ty == 0 && cols * ((ny + ty - 1) / ty) * std::max(1, nz / 2) < kTileSlots) {
+    per_lane = 1;  // even two-plane chunks leave CUs idle: smaller bands
+    tc.block = block_of(per_lane);
+    ty = default_ty(nx, ny, tc.block, cfg, per_lane);
   }
-  (void)ld;
-  const int ty = default_ty(nx, ny, elem, tc.block, cfg);
   tc.ty = ty;
   tc.nyt = (ny + ty - 1) / ty;
-  tc.tz = cfg.tz > 0 ? std::min(cfg.tz, nz) : nz;
-  tc.nzt = (nz + tc.tz - 1) / tc.tz;
   tc.P = (nx * ty + tc.block - 1) / tc.block;
   tc.ws = (nx + 2 * R <= 80) ? 80 : 128;
   auto smem_of = [&](int nv) {
     return static_cast<size_t>(elem) * nv * (2 * (static_cast<size_t>(tc.ws) * (ty + 2 * R) + 1) + nproj);
   };
-  // Default: two vectors per tile, so V, the reverse-CSR words and the
-  // projector payload are read once for both (these tables outweigh a
-  // column's own traffic; -10 % launch time on the 64^3 box in both
-  // precisions); one when two would not fit the LDS.
-  tc.nv = cfg.nv > 0 ? cfg.nv : (smem_of(2) <= 160 * 1024 ? 2 : 1);
+  if (cfg.nv > 0)
+    tc.nv = cfg.nv;
+  else
+    tc.nv = (smem_of(2) <= 160 * 1024 && (!fit || (cols + 1) / 2 * tc.nyt >= kTwoVecWgs)) ? 2 : 1;
+  if (fit) {
+    const int64_t wgs = (cols + tc.nv - 1) / tc.nv * tc.nyt;
+    int64_t nzt;
+    if (tc.nv == 2)
+      nzt = nz >= 56 ? 2 : 1;  // a shorter last round: 64^3 x 480 -2 % in both precisions, 80^3 x 702 equal
+    else
+      nzt = std::max(std::min<int64_t>((3 * kTileSlots + wgs - 1) / wgs, nz / 20),
+                     std::min<int64_t>(kTileSlots / wgs, nz / 2));
+    nzt = std::max<int64_t>(nzt, 1);
+    tc.tz = static_cast<int>((nz + nzt - 1) / nzt);
+  } else {
+    tc.tz = cfg.tz > 0 ? std::min(cfg.tz, nz) : nz;
+  }
+  tc.nzt = (nz + tc.tz - 1) / tc.tz;
   tc.smem = smem_of(tc.nv);
   return tc;
 }
@@ -854,8 +891,15 @@ inline void fd_weights6(double w[R + 1]) {
 using namespace stencil_detail;
 
 template <typename TC>
-static TileChoice tiles_for(const OpTables<TC>& op, int64_t ld, const StencilLaunch& cfg) {
-  return choose_tiles(op.nx, op.ny, op.nz, sizeof(TC), 4 * op.n_atoms, ld, op.periodic, cfg);
+static TileChoice tiles_for(const OpTables<TC>& op, int64_t cols, const StencilLaunch& cfg) {
+  return choose_tiles(op.nx, op.ny, op.nz, sizeof(TC), 4 * op.n_atoms, cols, op.periodic, cfg);
+}
+
+// residual sweeps keep per-column partial sums: one vector per tile
+inline StencilLaunch resid_cfg(const StencilLaunch& cfg) {
+  StencilLaunch c = cfg;
+  c.nv = 1;
+  return c;
 }
 
 #ifdef XLS_STENCIL_DEFINE_HOST
@@ -863,20 +907,20 @@ void stencil_validate(int nx, int ny, int nz, int periodic, int elem_bytes, int 
                       const StencilLaunch& cfg) {
   if (cfg.block != 0 && cfg.block != 256 && cfg.block != 512)
     fail(XLS_ERR_INVALID_ARG, "stencil block must be 0 (choose), 256 or 512");
-  if (cfg.ty < 0 || cfg.tz < 0) fail(XLS_ERR_INVALID_ARG, "stencil tile sizes must be >= 0");
+  if (cfg.ty < 0 || cfg.tz < -1) fail(XLS_ERR_INVALID_ARG, "stencil tile sizes must be >= 0");
   if (cfg.nv < 0 || cfg.nv > 2) fail(XLS_ERR_INVALID_ARG, "stencil vectors per tile must be 0, 1 or 2");
-  // both variants a launch may take (vector runs need an aligned column stride)
-  check_tiles(choose_tiles(nx, ny, nz, elem_bytes, nproj, 64, periodic, cfg), nx, periodic, elem_bytes);
+  // the shapes of the widest and the narrowest launch (points per lane, vectors per tile)
+  check_tiles(choose_tiles(nx, ny, nz, elem_bytes, nproj, 1 << 20, periodic, cfg), nx, periodic, elem_bytes);
   check_tiles(choose_tiles(nx, ny, nz, elem_bytes, nproj, 1, periodic, cfg), nx, periodic, elem_bytes);
 }
 
 size_t stencil_partial_elems(const OpTables<float>& op, int ncols, const StencilLaunch& cfg) {
-  const TileChoice a = tiles_for(op, 64, cfg), b = tiles_for(op, 1, cfg);
-  return static_cast<size_t>(kResidSums) * ncols * std::max(a.nyt * a.nzt, b.nyt * b.nzt);
+  const TileChoice tc = tiles_for(op, ncols, resid_cfg(cfg));
+  return static_cast<size_t>(kResidSums) * ncols * tc.nyt * tc.nzt;
 }
 size_t stencil_partial_elems(const OpTables<double>& op, int ncols, const StencilLaunch& cfg) {
-  const TileChoice a = tiles_for(op, 64, cfg), b = tiles_for(op, 1, cfg);
-  return static_cast<size_t>(kResidSums) * ncols * std::max(a.nyt * a.nzt, b.nyt * b.nzt);
+  const TileChoice tc = tiles_for(op, ncols, resid_cfg(cfg));
+  return static_cast<size_t>(kResidSums) * ncols * tc.nyt * tc.nzt;
 }
 
 #endif  // XLS_STENCIL_DEFINE_HOST
@@ -921,9 +965,7 @@ void launch_stencil(StencilMode mode, const OpTables<TC>& op, const TS* y, int64
                     const double* lam, double* partial, double* resid2, hipStream_t st,
                     const StencilLaunch& cfg, double* rq) {
   if (ncols <= 0) return;
-  StencilLaunch cfg1 = cfg;
-  if (mode == kResid) cfg1.nv = 1;  // per-column partial sums
-  const TileChoice tc = tiles_for(op, ld, cfg1);
+  const TileChoice tc = tiles_for(op, ncols, mode == kResid ? resid_cfg(cfg) : cfg);
   check_tiles(tc, op.nx, op.periodic, sizeof(TC));
   HArgs<TS, TC> A = make_hargs<TS, TC>(op, tc, y, ld, ncols, alpha, out, yprev);
   A.a = static_cast<TC>(a);
@@ -973,7 +1015,7 @@ void launch_filter_half(const OpTables<TC>& op, const TS* y, const uint16_t* y16
   static_assert(std::is_same<TS, TC>::value, "filter steps run in the storage precision");
   if (ncols <= 0) return;
   if ((y16 == nullptr) == (yprev16 == nullptr)) fail(XLS_ERR_INVALID_ARG, "one binary16 stream per half step");
-  const TileChoice tc = tiles_for(op, ld, cfg);
+  const TileChoice tc = tiles_for(op, ncols, cfg);
   check_tiles(tc, op.nx, op.periodic, sizeof(TC));
   HArgs<TS, TC> A = make_hargs<TS, TC>(op, tc, y16 ? reinterpret_cast<const TS*>(y16) : y, ld, ncols, alpha, out,
                                        reinterpret_cast<const TS*>(yprev16));
@@ -1108,10 +1150,13 @@ FilterGroup<TS>* filter_group_build(const std::vector<FilterGroupOp<TS>>& ops) {
     for (const auto& o : ops) g->steps = std::max(g->steps, o.degree);
     std::vector<TileChoice> tcs(n);
     std::vector<int> bucket_of(n);
+    // the group's points fill the chip together
+    int64_t points = 0;
+    for (const auto& o : ops) points += static_cast<int64_t>(o.op->nx) * o.op->ny * o.op->nz * o.ncols;
     for (int i = 0; i < n; ++i) {
       const auto& o = ops[i];
       if (o.degree < 1 || o.ncols < 1) fail(XLS_ERR_INVALID_ARG, "grouped filter: degree and ncols must be >= 1");
-      tcs[i] = tiles_for(*o.op, o.ld, o.cfg);
+      tcs[i] = tiles_for(*o.op, points / (static_cast<int64_t>(o.op->nx) * o.op->ny * o.op->nz), o.cfg);
       check_tiles(tcs[i], o.op->nx, o.op->periodic, sizeof(TS));
       int bi = -1;
       for (size_t j = 0; j < g->buckets.size(); ++j) {

@@ -1,0 +1,40 @@
+"""Stencil tiles chosen by the size of a launch (small launches cut the z range
+and take one vector per tile): the shape never changes a point's arithmetic,
+so filtered blocks are bit-identical to whole-box tiles, and the residual's
+partial sums differ by their order only."""
+import numpy as np
+import pytest
+
+from paper_2609_13115_amd import workloads, xls
+
+pytestmark = pytest.mark.gpu
+
+
+def box(shape, ns, periodic):
+    if periodic:
+        return workloads.periodic_si_cell(shape[0], ns, workloads.workload_key(1), True)
+    return workloads.small_dirichlet(shape[0], ns, shape=shape, h=0.6)
+
+
+# one column, odd extents, a z range shorter than a chunk, more columns than
+# fill the chip with whole boxes, rows wider than a wavefront
+@pytest.mark.parametrize("shape,ns,periodic", [((8, 8, 8), 1, True), ((24, 24, 24), 20, True), ((5, 7, 3), 3, False),
+                                               ((17, 21, 14), 31, False), ((70, 9, 11), 5, False),
+                                               ((20, 33, 45), 150, False), ((13, 12, 1), 2, False),
+                                               ((16, 64, 57), 400, False)])
+@pytest.mark.parametrize("prec", [xls.XLS_PREC_FP64, xls.XLS_PREC_FP32])
+def test_chosen_tiles_match_whole_box_tiles(shape, ns, periodic, prec):
+    print(f"[case] tiles {shape} ns={ns} periodic={periodic} prec={prec}", flush=True)
+    sd = box(shape, ns, periodic)
+    lam = np.linspace(-0.2, 0.5, ns)
+    out = []
+    for whole in (False, True):
+        with xls.Subdomain(sd, filter_prec=prec) as s:
+            if whole:
+                s.xls_subdomain_tune(xls.XLS_PREC_FP64, 0, 0, 0, 1)
+                s.xls_subdomain_tune(xls.XLS_PREC_FP32, 0, 0, 0, 1)
+            s.xls_subdomain_filter(4, -3.0, 4.0, 45.0)
+            out.append((s.xls_subdomain_get_block(), s.xls_subdomain_residual(lam)))
+    assert np.array_equal(out[0][0], out[1][0])
+    # N_d squares summed in another order: about N_d eps of the sum, twice
+    assert np.allclose(out[0][1], out[1][1], rtol=2 * sd.nd * 2.3e-16 + 1e-15, atol=0)
