@@ -895,10 +895,14 @@ static TileChoice tiles_for(const OpTables<TC>& op, int64_t cols, const StencilL
   return choose_tiles(op.nx, op.ny, op.nz, sizeof(TC), 4 * op.n_atoms, cols, op.periodic, cfg);
 }
 
-// residual sweeps keep per-column partial sums: one vector per tile
+// residual sweeps keep per-column partial sums: one vector per tile, and a z
+// cut of their own unless a chunk length was asked for, so that a handle
+// tuned to whole-box filter tiles sums its residuals in the order of an
+// untuned one
 inline StencilLaunch resid_cfg(const StencilLaunch& cfg) {
   StencilLaunch c = cfg;
   c.nv = 1;
+  if (c.tz == 0) c.tz = -1;
   return c;
 }
 
