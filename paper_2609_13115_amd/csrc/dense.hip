@@ -15,8 +15,8 @@
 //   T = S L S^T        split at negligible off-diagonals; eigenvalues by
 //                      Sturm-count multisection (one wavefront per eigenvalue);
 //                      eigenvectors by inverse iteration with partial
-//                      pivoting (one workgroup per cluster of close
-//                      eigenvalues, modified Gram-Schmidt inside a cluster)
+//                      pivoting (one wavefront per vector), modified
+//                      Gram-Schmidt inside clusters of close eigenvalues
 //   Y = Rinv Q S       reflectors applied in reverse order (LDS-resident
 //                      column blocks), then an MFMA GEMM
 // Every launch count depends on n only, never on the data.
@@ -29,6 +29,7 @@
 #include <cmath>
 #include <mutex>
 #include <string>
+#include <type_traits>
 
 #include "xls_handle.h"
 
@@ -38,7 +39,7 @@ namespace {
 constexpr double kEps = 2.220446049250313e-16;
 constexpr double kSafeMin = 2.2250738585072014e-308;
 constexpr int kPanel = 32;       // Cholesky panel width
-constexpr int kInvIters = 3;     // inverse-iteration solves per vector in a cluster (2 when alone)
+constexpr int kInvIters = 3;     // inverse-iteration solves per vector in a cluster (one less when alone)
 constexpr int kInvChunk = 16;    // steps of a sequential sweep whose inputs load together
 constexpr double kOrtol = 1e-3;  // cluster gap, relative to |T|_1
 constexpr int kSturmChunk = 16;  // rows of a Sturm-count recurrence read per LDS batch
@@ -409,19 +410,19 @@ __global__ __launch_bounds__(256) void trd_step_kernel(double* __restrict__ A, i
   if (lane == 0) pcur[i] = t * acc;
 }
 
-// The same step for trailing sizes n - k <= 64 kTrdPre.  Every wavefront
+// The same step for trailing sizes n - k <= 64 R (R 8 or 16).  Every wavefront
 // forms the step's reflector itself, in registers: lane l holds entries
 // j = k + l + 64 r of column k, of v_{k-1}, p_{k-1}, w_{k-1} and of its own
 // trailing column, and every sum is a butterfly over the wave (each lane ends
 // with the same bits), so there is no LDS traffic and no workgroup barrier.
 // Every wave computes the same reflector bit for bit; workgroup 0's first
 // wave stores it.
+template <int R>
 __global__ __launch_bounds__(256) void trd_step_wave_kernel(double* __restrict__ A, int n, int k,
                                                             double* __restrict__ Vh, double* __restrict__ tau,
                                                             double* __restrict__ d, double* __restrict__ e,
                                                             double* __restrict__ vbuf, double* __restrict__ pbuf,
                                                             const int32_t* __restrict__ flag) {
-  constexpr int R = kTrdPre;
   const int32_t failed = *flag;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int iown = k + 1 + blockIdx.x * 4 + wv;
@@ -805,30 +806,39 @@ __global__ __launch_bounds__(256) void tri_cluster_kernel(const double* __restri
     if (first(s)) cstart[off++] = s;
 }
 
-// One workgroup per cluster: for each slot s of the cluster, in order, inverse
-// iteration on the cluster's block with shift lam_s (raised to at least the
-// previous shift + 10 eps |T|_1 so that equal eigenvalues get distinct
-// vectors): LU of T - x I with partial pivoting (thread 0), kInvIters solves,
-// each followed by modified Gram-Schmidt against the cluster's earlier vectors
-// and normalisation.  Column s of Z receives the vector (zero off the block).
-// LDS: d, e, u0^-1, u1, u2, multipliers, x (m doubles each) and pivots.
-__global__ __launch_bounds__(256) void tri_inviter_kernel(const double* __restrict__ d,
-                                                          const double* __restrict__ ez,
-                                                          const int32_t* __restrict__ bs,
-                                                          const int32_t* __restrict__ be,
-                                                          const double* __restrict__ lam,
-                                                          const int32_t* __restrict__ cstart,
-                                                          const int32_t* __restrict__ ncl,
-                                                          const double* __restrict__ scal, int n,
-                                                          double* __restrict__ Z, const int32_t* __restrict__ flag) {
+// Inverse iteration, one wavefront per eigenvalue slot s: `solves` solves with
+// T - x_s I (LU with partial pivoting) on the slot's block, the vector
+// normalised after each, into column s of Z (zero off the block).  The shift
+// x_s is lam_s, raised so that the shifts of a cluster stay 10 eps |T|_1 apart
+// (equal eigenvalues get distinct vectors).  first: from the slot's start
+// vector; otherwise from column s of Z, for slots of clusters only.
+// Orthogonality inside a cluster is left to tri_ortho_kernel, so every vector
+// of the spectrum is solved at once.  What bounds it is the serial chain of
+// the LU and of the two sweeps of a solve (about 40 ns a row in all); one
+// workgroup per cluster, vector after vector, took the longest cluster's
+// length times that: 1.55 ms for a 480-state pencil, 8.5 ms for 1,201.
+// LDS: d, e, u0^-1, u1, u2, multipliers, x (n doubles each) and pivots.
+__global__ __launch_bounds__(64) void tri_solve_kernel(const double* __restrict__ d, const double* __restrict__ ez,
+                                                       const int32_t* __restrict__ bs,
+                                                       const int32_t* __restrict__ be,
+                                                       const double* __restrict__ lam,
+                                                       const int32_t* __restrict__ cstart,
+                                                       const int32_t* __restrict__ ncl,
+                                                       const double* __restrict__ scal, int n, int first, int solves,
+                                                       double* __restrict__ Z, const int32_t* __restrict__ flag) {
   extern __shared__ double sm[];
-  __shared__ double red[4];
   if (*flag) return;
-  const int c = blockIdx.x, nc = *ncl;
-  if (c >= nc) return;
-  const int tid = threadIdx.x;
+  const int s = blockIdx.x, lane = threadIdx.x, nc = *ncl;
+  // the slot's cluster: the last of the ascending starts at or before s
+  int c = 0;
+  for (int t0 = 0; t0 < nc; t0 += 64) {
+    const int t = t0 + lane;
+    c += __popcll(__ballot(t < nc && cstart[min(t, nc - 1)] <= s));
+  }
+  --c;
   const int sb = cstart[c], se = (c + 1 < nc) ? cstart[c + 1] : n;
-  const int s0 = bs[sb], s1 = be[sb], m = s1 - s0;
+  if (!first && se - sb == 1) return;
+  const int s0 = bs[s], s1 = be[s], m = s1 - s0;
   double* dd = sm;
   double* ee = sm + n;
   double* r0 = sm + 2 * n;
@@ -837,202 +847,38 @@ __global__ __launch_bounds__(256) void tri_inviter_kernel(const double* __restri
   double* ll = sm + 5 * n;
   double* x = sm + 6 * n;
   uint8_t* piv = reinterpret_cast<uint8_t*>(sm + 7 * n);
-  for (int j = tid; j < m; j += 256) {
+  for (int j = lane; j < m; j += 64) {
     dd[j] = d[s0 + j];
     ee[j] = (j + 1 < m) ? ez[s0 + j] : 0.0;
   }
-  __syncthreads();
   const double tn = scal[0];
   const double pertol = 10.0 * kEps * tn;
   const double pmin = fmax(1e-3 * kEps * tn, 1e-150);  // pivot floor; growth stays far from overflow
-  double xprev = 0.0;
-  for (int s = sb; s < se; ++s) {
-    double xs = lam[s];
-    if (s > sb && xs - xprev < pertol) xs = xprev + pertol;
-    xprev = xs;
-    // The three sequential sweeps below (LU, forward, backward) run on one
-    // thread.  Each loads kInvChunk steps' inputs into registers before it
-    // runs them, so the dependent chain waits on LDS once per chunk instead
-    // of once per step (the arrays share one LDS block, so the compiler
-    // cannot move a load above an earlier store by itself).
-    if (tid == 0) {
-      double bb = dd[0] - xs, cc = ee[0];
-      for (int i0 = 0; i0 + 1 < m; i0 += kInvChunk) {
-        const int nstep = min(kInvChunk, m - 1 - i0);
-        double ea[kInvChunk + 1], db[kInvChunk];
-#pragma unroll
-        for (int t = 0; t <= kInvChunk; ++t) ea[t] = ee[min(i0 + t, m - 1)];
-#pragma unroll
-        for (int t = 0; t < kInvChunk; ++t) db[t] = dd[min(i0 + 1 + t, m - 1)];
-#pragma unroll
-        for (int t = 0; t < kInvChunk; ++t) {
-          if (t < nstep) {
-            const int i = i0 + t;
-            const double a = ea[t], b = db[t] - xs, cn = ea[t + 1];
-            const double ra = rcp_nr(a);  // depends on the inputs only: off the recurrence's chain
-            if (fabs(a) > fabs(bb)) {
-              piv[i] = 1;
-              r0[i] = ra;
-              u1[i] = b;
-              u2[i] = cn;
-              const double mult = bb * ra;
-              ll[i] = mult;
-              bb = cc - mult * b;
-              cc = -mult * cn;
-            } else {
-              piv[i] = 0;
-              const double p = (fabs(bb) < pmin) ? copysign(pmin, bb) : bb;
-              const double rp = rcp_nr(p);
-              r0[i] = rp;
-              u1[i] = cc;
-              u2[i] = 0.0;
-              const double mult = a * rp;
-              ll[i] = mult;
-              bb = b - mult * cc;
-              cc = cn;
-            }
-          }
-        }
-      }
-      r0[m - 1] = rcp_nr((fabs(bb) < pmin) ? copysign(pmin, bb) : bb);
-    }
-    double part = 0.0;
-    for (int j = tid; j < m; j += 256) {
-      const double b = start_value(static_cast<uint32_t>(s), static_cast<uint32_t>(j));
-      x[j] = b;
-      part += b * b;
-    }
-    const double scale0 = 1.0 / sqrt(block_sum(part, red));
-    for (int j = tid; j < m; j += 256) x[j] *= scale0;
-    __syncthreads();
-    const int iters = (se - sb == 1) ? kInvIters - 1 : kInvIters;  // clusters get one more solve
-    for (int it = 0; it < iters; ++it) {
-      if (tid == 0) {
-        double cur = x[0];
-        for (int i0 = 0; i0 + 1 < m; i0 += kInvChunk) {
-          const int nstep = min(kInvChunk, m - 1 - i0);
-          double xn[kInvChunk], lc[kInvChunk];
-          uint8_t pc[kInvChunk];
-#pragma unroll
-          for (int t = 0; t < kInvChunk; ++t) {
-            const int i = min(i0 + t, m - 2);
-            xn[t] = x[i + 1];  // read before this chunk writes x[i0 + t]
-            lc[t] = ll[i];
-            pc[t] = piv[i];
-          }
-#pragma unroll
-          for (int t = 0; t < kInvChunk; ++t) {
-            if (t < nstep) {
-              const double nx = xn[t];
-              if (pc[t]) {
-                x[i0 + t] = nx;
-                cur = cur - lc[t] * nx;
-              } else {
-                x[i0 + t] = cur;
-                cur = nx - lc[t] * cur;
-              }
-            }
-          }
-        }
-        double x1 = cur * r0[m - 1], x2 = 0.0;
-        x[m - 1] = x1;
-        for (int i1 = m - 2; i1 >= 0; i1 -= kInvChunk) {
-          const int nstep = min(kInvChunk, i1 + 1);
-          double xc[kInvChunk], a1[kInvChunk], a2[kInvChunk], rc[kInvChunk];
-#pragma unroll
-          for (int t = 0; t < kInvChunk; ++t) {
-            const int i = max(i1 - t, 0);
-            xc[t] = x[i];
-            a1[t] = u1[i];
-            a2[t] = u2[i];
-            rc[t] = r0[i];
-          }
-#pragma unroll
-          for (int t = 0; t < kInvChunk; ++t) {
-            if (t < nstep) {
-              const double xi = (xc[t] - a1[t] * x1 - a2[t] * x2) * rc[t];
-              x[i1 - t] = xi;
-              x2 = x1;
-              x1 = xi;
-            }
-          }
-        }
-      }
-      __syncthreads();
-      for (int t = sb; t < s; ++t) {
-        const double* zt = Z + static_cast<int64_t>(t) * n + s0;
-        double p = 0.0;
-        for (int j = tid; j < m; j += 256) p += zt[j] * x[j];
-        const double dot = block_sum(p, red);
-        for (int j = tid; j < m; j += 256) x[j] -= dot * zt[j];
-      }
-      double mx = 0.0;
-      for (int j = tid; j < m; j += 256) mx = fmax(mx, fabs(x[j]));
-      const double rmx = 1.0 / block_max(mx, red);
-      double q = 0.0;
-      for (int j = tid; j < m; j += 256) {
-        const double y = x[j] * rmx;
-        q += y * y;
-      }
-      const double rs = rmx / sqrt(block_sum(q, red));
-      for (int j = tid; j < m; j += 256) x[j] *= rs;
-      __syncthreads();
-    }
-    double* zs = Z + static_cast<int64_t>(s) * n;
-    for (int r = tid; r < n; r += 256) zs[r] = (r >= s0 && r < s1) ? x[r - s0] : 0.0;
-    __syncthreads();
+  double xs = lam[s];
+  for (int t = sb + lane; t < s; t += 64) xs = fmax(xs, lam[t] + static_cast<double>(s - t) * pertol);
+  xs = wave_max(xs);
+  double* zs = Z + static_cast<int64_t>(s) * n;
+  double part = 0.0;
+  for (int j = lane; j < m; j += 64) {
+    const double v = first ? start_value(static_cast<uint32_t>(s), static_cast<uint32_t>(j)) : zs[s0 + j];
+    x[j] = v;
+    part += v * v;
   }
-}
-
-// The same inverse iteration for n <= kPipeMaxN with the next slot's LU
-// overlapped: while wave 0 runs slot s's solves, Gram-Schmidt and
-// normalisation (wave reductions only, no workgroup barrier inside a slot),
-// the first lane of wave 1 factors T - x_{s+1} I into the other set of
-// factor arrays; one barrier per slot.  Same steps and shifts as
-// tri_inviter_kernel; its sums run over one wave instead of the workgroup.
-// LDS: d, e, x (n each), two sets of u0^-1, u1, u2 and multipliers (4n each)
-// and two pivot arrays (n bytes each).
-constexpr int kPipeMaxN = 1800;
-__global__ __launch_bounds__(256) void tri_inviter_pipe_kernel(const double* __restrict__ d,
-                                                               const double* __restrict__ ez,
-                                                               const int32_t* __restrict__ bs,
-                                                               const int32_t* __restrict__ be,
-                                                               const double* __restrict__ lam,
-                                                               const int32_t* __restrict__ cstart,
-                                                               const int32_t* __restrict__ ncl,
-                                                               const double* __restrict__ scal, int n,
-                                                               double* __restrict__ Z,
-                                                               const int32_t* __restrict__ flag) {
-  extern __shared__ double sm[];
-  if (*flag) return;
-  const int c = blockIdx.x, nc = *ncl;
-  if (c >= nc) return;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int sb = cstart[c], se = (c + 1 < nc) ? cstart[c + 1] : n;
-  const int s0 = bs[sb], s1 = be[sb], m = s1 - s0;
-  double* dd = sm;
-  double* ee = sm + n;
-  double* x = sm + 2 * n;
-  double* fac = sm + 3 * n;  // set b: r0, u1, u2, ll at fac + (4 b + k) n
-  uint8_t* pvs = reinterpret_cast<uint8_t*>(sm + 11 * n);  // set b at pvs + b n
-  for (int j = tid; j < m; j += 256) {
-    dd[j] = d[s0 + j];
-    ee[j] = (j + 1 < m) ? ez[s0 + j] : 0.0;
+  if (first) {
+    const double scale0 = 1.0 / sqrt(wave_sum(part));
+    for (int j = lane; j < m; j += 64) x[j] *= scale0;
   }
   __syncthreads();
-  const double tn = scal[0];
-  const double pertol = 10.0 * kEps * tn;
-  const double pmin = fmax(1e-3 * kEps * tn, 1e-150);
-  // LU with partial pivoting of T - xs I into factor set b (one thread)
-  auto lu = [&](double xs, int b) {
-    double* r0 = fac + (4 * b + 0) * static_cast<int64_t>(n);
-    double* u1 = fac + (4 * b + 1) * static_cast<int64_t>(n);
-    double* u2 = fac + (4 * b + 2) * static_cast<int64_t>(n);
-    double* ll = fac + (4 * b + 3) * static_cast<int64_t>(n);
-    uint8_t* piv = pvs + b * static_cast<int64_t>(n);
+  // The three sequential sweeps below (LU, forward, backward) run on one
+  // lane.  Each loads kInvChunk steps' inputs into registers before it runs
+  // them, so the dependent chain waits on LDS once per chunk instead of once
+  // per step (the arrays share one LDS block, so the compiler cannot move a
+  // load above an earlier store by itself).  Steps are branch-free, and whole
+  // chunks carry no bounds test, so a chunk is one basic block whose
+  // independent parts (the reciprocals of e, the stores) overlap the chain.
+  if (lane == 0) {
     double bb = dd[0] - xs, cc = ee[0];
-    for (int i0 = 0; i0 + 1 < m; i0 += kInvChunk) {
-      const int nstep = min(kInvChunk, m - 1 - i0);
+    auto chunk = [&](auto whole, int i0, int nstep) {
       double ea[kInvChunk + 1], db[kInvChunk];
 #pragma unroll
       for (int t = 0; t <= kInvChunk; ++t) ea[t] = ee[min(i0 + t, m - 1)];
@@ -1040,142 +886,139 @@ __global__ __launch_bounds__(256) void tri_inviter_pipe_kernel(const double* __r
       for (int t = 0; t < kInvChunk; ++t) db[t] = dd[min(i0 + 1 + t, m - 1)];
 #pragma unroll
       for (int t = 0; t < kInvChunk; ++t) {
-        if (t < nstep) {
-          const int i = i0 + t;
-          const double a = ea[t], bv = db[t] - xs, cn = ea[t + 1];
-          const double ra = rcp_nr(a);
-          if (fabs(a) > fabs(bb)) {
-            piv[i] = 1;
-            r0[i] = ra;
-            u1[i] = bv;
-            u2[i] = cn;
-            const double mult = bb * ra;
-            ll[i] = mult;
-            bb = cc - mult * bv;
-            cc = -mult * cn;
-          } else {
-            piv[i] = 0;
-            const double p = (fabs(bb) < pmin) ? copysign(pmin, bb) : bb;
-            const double rp = rcp_nr(p);
-            r0[i] = rp;
-            u1[i] = cc;
-            u2[i] = 0.0;
-            const double mult = a * rp;
-            ll[i] = mult;
-            bb = bv - mult * cc;
-            cc = cn;
-          }
-        }
+        if (!decltype(whole)::value && t >= nstep) continue;
+        const int i = i0 + t;
+        const double a = ea[t], bv = db[t] - xs, cn = ea[t + 1];
+        const bool swap = fabs(a) > fabs(bb);
+        const double p = (fabs(bb) < pmin) ? copysign(pmin, bb) : bb;
+        const double rp = swap ? rcp_nr(a) : rcp_nr(p);
+        const double mult = (swap ? bb : a) * rp;
+        const double top = swap ? bv : cc;  // the pivot row's second entry
+        piv[i] = swap ? 1 : 0;
+        r0[i] = rp;
+        u1[i] = top;
+        u2[i] = swap ? cn : 0.0;
+        ll[i] = mult;
+        bb = (swap ? cc : bv) - mult * top;
+        cc = swap ? -mult * cn : cn;
       }
-    }
+    };
+    int i0 = 0;
+    for (; i0 + kInvChunk < m; i0 += kInvChunk) chunk(std::true_type{}, i0, kInvChunk);
+    if (i0 + 1 < m) chunk(std::false_type{}, i0, m - 1 - i0);
     r0[m - 1] = rcp_nr((fabs(bb) < pmin) ? copysign(pmin, bb) : bb);
-  };
-  double xcur = lam[sb];
-  if (tid == 0) lu(xcur, 0);
-  __syncthreads();
-  const int iters = (se - sb == 1) ? kInvIters - 1 : kInvIters;  // clusters get one more solve
-  for (int s = sb; s < se; ++s) {
-    const int b = (s - sb) & 1;
-    double xnext = 0.0;
-    if (s + 1 < se) {
-      xnext = lam[s + 1];
-      if (xnext - xcur < pertol) xnext = xcur + pertol;
-    }
-    if (wv == 0) {
-      const double* r0 = fac + (4 * b + 0) * static_cast<int64_t>(n);
-      const double* u1 = fac + (4 * b + 1) * static_cast<int64_t>(n);
-      const double* u2 = fac + (4 * b + 2) * static_cast<int64_t>(n);
-      const double* ll = fac + (4 * b + 3) * static_cast<int64_t>(n);
-      const uint8_t* piv = pvs + b * static_cast<int64_t>(n);
-      double part = 0.0;
-      for (int j = lane; j < m; j += 64) {
-        const double v = start_value(static_cast<uint32_t>(s), static_cast<uint32_t>(j));
-        x[j] = v;
-        part += v * v;
-      }
-      const double scale0 = 1.0 / sqrt(wave_sum(part));
-      for (int j = lane; j < m; j += 64) x[j] *= scale0;
-      asm volatile("" ::: "memory");
-      for (int it = 0; it < iters; ++it) {
-        if (lane == 0) {
-          double cur = x[0];
-          for (int i0 = 0; i0 + 1 < m; i0 += kInvChunk) {
-            const int nstep = min(kInvChunk, m - 1 - i0);
-            double xn[kInvChunk], lc[kInvChunk];
-            uint8_t pc[kInvChunk];
+  }
+  for (int it = 0; it < solves; ++it) {
+    if (lane == 0) {
+      double cur = x[0];
+      auto forward = [&](auto whole, int i0, int nstep) {
+        double xn[kInvChunk], lc[kInvChunk];
+        uint8_t pc[kInvChunk];
 #pragma unroll
-            for (int t = 0; t < kInvChunk; ++t) {
-              const int i = min(i0 + t, m - 2);
-              xn[t] = x[i + 1];
-              lc[t] = ll[i];
-              pc[t] = piv[i];
-            }
-#pragma unroll
-            for (int t = 0; t < kInvChunk; ++t) {
-              if (t < nstep) {
-                const double nx = xn[t];
-                if (pc[t]) {
-                  x[i0 + t] = nx;
-                  cur = cur - lc[t] * nx;
-                } else {
-                  x[i0 + t] = cur;
-                  cur = nx - lc[t] * cur;
-                }
-              }
-            }
-          }
-          double x1 = cur * r0[m - 1], x2 = 0.0;
-          x[m - 1] = x1;
-          for (int i1 = m - 2; i1 >= 0; i1 -= kInvChunk) {
-            const int nstep = min(kInvChunk, i1 + 1);
-            double xc[kInvChunk], a1[kInvChunk], a2[kInvChunk], rc[kInvChunk];
-#pragma unroll
-            for (int t = 0; t < kInvChunk; ++t) {
-              const int i = max(i1 - t, 0);
-              xc[t] = x[i];
-              a1[t] = u1[i];
-              a2[t] = u2[i];
-              rc[t] = r0[i];
-            }
-#pragma unroll
-            for (int t = 0; t < kInvChunk; ++t) {
-              if (t < nstep) {
-                const double xi = (xc[t] - a1[t] * x1 - a2[t] * x2) * rc[t];
-                x[i1 - t] = xi;
-                x2 = x1;
-                x1 = xi;
-              }
-            }
-          }
+        for (int t = 0; t < kInvChunk; ++t) {
+          const int i = min(i0 + t, m - 2);
+          xn[t] = x[i + 1];  // read before this chunk writes x[i0 + t]
+          lc[t] = ll[i];
+          pc[t] = piv[i];
         }
-        asm volatile("" ::: "memory");  // the wave reads x after lane 0's writes (LDS is in order per wave)
-        for (int t = sb; t < s; ++t) {
-          const double* zt = Z + static_cast<int64_t>(t) * n + s0;
-          double p = 0.0;
-          for (int j = lane; j < m; j += 64) p += zt[j] * x[j];
-          const double dot = wave_sum(p);
-          for (int j = lane; j < m; j += 64) x[j] -= dot * zt[j];
-          asm volatile("" ::: "memory");
+#pragma unroll
+        for (int t = 0; t < kInvChunk; ++t) {
+          if (!decltype(whole)::value && t >= nstep) continue;
+          const double top = pc[t] ? xn[t] : cur, bot = pc[t] ? cur : xn[t];
+          x[i0 + t] = top;
+          cur = bot - lc[t] * top;
         }
-        double mx = 0.0;
-        for (int j = lane; j < m; j += 64) mx = fmax(mx, fabs(x[j]));
-        const double rmx = 1.0 / wave_max(mx);
-        double q = 0.0;
-        for (int j = lane; j < m; j += 64) {
-          const double y = x[j] * rmx;
-          q += y * y;
+      };
+      int i0 = 0;
+      for (; i0 + kInvChunk < m; i0 += kInvChunk) forward(std::true_type{}, i0, kInvChunk);
+      if (i0 + 1 < m) forward(std::false_type{}, i0, m - 1 - i0);
+      double x1 = cur * r0[m - 1], x2 = 0.0;
+      x[m - 1] = x1;
+      auto backward = [&](auto whole, int i1, int nstep) {
+        double xc[kInvChunk], a1[kInvChunk], a2[kInvChunk], rc[kInvChunk];
+#pragma unroll
+        for (int t = 0; t < kInvChunk; ++t) {
+          const int i = max(i1 - t, 0);
+          xc[t] = x[i];
+          a1[t] = u1[i];
+          a2[t] = u2[i];
+          rc[t] = r0[i];
         }
-        const double rs = rmx / sqrt(wave_sum(q));
-        for (int j = lane; j < m; j += 64) x[j] *= rs;
-        asm volatile("" ::: "memory");
-      }
-      double* zs = Z + static_cast<int64_t>(s) * n;
-      for (int r = lane; r < n; r += 64) zs[r] = (r >= s0 && r < s1) ? x[r - s0] : 0.0;
-    } else if (wv == 1 && lane == 0 && s + 1 < se) {
-      lu(xnext, b ^ 1);
+#pragma unroll
+        for (int t = 0; t < kInvChunk; ++t) {
+          if (!decltype(whole)::value && t >= nstep) continue;
+          const double xi = ((xc[t] - a2[t] * x2) - a1[t] * x1) * rc[t];
+          x[i1 - t] = xi;
+          x2 = x1;
+          x1 = xi;
+        }
+      };
+      int i1 = m - 2;
+      for (; i1 + 1 >= kInvChunk; i1 -= kInvChunk) backward(std::true_type{}, i1, kInvChunk);
+      if (i1 >= 0) backward(std::false_type{}, i1, i1 + 1);
     }
     __syncthreads();
-    xcur = xnext;
+    double mx = 0.0;
+    for (int j = lane; j < m; j += 64) mx = fmax(mx, fabs(x[j]));
+    const double rmx = 1.0 / wave_max(mx);
+    double q = 0.0;
+    for (int j = lane; j < m; j += 64) {
+      const double y = x[j] * rmx;
+      q += y * y;
+    }
+    const double rs = rmx / sqrt(wave_sum(q));
+    for (int j = lane; j < m; j += 64) x[j] *= rs;
+    __syncthreads();
+  }
+  for (int r = lane; r < n; r += 64) zs[r] = (r >= s0 && r < s1) ? x[r - s0] : 0.0;
+}
+
+// Modified Gram-Schmidt over the vectors of each cluster, one workgroup per
+// cluster: once vector j is final, every wavefront takes its component out of
+// the later vectors it owns (one barrier per vector).  The vectors are unit
+// when they come in and are normalised at the end.
+constexpr int kOrthoThreads = 1024;
+__global__ __launch_bounds__(kOrthoThreads) void tri_ortho_kernel(const int32_t* __restrict__ bs,
+                                                                  const int32_t* __restrict__ be,
+                                                                  const int32_t* __restrict__ cstart,
+                                                                  const int32_t* __restrict__ ncl, int n,
+                                                                  double* __restrict__ Z,
+                                                                  const int32_t* __restrict__ flag) {
+  if (*flag) return;
+  const int c = blockIdx.x, nc = *ncl;
+  if (c >= nc) return;
+  const int sb = cstart[c], se = (c + 1 < nc) ? cstart[c + 1] : n;
+  if (se - sb == 1) return;
+  constexpr int NW = kOrthoThreads / 64;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int s0 = bs[sb], m = be[sb] - s0;
+  for (int j = sb; j + 1 < se; ++j) {
+    const double* zj = Z + static_cast<int64_t>(j) * n + s0;
+    for (int t = j + 1 + wv; t < se; t += NW) {
+      double* zt = Z + static_cast<int64_t>(t) * n + s0;
+      double pj = 0.0, pt = 0.0;
+      for (int r = lane; r < m; r += 64) {
+        const double v = zj[r];
+        pj += v * v;
+        pt += v * zt[r];
+      }
+      const double f = wave_sum(pt) / wave_sum(pj);
+      for (int r = lane; r < m; r += 64) zt[r] -= f * zj[r];
+    }
+    __syncthreads();
+  }
+  for (int t = sb + wv; t < se; t += NW) {
+    double* zt = Z + static_cast<int64_t>(t) * n + s0;
+    double mx = 0.0;
+    for (int r = lane; r < m; r += 64) mx = fmax(mx, fabs(zt[r]));
+    const double rmx = 1.0 / wave_max(mx);
+    double q = 0.0;
+    for (int r = lane; r < m; r += 64) {
+      const double y = zt[r] * rmx;
+      q += y * y;
+    }
+    const double rs = rmx / sqrt(wave_sum(q));
+    for (int r = lane; r < m; r += 64) zt[r] *= rs;
   }
 }
 
@@ -1203,31 +1046,31 @@ __global__ __launch_bounds__(256) void tri_rank_kernel(const double* __restrict_
 // (T_jj = tau_j, T[0:j, j] = -tau_j T[0:j, 0:j] V[:, 0:j]^T v_j).
 constexpr int kWyNB = 16;
 constexpr int kWyMaxN = 900;  // LDS: 4 columns + the block's 16 reflectors + T, (20 n + 256) doubles
-// T of block b (reflectors 16 b ...) into Tbuf + 256 b, column-major 16 x 16
+// T of block b (reflectors NB b ...) into Tbuf + NB^2 b, column-major NB x NB
 // (zero beyond the block's nb reflectors).  The block's reflectors are
-// staged in LDS (kWyNB n doubles); each wave forms a share of the Gram
+// staged in LDS (NB n doubles); each wave forms a share of the Gram
 // entries with lanes over the rows and a wave sum.
+template <int NB>
 __global__ __launch_bounds__(256) void bt_tfactor_kernel(const double* __restrict__ Vh,
                                                          const double* __restrict__ tau, int n,
                                                          double* __restrict__ Tbuf,
                                                          const int32_t* __restrict__ flag) {
-  extern __shared__ double vsh[];  // kWyNB * n
-  __shared__ double G[kWyNB * kWyNB];
-  __shared__ double Ts[kWyNB * kWyNB];
+  extern __shared__ double vsh[];  // NB * n
+  __shared__ double G[NB * NB];
+  __shared__ double Ts[NB * NB];
   if (*flag) return;
-  const int b = blockIdx.x, kb = b * kWyNB, nb = min(kWyNB, n - 1 - kb), tid = threadIdx.x;
+  const int b = blockIdx.x, kb = b * NB, nb = min(NB, n - 1 - kb), tid = threadIdx.x;
   const int lane = tid & 63, wv = tid >> 6;
-  for (int q = 0; q < kWyNB; ++q) {
+  for (int q = 0; q < NB; ++q) {
     const double* v = Vh + static_cast<int64_t>(min(kb + q, n - 1)) * n;
     for (int r = tid; r < n; r += 256) vsh[q * n + r] = (q < nb && r > kb + q) ? v[r] : 0.0;
   }
-  G[tid] = 0.0;
-  Ts[tid] = 0.0;
+  if (tid < NB * NB) G[tid] = Ts[tid] = 0.0;
   __syncthreads();
   // G[i + 16 j] = v_{kb+i} . v_{kb+j} for i < j (v_{kb+j} is zero in rows <= kb + j):
   // pair p = (i, j) goes to wave p mod 4
-  for (int pr = wv; pr < kWyNB * kWyNB; pr += 4) {
-    const int i = pr % kWyNB, j = pr / kWyNB;
+  for (int pr = wv; pr < NB * NB; pr += 4) {
+    const int i = pr % NB, j = pr / NB;
     if (!(i < j && j < nb)) continue;  // uniform across the wave
     double g = 0.0;
     for (int r = kb + j + 1 + lane; r < n; r += 64) g += vsh[i * n + r] * vsh[j * n + r];
@@ -1239,13 +1082,13 @@ __global__ __launch_bounds__(256) void bt_tfactor_kernel(const double* __restric
     const double ti = tau[kb + i];
     if (tid < i) {
       double acc = 0.0;
-      for (int c = tid; c < i; ++c) acc += Ts[tid + c * kWyNB] * G[c + i * kWyNB];
-      Ts[tid + i * kWyNB] = -ti * acc;
+      for (int c = tid; c < i; ++c) acc += Ts[tid + c * NB] * G[c + i * NB];
+      Ts[tid + i * NB] = -ti * acc;
     }
-    if (tid == i) Ts[i + i * kWyNB] = ti;
+    if (tid == i) Ts[i + i * NB] = ti;
     __syncthreads();
   }
-  Tbuf[static_cast<int64_t>(b) * kWyNB * kWyNB + tid] = Ts[tid];
+  if (tid < NB * NB) Tbuf[static_cast<int64_t>(b) * NB * NB + tid] = Ts[tid];
 }
 
 // out[:, c] = H_0 ... H_{n-2} Z[:, perm[c]], blocks applied from the last to
@@ -1339,6 +1182,111 @@ __global__ __launch_bounds__(256) void bt_wy_kernel(const double* __restrict__ Z
   }
 }
 
+// The same for larger n: each of eight wavefronts holds one column in
+// registers (ZR values a lane, ZR >= n / 64), and LDS holds only the block's
+// NB reflectors and T, the next block's being loaded meanwhile.  LDS reads of
+// the reflectors bound it: n = 1,201 (NB 16) BTMS ms, against 5.1 ms one
+// reflector at a time from LDS columns.
+constexpr int kWyRegThreads = 512;
+template <int ZR, int NB>
+__global__ __launch_bounds__(kWyRegThreads) void bt_wy_reg_kernel(const double* __restrict__ Z,
+                                                                  const int32_t* __restrict__ perm,
+                                                                  const double* __restrict__ Vh,
+                                                                  const double* __restrict__ Tbuf, int n,
+                                                                  double* __restrict__ out,
+                                                                  const int32_t* __restrict__ flag) {
+  extern __shared__ double sm[];
+  if (*flag) return;
+  constexpr int NT = kWyRegThreads, PF = (64 * ZR + NT - 1) / NT, LD = 64 * ZR;
+  double* vs = sm;            // NB columns of LD: vs[q LD + r] = v_{kb+q}[r], zero up to row kb + q and past n
+  double* ts = sm + NB * LD;  // NB * NB
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int c = blockIdx.x * (NT / 64) + (tid >> 6);
+  double z[ZR];
+  {
+    int pc = c < n ? perm[c] : 0;
+    pc = (pc >= 0 && pc < n) ? pc : 0;  // a rank is always in range; never index out of bounds
+    const double* src = Z + static_cast<int64_t>(pc) * n;
+#pragma unroll
+    for (int i = 0; i < ZR; ++i) {
+      const int r = lane + 64 * i;
+      z[i] = (c < n && r < n) ? src[r] : 0.0;
+    }
+  }
+  double pre[NB][PF], tpre;
+  auto fetch = [&](int b) {
+    const int kb = b * NB, nb = min(NB, n - 1 - kb);
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      const double* v = Vh + static_cast<int64_t>(min(kb + q, n - 1)) * n;
+#pragma unroll
+      for (int p = 0; p < PF; ++p) {
+        const int r = tid + NT * p;
+        pre[q][p] = (q < nb && r < n && r > kb + q) ? v[r] : 0.0;
+      }
+    }
+    tpre = tid < NB * NB ? Tbuf[static_cast<int64_t>(b) * NB * NB + tid] : 0.0;
+  };
+  const int nblocks = (n - 1 + NB - 1) / NB;
+  fetch(nblocks - 1);
+  for (int b = nblocks - 1; b >= 0; --b) {
+    __syncthreads();  // the previous block's readers are done
+#pragma unroll
+    for (int q = 0; q < NB; ++q)
+#pragma unroll
+      for (int p = 0; p < PF; ++p) {
+        const int r = tid + NT * p;
+        if (r < LD) vs[q * LD + r] = pre[q][p];
+      }
+    if (tid < NB * NB) ts[tid] = tpre;
+    __syncthreads();
+    if (b > 0) fetch(b - 1);
+    const int i0 = (b * NB) >> 6;  // rows below 64 i0 meet no reflector of the block
+    double acc[NB];
+#pragma unroll
+    for (int q = 0; q < NB; ++q) acc[q] = 0.0;
+    // the memory clobbers keep the compiler from hoisting every row's LDS reads
+    // above the first row (and spilling them)
+#pragma unroll
+    for (int i = 0; i < ZR; ++i) {
+      if (i >= i0) {
+        const double* row = vs + lane + 64 * i;
+#pragma unroll
+        for (int q = 0; q < NB; ++q) acc[q] += row[q * LD] * z[i];
+      }
+      asm volatile("" ::: "memory");
+    }
+    double u[NB];
+#pragma unroll
+    for (int q = 0; q < NB; ++q) acc[q] = wave_sum(acc[q]);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      double t = 0.0;
+#pragma unroll
+      for (int j = i; j < NB; ++j) t += ts[i + j * NB] * acc[j];
+      u[i] = t;
+    }
+#pragma unroll
+    for (int i = 0; i < ZR; ++i) {
+      if (i >= i0) {
+        const double* row = vs + lane + 64 * i;
+        double t = 0.0;
+#pragma unroll
+        for (int q = 0; q < NB; ++q) t += row[q * LD] * u[q];
+        z[i] -= t;
+      }
+      asm volatile("" ::: "memory");
+    }
+  }
+  if (c < n) {
+#pragma unroll
+    for (int i = 0; i < ZR; ++i) {
+      const int r = lane + 64 * i;
+      if (r < n) out[r + static_cast<int64_t>(c) * n] = z[i];
+    }
+  }
+}
+
 // out[:, c] = H_0 H_1 ... H_{n-2} Z[:, perm[c]]: four columns per workgroup,
 // one per wavefront, held in LDS.  Each wavefront steps through the
 // reflectors on its own (dot product by shuffles, no workgroup barrier);
@@ -1393,6 +1341,20 @@ __global__ __launch_bounds__(256) void bt_kernel(const double* __restrict__ Z, c
 }
 
 void set_smem(const void* fn, size_t bytes) { ensure_dyn_smem(fn, bytes); }
+
+// w.T = Q Z by blocks of NB reflectors with register-resident columns
+template <int ZR, int NB>
+void back_transform(DenseWork& w, const int32_t* perm, const double* tau, int n, hipStream_t st) {
+  // T of every block into C1 (free after C was formed): NB n doubles at most
+  const int nblocks = (n - 1 + NB - 1) / NB;
+  const size_t tf_sm = static_cast<size_t>(NB) * n * sizeof(double);
+  set_smem(reinterpret_cast<const void*>(bt_tfactor_kernel<NB>), tf_sm);
+  hipLaunchKernelGGL(bt_tfactor_kernel<NB>, dim3(nblocks), dim3(256), tf_sm, st, w.Vh, tau, n, w.C1, w.flag);
+  const size_t sm = (NB * 64 * ZR + NB * NB) * sizeof(double);
+  const auto kern = bt_wy_reg_kernel<ZR, NB>;
+  set_smem(reinterpret_cast<const void*>(kern), sm);
+  hipLaunchKernelGGL(kern, dim3(nblk(n, kWyRegThreads / 64)), dim3(kWyRegThreads), sm, st, w.Z, perm, w.Vh, w.C1, n, w.T, w.flag);
+}
 
 }  // namespace
 
@@ -1508,8 +1470,11 @@ int dense_geneig(DenseWork& w, const double* Hs, const double* M, double* Y, hip
   const int k0 = std::max(0, n - kTrdTail);
   for (int k = 0; k < k0; ++k) {
     const dim3 grid(std::max(1u, nblk(n - k - 1, 4)));
-    if (n - k <= 64 * kTrdPre)
-      hipLaunchKernelGGL(trd_step_wave_kernel, grid, dim3(256), 0, st, w.C0, n, k, w.Vh, tau, d, e, vbuf, pbuf,
+    if (n - k <= 512)
+      hipLaunchKernelGGL(trd_step_wave_kernel<8>, grid, dim3(256), 0, st, w.C0, n, k, w.Vh, tau, d, e, vbuf, pbuf,
+                         w.flag);
+    else if (n - k <= 1024)
+      hipLaunchKernelGGL(trd_step_wave_kernel<16>, grid, dim3(256), 0, st, w.C0, n, k, w.Vh, tau, d, e, vbuf, pbuf,
                          w.flag);
     else
       hipLaunchKernelGGL(trd_step_kernel, grid, dim3(256), trd_smem, st, w.C0, n, k, w.Vh, tau, d, e, vbuf, pbuf,
@@ -1529,17 +1494,14 @@ int dense_geneig(DenseWork& w, const double* Hs, const double* M, double* Y, hip
   hipLaunchKernelGGL(tri_multisect_kernel, dim3(n), dim3(64), 2 * static_cast<size_t>(n) * sizeof(double), st, d,
                      ez, e2, bs, be, w.scal, n, raw, w.flag);
   hipLaunchKernelGGL(tri_cluster_kernel, dim3(1), dim3(256), 0, st, raw, bs, w.scal, n, cstart, ncl, w.flag);
-  if (n <= kPipeMaxN) {
-    const size_t pipe_smem =
-        11 * static_cast<size_t>(n) * sizeof(double) + ((2 * static_cast<size_t>(n) + 7) & ~size_t{7});
-    set_smem(reinterpret_cast<const void*>(tri_inviter_pipe_kernel), pipe_smem);
-    hipLaunchKernelGGL(tri_inviter_pipe_kernel, dim3(n), dim3(256), pipe_smem, st, d, ez, bs, be, raw, cstart, ncl,
-                       w.scal, n, w.Z, w.flag);
-  } else {
-    const size_t inv_smem = 7 * static_cast<size_t>(n) * sizeof(double) + ((static_cast<size_t>(n) + 7) & ~size_t{7});
-    set_smem(reinterpret_cast<const void*>(tri_inviter_kernel), inv_smem);
-    hipLaunchKernelGGL(tri_inviter_kernel, dim3(n), dim3(256), inv_smem, st, d, ez, bs, be, raw, cstart, ncl,
-                       w.scal, n, w.Z, w.flag);
+  const size_t inv_smem = 7 * static_cast<size_t>(n) * sizeof(double) + ((static_cast<size_t>(n) + 7) & ~size_t{7});
+  set_smem(reinterpret_cast<const void*>(tri_solve_kernel), inv_smem);
+  // two solves from the start vectors, then, for clusters, an orthogonal
+  // basis, one more solve from it and the final basis
+  for (int round = 0; round < 2; ++round) {
+    hipLaunchKernelGGL(tri_solve_kernel, dim3(n), dim3(64), inv_smem, st, d, ez, bs, be, raw, cstart, ncl, w.scal, n,
+                       round == 0 ? 1 : 0, round == 0 ? kInvIters - 1 : 1, w.Z, w.flag);
+    hipLaunchKernelGGL(tri_ortho_kernel, dim3(n), dim3(kOrthoThreads), 0, st, bs, be, cstart, ncl, n, w.Z, w.flag);
   }
   hipLaunchKernelGGL(tri_rank_kernel, dim3(nblk(n, 256)), dim3(256), static_cast<size_t>(n) * sizeof(double), st,
                      raw, n, lam, perm, w.flag);
@@ -1549,12 +1511,18 @@ int dense_geneig(DenseWork& w, const double* Hs, const double* M, double* Y, hip
     // T of every block into C1 (free after C was formed): 256 (n / 16 + 1) <= n^2 doubles here
     const int nblocks = (n - 1 + kWyNB - 1) / kWyNB;
     const size_t tf_sm = static_cast<size_t>(kWyNB) * n * sizeof(double);
-    set_smem(reinterpret_cast<const void*>(bt_tfactor_kernel), tf_sm);
-    hipLaunchKernelGGL(bt_tfactor_kernel, dim3(nblocks), dim3(256), tf_sm, st, w.Vh, tau, n, w.C1, w.flag);
+    set_smem(reinterpret_cast<const void*>(bt_tfactor_kernel<kWyNB>), tf_sm);
+    hipLaunchKernelGGL(bt_tfactor_kernel<kWyNB>, dim3(nblocks), dim3(256), tf_sm, st, w.Vh, tau, n, w.C1, w.flag);
     const size_t sm = (static_cast<size_t>(4 + kWyNB) * n + kWyNB * kWyNB) * sizeof(double);
     set_smem(reinterpret_cast<const void*>(bt_wy_kernel), sm);
     hipLaunchKernelGGL(bt_wy_kernel, dim3(nblk(n, 4)), dim3(256), sm, st, w.Z, perm, w.Vh, w.C1, n, w.T, w.flag);
-  } else {
+  } else if (n > kWyMaxN && n <= 1216) {  // 16 reflectors fill the LDS
+    back_transform<19, 16>(w, perm, tau, n, st);
+  } else if (n > 1216 && n <= 1920) {
+    back_transform<30, 8>(w, perm, tau, n, st);
+  } else if (n > 1920 && n <= 2432) {
+    back_transform<38, 8>(w, perm, tau, n, st);
+  } else {  // below two blocks, and past 8 reflectors in LDS
     const size_t zbytes = kBtCols * static_cast<size_t>(n) * sizeof(double);
     const size_t budget = 150 * 1024;
     const int ch = static_cast<int>(std::max<size_t>(1, std::min<size_t>(32, (budget - zbytes) / ((n + 1) * sizeof(double)))));
