@@ -44,8 +44,7 @@ constexpr int kInvChunk = 16;    // steps of a sequential sweep whose inputs loa
 constexpr double kOrtol = 1e-3;  // cluster gap, relative to |T|_1
 constexpr int kSturmChunk = 16;  // rows of a Sturm-count recurrence read per LDS batch
 constexpr int kTrdPre = 8;       // column values per lane loaded ahead in a tridiagonalisation step
-constexpr int kTrdTail = 128;    // trailing steps done in one workgroup, block in LDS (m (m + 2) + 2m doubles);
-                                 // the tail kernel's update gives each lane two rows, so at most 128
+constexpr int kTrdTail = 192;   // trailing steps done in one workgroup, block in registers
 
 inline unsigned nblk(int64_t n, int b) { return static_cast<unsigned>((n + b - 1) / b); }
 
@@ -129,62 +128,117 @@ __global__ void copy_diag_kernel(const double* __restrict__ A, int n, double* __
 }
 
 // ---------------------------------------------------------------------------
+// Workgroup barrier that waits for LDS traffic only (lgkmcnt 0): global stores
+// stay in flight (a full barrier waits about a microsecond for them).
+__device__ __forceinline__ void lds_barrier() {
+  __asm__ __volatile__("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xC07F);
+  __builtin_amdgcn_s_barrier();
+  __asm__ __volatile__("" ::: "memory");
+}
+
 // Cholesky.  Panel j0: every workgroup factors the nb x nb diagonal block of
-// the (updated) upper triangle in LDS; workgroup 0 stores R11, the others
-// solve R11^T R12 = A12 for 256 columns each (one column per thread).
+// the (updated) upper triangle; workgroup 0 stores R11, the others solve
+// R11^T R12 = A12 for 256 columns each (one column per thread).  The block is
+// held in registers, four elements a lane, and eliminated unscaled: a step
+// publishes its row in LDS (two row buffers, one barrier), every lane
+// subtracts row_r row_c / pivot, and the square root and the scaled row are
+// off the chain.  The solve takes each x_i out of all later rows at once
+// (independent operations), times the stored reciprocal of the diagonal.  A
+// latency chain either way: 24 us a panel at n = 480, against 36 us with
+// three barriers, a square root and a division in turn per column.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void chol_panel_kernel(const double* __restrict__ A, int n, int j0, int nb,
                                                          const double* __restrict__ diag0,
                                                          int32_t* __restrict__ flag, double* __restrict__ R) {
-  __shared__ double S[kPanel * (kPanel + 1)];
+  constexpr int LD = kPanel + 2;  // rows of S 16-byte aligned
+  __shared__ __align__(16) double S[kPanel * LD];  // S[i LD + j] = R11[i][j]
+  __shared__ double row[2][kPanel], rinv[kPanel], floor_[kPanel];
+  const int tid = threadIdx.x, tr = tid >> 4, tc = tid & 15;
+  // this thread's column of A12, loaded while the block is factored
+  const int c = j0 + nb + (static_cast<int>(blockIdx.x) - 1) * 256 + tid;
+  const bool solves = blockIdx.x > 0 && c < n;
+  double x[kPanel];
+#pragma unroll
+  for (int i = 0; i < kPanel; ++i) x[i] = (solves && i < nb) ? A[static_cast<int64_t>(c) * n + j0 + i] : 0.0;
   if (*flag) return;
-  const int tid = threadIdx.x;
-  constexpr int LD = kPanel + 1;
-  for (int e = tid; e < kPanel * kPanel; e += 256) {
-    const int i = e % kPanel, j = e / kPanel;
-    S[i + j * LD] = (i < nb && j < nb && i <= j) ? A[(j0 + i) + static_cast<int64_t>(j0 + j) * n] : 0.0;
+  double a[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int r = tr + 16 * i, q = tc + 16 * j;
+      a[i][j] = (r <= q && q < nb) ? A[(j0 + r) + static_cast<int64_t>(j0 + q) * n] : 0.0;
+    }
+  if (tid < kPanel) {
+    floor_[tid] = tid < nb ? static_cast<double>(n) * kEps * diag0[j0 + tid] : 0.0;
+    rinv[tid] = 0.0;
   }
-  __syncthreads();
-  for (int kk = 0; kk < nb; ++kk) {
-    const double piv = S[kk + kk * LD];
-    if (!(piv > static_cast<double>(n) * kEps * diag0[j0 + kk])) {  // uniform across the workgroup
-      if (blockIdx.x == 0 && tid == 0) *flag = 1;
-      return;
+  for (int e = tid; e < kPanel * LD; e += 256) S[e] = 0.0;
+  lds_barrier();
+  bool ok = true;
+  auto half = [&](auto hc) {
+    constexpr int H = decltype(hc)::value;
+    for (int kq = 0; kq < 16; ++kq) {
+      const int kk = 16 * H + kq;
+      if (kk >= nb || !ok) return;  // uniform across the workgroup
+      double* rw = row[kk & 1];
+      if (tr == kq) {
+        rw[tc] = a[H][0];
+        rw[tc + 16] = a[H][1];
+      }
+      lds_barrier();
+      const double piv = rw[kk];
+      if (!(piv > floor_[kk])) {
+        ok = false;
+        return;
+      }
+      const double ip = 1.0 / piv;
+      double u[2], v[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        u[i] = rw[tr + 16 * i] * ip;
+        v[i] = rw[tc + 16 * i];
+      }
+      if (tr == kq) {  // the scaled row
+        const double r = sqrt(piv), ri = 1.0 / r;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int q = tc + 16 * j;
+          if (q >= kk) S[kk * LD + q] = q == kk ? r : v[j] * ri;
+        }
+        if (tc == 0) rinv[kk] = ri;
+      }
+      // rows and columns up to kk are done; what they hold is not read again
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) a[i][j] -= u[i] * v[j];
     }
-    const double r = sqrt(piv);
-    __syncthreads();
-    if (tid < nb) {
-      if (tid > kk) S[kk + tid * LD] /= r;
-      if (tid == kk) S[kk + kk * LD] = r;
-    }
-    __syncthreads();
-    for (int e = tid; e < kPanel * kPanel; e += 256) {
-      const int i = e % kPanel, j = e / kPanel;
-      if (i > kk && i <= j && j < nb) S[i + j * LD] -= S[kk + i * LD] * S[kk + j * LD];
-    }
-    __syncthreads();
+  };
+  half(std::integral_constant<int, 0>{});
+  half(std::integral_constant<int, 1>{});
+  if (!ok) {
+    if (blockIdx.x == 0 && tid == 0) *flag = 1;
+    return;
   }
+  lds_barrier();
   if (blockIdx.x == 0) {
     for (int e = tid; e < nb * nb; e += 256) {
       const int i = e % nb, j = e / nb;
-      R[(j0 + i) + static_cast<int64_t>(j0 + j) * n] = (i <= j) ? S[i + j * LD] : 0.0;
+      R[(j0 + i) + static_cast<int64_t>(j0 + j) * n] = (i <= j) ? S[i * LD + j] : 0.0;
     }
     return;
   }
-  const int c = j0 + nb + (blockIdx.x - 1) * 256 + tid;
-  if (c >= n) return;
-  const double* a = A + static_cast<int64_t>(c) * n + j0;
-  double x[kPanel];
+  if (!solves) return;
 #pragma unroll
   for (int i = 0; i < kPanel; ++i) {
-    if (i < nb) {
-      double s = a[i];
+    x[i] *= rinv[i];
+    // row i's address behind x_i: hoisting every row's LDS reads spills them
+    int o = i * LD;
+    asm("" : "+v"(o) : "v"(x[i]));
 #pragma unroll
-      for (int l = 0; l < i; ++l) s -= S[l + i * LD] * x[l];
-      x[i] = s / S[i + i * LD];
-    } else {
-      x[i] = 0.0;
-    }
+    for (int l = i + 1; l < kPanel; ++l) x[l] -= S[o + l] * x[i];
   }
   double* out = R + static_cast<int64_t>(c) * n + j0;
 #pragma unroll
@@ -516,128 +570,167 @@ __global__ __launch_bounds__(256) void trd_step_wave_kernel(double* __restrict__
   if (lane == 0) pcur[iown] = t * acc;
 }
 
-// The last m = n - k0 <= kTrdTail steps of the tridiagonalisation in one
-// workgroup: the trailing m x m block (with step k0-1's deferred update
-// applied on load) lives in LDS, column stride m + 2, and each step forms its
-// reflector, p = tau A v, w = p - (tau/2)(p^T v) v and the rank-2 update
-// there, with workgroup barriers in place of kernel boundaries.  Writes the
-// same tau, d, e and Householder columns as the per-step kernels, and the
-// final block back to A (its last diagonal entry is T's).
-constexpr int kTailThreads = 1024;  // 16 waves: short dependent chains per lane, latency hidden across waves
-__global__ __launch_bounds__(kTailThreads) void trd_tail_kernel(double* __restrict__ A, int n, int k0,
-                                                                double* __restrict__ Vh, double* __restrict__ tau,
-                                                                double* __restrict__ d, double* __restrict__ e,
-                                                                const double* __restrict__ vbuf,
-                                                                const double* __restrict__ pbuf,
-                                                                const int32_t* __restrict__ flag) {
-  constexpr int NT = kTailThreads, NW = NT / 64;
-  extern __shared__ double sm[];
-  __shared__ double red[2 * NW];  // two halves, used in turn: one barrier per sum
+// The last m = n - k0 <= 16 TC steps of the tridiagonalisation in one
+// workgroup, the trailing m x m block (with step k0-1's deferred update applied
+// on load) in registers: lane (tr, tc) of a GR x 16 arrangement holds rows
+// tr + GR i (i < TR) and columns tc + 16 j (j < TC), GR TR = 16 TC.  A step
+// puts column k into LDS; every wavefront forms the reflector from it by
+// itself (the sums are butterflies, every wave gets the same bits), q = A v is
+// a sum over 16 lanes, goes through LDS once, and p = tau q, w = p - (tau/2)
+// (p^T v) v and the rank-2 update follow: two barriers a step.  Steps run in
+// groups of 16 with compile-time register indices, so finished rows and
+// columns drop out of the loops.  A step is a latency chain (two wave sums, a
+// square root, a division, two LDS round trips): 0.8 us at m = 31, 1.1 us at
+// m = 128 and 1.9 us at m = 192, against 3.1 us at 128 with the block in LDS
+// and 4.7 us for a launch a step.  Writes the same tau, d, e and Householder columns as the per-step
+// kernels, and T's last diagonal entry to A.
+template <int GR, int TR, int TC>
+__global__ __launch_bounds__(GR * 16) void trd_tail_kernel(double* __restrict__ A, int n, int k0,
+                                                           double* __restrict__ Vh, double* __restrict__ tau,
+                                                           double* __restrict__ d, double* __restrict__ e,
+                                                           const double* __restrict__ vbuf,
+                                                           const double* __restrict__ pbuf,
+                                                           const int32_t* __restrict__ flag) {
+  constexpr int M = 16 * TC, ML = (M + 63) / 64;
+  static_assert(GR * TR == M, "square block");
+  __shared__ double col[64 * ML], qb[64 * ML];
   if (*flag) return;
-  const int m = n - k0, ld = m + 2, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  double* As = sm;  // m columns of ld
-  double* vs = sm + static_cast<int64_t>(m) * ld;
-  double* ps = vs + m;  // p, then w
-  int phase = 0;
-  // fixed-order workgroup sum with one barrier; red's halves alternate
-  auto bsum = [&](double v) {
-    v = wave_sum(v);
-    double* rr = red + NW * (phase & 1);
-    ++phase;
-    if (lane == 0) rr[wv] = v;
-    __syncthreads();
-    double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-    for (int q = 0; q < NW; q += 2) {
-      s0 += rr[q];
-      s1 += rr[q + 1];
-    }
-    return s0 + s1;
-  };
+  const int m = n - k0, tid = threadIdx.x, lane = tid & 63, tr = tid >> 4, tc = tid & 15;
+  double a[TR][TC];
+  // step k0-1's v and w = p - (tau/2)(p^T v) v
+  double K = 0.0;
+  const double* vprev = vbuf + ((k0 - 1) & 1) * static_cast<int64_t>(n) + k0;
+  const double* pprev = pbuf + ((k0 - 1) & 1) * static_cast<int64_t>(n) + k0;
   if (k0 > 0) {
-    const double* vprev = vbuf + ((k0 - 1) & 1) * static_cast<int64_t>(n);
-    const double* pprev = pbuf + ((k0 - 1) & 1) * static_cast<int64_t>(n);
     double part = 0.0;
-    for (int r = tid; r < m; r += NT) {
-      const double vv = vprev[k0 + r], pp = pprev[k0 + r];
-      vs[r] = vv;
-      ps[r] = pp;
-      part += pp * vv;
-    }
-    const double K = 0.5 * tau[k0 - 1] * bsum(part);
-    for (int r = tid; r < m; r += NT) ps[r] -= K * vs[r];
-    __syncthreads();
+    for (int r = lane; r < m; r += 64) part += pprev[r] * vprev[r];
+    K = 0.5 * tau[k0 - 1] * wave_sum(part);
   }
-  for (int c = wv; c < m; c += NW) {
-    const double* src = A + k0 + static_cast<int64_t>(k0 + c) * n;
-    const double pc = (k0 > 0) ? ps[c] : 0.0, vc = (k0 > 0) ? vs[c] : 0.0;
-    for (int r = lane; r < m; r += 64) {
-      double x = src[r];
-      if (k0 > 0) x -= vs[r] * pc + ps[r] * vc;
-      As[r + c * ld] = x;
+#pragma unroll
+  for (int j = 0; j < TC; ++j) {
+    const int c = tc + 16 * j;
+    double vc = 0.0, wc = 0.0;
+    if (k0 > 0 && c < m) {
+      vc = vprev[c];
+      wc = pprev[c] - K * vc;
     }
-  }
-  __syncthreads();
-  for (int k = 0; k + 1 < m; ++k) {
-    const double* colk = As + k * ld;
-    const double dk = colk[k], alpha = colk[k + 1];
-    const int rk = k + 2 + tid;
-    const double ck = (rk < m) ? colk[rk] : 0.0;
-    const double sig = bsum(ck * ck);
-    double t = 0.0, beta = alpha, sc = 0.0;
-    if (sig > 0.0) {
-      beta = -copysign(sqrt(alpha * alpha + sig), alpha);
-      t = (beta - alpha) / beta;
-      sc = 1.0 / (alpha - beta);
-    }
-    {
-      const int r = k + 1 + tid;
-      if (r < m) {
-        const double v = (r == k + 1) ? 1.0 : (sig > 0.0 ? colk[r] * sc : 0.0);
-        vs[r] = v;
-        Vh[(k0 + r) + static_cast<int64_t>(k0 + k) * n] = v;
+#pragma unroll
+    for (int i = 0; i < TR; ++i) {
+      const int r = tr + GR * i;
+      double x = 0.0;
+      if (r < m && c < m) {
+        x = A[(k0 + r) + static_cast<int64_t>(k0 + c) * n];
+        if (k0 > 0) {
+          const double vr = vprev[r];
+          x -= vr * wc + (pprev[r] - K * vr) * vc;
+        }
       }
+      a[i][j] = x;
     }
-    if (tid == 0) {
-      tau[k0 + k] = t;
-      d[k0 + k] = dk;
-      e[k0 + k] = beta;
-    }
-    __syncthreads();
-    // p_i = t sum_{j > k} A_ji v_j (a row of 16 lanes per column i > k) and
-    // K = (t/2) p^T v
-    double kpart = 0.0;
-    for (int i0 = k + 1; i0 < m; i0 += NT / 16) {
-      const int i = i0 + (tid >> 4), h = tid & 15;
-      double acc = 0.0;
-      if (i < m) {
-        const double* col = As + i * ld;
-        for (int r = k + 1 + h; r < m; r += 16) acc += col[r] * vs[r];
-      }
-      acc = row_sum(acc);
-      if (i < m && h == 0) {
-        const double pi = t * acc;
-        ps[i] = pi;
-        kpart += pi * vs[i];
-      }
-    }
-    const double K = 0.5 * t * bsum(kpart);
-    // A -= v w^T + w v^T with w = p - K v; lane rows r0, r0 + 64, wave columns
-    const int r0 = k + 1 + lane, r1 = r0 + 64;
-    const double v0 = (r0 < m) ? vs[r0] : 0.0, w0 = (r0 < m) ? ps[r0] - K * v0 : 0.0;
-    const double v1 = (r1 < m) ? vs[r1] : 0.0, w1 = (r1 < m) ? ps[r1] - K * v1 : 0.0;
-    for (int c = k + 1 + wv; c < m; c += NW) {
-      const double vc = vs[c], wc = ps[c] - K * vc;
-      double* col = As + c * ld;
-      if (r0 < m) col[r0] -= v0 * wc + w0 * vc;
-      if (r1 < m) col[r1] -= v1 * wc + w1 * vc;
-    }
-    __syncthreads();
   }
-  for (int c = wv; c < m; c += NW) {
-    double* dst = A + k0 + static_cast<int64_t>(k0 + c) * n;
-    for (int r = lane; r < m; r += 64) dst[r] = As[r + c * ld];
-  }
+  for (int r = tid; r < 64 * ML; r += GR * 16) col[r] = qb[r] = 0.0;
+  lds_barrier();
+  // steps 16 JK .. 16 JK + 15; rows below GR IK and columns below 16 JK are done
+  auto group = [&](auto jkc) {
+    constexpr int JK = decltype(jkc)::value, IK = JK * 16 / GR;
+    for (int kk = 0; kk < 16; ++kk) {
+      const int k = 16 * JK + kk;
+      if (k + 1 >= m) return;  // uniform
+      if (tc == kk) {
+#pragma unroll
+        for (int i = IK; i < TR; ++i) col[tr + GR * i] = a[i][JK];
+      }
+      lds_barrier();
+      double cl[ML], vr[TR], vc[TC];
+#pragma unroll
+      for (int q = 0; q < ML; ++q) cl[q] = col[lane + 64 * q];
+#pragma unroll
+      for (int i = IK; i < TR; ++i) vr[i] = col[tr + GR * i];
+#pragma unroll
+      for (int j = JK; j < TC; ++j) vc[j] = col[tc + 16 * j];
+      const double dk = col[k], alpha = col[k + 1];
+      double part = 0.0;
+#pragma unroll
+      for (int q = 0; q < ML; ++q) {
+        if (lane + 64 * q >= m) cl[q] = 0.0;
+        if (lane + 64 * q >= k + 2) part += cl[q] * cl[q];
+      }
+      const double sig = wave_sum(part);
+      double t = 0.0, beta = alpha, sc = 0.0;
+      if (sig > 0.0) {
+        beta = -copysign(sqrt(alpha * alpha + sig), alpha);
+        t = (beta - alpha) / beta;
+        sc = 1.0 / (alpha - beta);
+      }
+      auto refl = [&](int r, double c) { return r > k + 1 ? c * sc : (r == k + 1 ? 1.0 : 0.0); };
+#pragma unroll
+      for (int q = 0; q < ML; ++q) cl[q] = refl(lane + 64 * q, cl[q]);
+#pragma unroll
+      for (int i = IK; i < TR; ++i) vr[i] = refl(tr + GR * i, vr[i]);
+#pragma unroll
+      for (int j = JK; j < TC; ++j) vc[j] = refl(tc + 16 * j, vc[j]);
+      double qr[TR];
+#pragma unroll
+      for (int i = IK; i < TR; ++i) {
+        double acc = 0.0;
+#pragma unroll
+        for (int j = JK; j < TC; ++j) acc += a[i][j] * vc[j];
+        qr[i] = row_sum(acc);
+      }
+      if (tc == 0) {
+#pragma unroll
+        for (int i = IK; i < TR; ++i) qb[tr + GR * i] = qr[i];
+      }
+      if (tid < 64) {
+        if (lane == 0) {
+          tau[k0 + k] = t;
+          d[k0 + k] = dk;
+          e[k0 + k] = beta;
+        }
+#pragma unroll
+        for (int q = 0; q < ML; ++q) {
+          const int r = lane + 64 * q;
+          if (r > k && r < m) Vh[(k0 + r) + static_cast<int64_t>(k0 + k) * n] = cl[q];
+        }
+      }
+      lds_barrier();
+      double qc[TC];
+#pragma unroll
+      for (int j = JK; j < TC; ++j) qc[j] = qb[tc + 16 * j];
+      double pv = 0.0;
+#pragma unroll
+      for (int q = 0; q < ML; ++q) pv += qb[lane + 64 * q] * cl[q];
+      const double kq = 0.5 * t * t * wave_sum(pv);
+      // w = t q - kq v; rows and columns up to k are done (v is zero there)
+#pragma unroll
+      for (int i = IK; i < TR; ++i) qr[i] = tr + GR * i > k ? t * qr[i] - kq * vr[i] : 0.0;
+#pragma unroll
+      for (int j = JK; j < TC; ++j) qc[j] = tc + 16 * j > k ? t * qc[j] - kq * vc[j] : 0.0;
+#pragma unroll
+      for (int i = IK; i < TR; ++i)
+#pragma unroll
+        for (int j = JK; j < TC; ++j) a[i][j] -= vr[i] * qc[j] + qr[i] * vc[j];
+    }
+  };
+  using std::integral_constant;
+  group(integral_constant<int, 0>{});
+  if constexpr (TC > 1) group(integral_constant<int, 1>{});
+  if constexpr (TC > 2) group(integral_constant<int, 2>{});
+  if constexpr (TC > 3) group(integral_constant<int, 3>{});
+  if constexpr (TC > 4) group(integral_constant<int, 4>{});
+  if constexpr (TC > 5) group(integral_constant<int, 5>{});
+  if constexpr (TC > 6) group(integral_constant<int, 6>{});
+  if constexpr (TC > 7) group(integral_constant<int, 7>{});
+  if constexpr (TC > 8) group(integral_constant<int, 8>{});
+  if constexpr (TC > 9) group(integral_constant<int, 9>{});
+  if constexpr (TC > 10) group(integral_constant<int, 10>{});
+  if constexpr (TC > 11) group(integral_constant<int, 11>{});
+  static_assert(TC <= 12, "groups above");
+#pragma unroll
+  for (int i = 0; i < TR; ++i)
+#pragma unroll
+    for (int j = 0; j < TC; ++j)
+      if (tr + GR * i == m - 1 && tc + 16 * j == m - 1) A[(n - 1) + static_cast<int64_t>(n - 1) * n] = a[i][j];
 }
 
 // T's last diagonal entry, |T|_1, negligible off-diagonals set to zero
@@ -1185,7 +1278,7 @@ __global__ __launch_bounds__(256) void bt_wy_kernel(const double* __restrict__ Z
 // The same for larger n: each of eight wavefronts holds one column in
 // registers (ZR values a lane, ZR >= n / 64), and LDS holds only the block's
 // NB reflectors and T, the next block's being loaded meanwhile.  LDS reads of
-// the reflectors bound it: n = 1,201 (NB 16) BTMS ms, against 5.1 ms one
+// the reflectors bound it: n = 1,201 (NB 16) 1.15 ms, against 5.1 ms one
 // reflector at a time from LDS columns.
 constexpr int kWyRegThreads = 512;
 template <int ZR, int NB>
@@ -1245,8 +1338,8 @@ __global__ __launch_bounds__(kWyRegThreads) void bt_wy_reg_kernel(const double* 
     double acc[NB];
 #pragma unroll
     for (int q = 0; q < NB; ++q) acc[q] = 0.0;
-    // the memory clobbers keep the compiler from hoisting every row's LDS reads
-    // above the first row (and spilling them)
+    // the scheduling barriers keep every row's LDS reads from being hoisted
+    // above the first row (and spilled)
 #pragma unroll
     for (int i = 0; i < ZR; ++i) {
       if (i >= i0) {
@@ -1254,7 +1347,7 @@ __global__ __launch_bounds__(kWyRegThreads) void bt_wy_reg_kernel(const double* 
 #pragma unroll
         for (int q = 0; q < NB; ++q) acc[q] += row[q * LD] * z[i];
       }
-      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
     }
     double u[NB];
 #pragma unroll
@@ -1275,7 +1368,7 @@ __global__ __launch_bounds__(kWyRegThreads) void bt_wy_reg_kernel(const double* 
         for (int q = 0; q < NB; ++q) t += row[q * LD] * u[q];
         z[i] -= t;
       }
-      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
   if (c < n) {
@@ -1482,10 +1575,17 @@ int dense_geneig(DenseWork& w, const double* Hs, const double* M, double* Y, hip
   }
   if (n > 1) {
     const int m = n - k0;
-    const size_t tail_smem = (static_cast<size_t>(m) * (m + 2) + 2 * static_cast<size_t>(m)) * sizeof(double);
-    set_smem(reinterpret_cast<const void*>(trd_tail_kernel), tail_smem);
-    hipLaunchKernelGGL(trd_tail_kernel, dim3(1), dim3(kTailThreads), tail_smem, st, w.C0, n, k0, w.Vh, tau, d, e, vbuf, pbuf,
-                       w.flag);
+    auto tail = [&](auto kern, int threads) {
+      hipLaunchKernelGGL(kern, dim3(1), dim3(threads), 0, st, w.C0, n, k0, w.Vh, tau, d, e, vbuf, pbuf, w.flag);
+    };
+    if (m <= 32)
+      tail(trd_tail_kernel<16, 2, 2>, 256);
+    else if (m <= 64)
+      tail(trd_tail_kernel<16, 4, 4>, 256);
+    else if (m <= 128)
+      tail(trd_tail_kernel<16, 8, 8>, 256);
+    else
+      tail(trd_tail_kernel<32, 6, 12>, 512);
   }
   XLS_LAUNCH_CHECK("trd_step_kernel");
   // --- tridiagonal eigenproblem ---
