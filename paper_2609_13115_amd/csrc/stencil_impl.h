@@ -24,7 +24,7 @@ namespace stencil_detail {
 
 constexpr int R = kRadius;
 constexpr int Q = 2 * R + 1;  // register-queue depth
-constexpr int HMAX = 4;       // halo cells per thread per plane (host checks)
+constexpr int HMAX = 4;       // halo cells per thread per plane at most (host checks)
 constexpr int EMAX = 1;       // reverse-CSR entries per point prefetched (more: slow path)
 constexpr int EMASK = (1 << 27) - 1;
 constexpr int kResidSums = 3;  // residual sweep partial planes: ||H y - lam y||^2, y^T H y, y^T y
@@ -208,9 +208,20 @@ __device__ __forceinline__ Ent4<double> load_ent<double>(__amdgpu_buffer_rsrc_t 
 // HF (half-input filter steps of a warm start): bit 0, y (Y_k) is binary16
 // with leading dimension ld16; bit 1, yprev (Y_{k-1}) is.  The output and
 // the arithmetic keep TS / TC.
-template <typename TS, typename TC, int MODE, int P, int NT, int WS, int NV, int HF = 0>
+// HM: halo cells a lane loads and stages per plane (3 where the tile's halo
+// fits, else 4: the fourth would be an unused load and LDS write; FP64 64^3 x
+// 480 855 -> 822 us with it gone).
+// PAIR (FP32 arithmetic, two points a lane, rows of whole 128-byte lines): the
+// lane's points are consecutive rows, whose y neighbours overlap: 12 LDS reads
+// serve both points, own rows come from registers, where separate rows take 24
+// (the LDS pipe is the busiest one in FP32: 64^3 x 480 424 -> 374 us).  With
+// other row lengths the pairs break up the lanes' contiguous loads (43^3 360
+// -> 423 us, 80^3 323 -> 335 for 9e7 points), and in FP64 the shared run costs
+// 56 registers and spills: there lanes own points one workgroup apart.
+template <typename TS, typename TC, int MODE, int P, int NT, int WS, int NV, int HF, int HM, bool PAIR>
 __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t logical, TC ca, TC cc, TC cb,
                                              unsigned char* smem_raw) {
+  static_assert(!PAIR || (P == 2 && sizeof(TC) == 4), "row pairs: two points a lane, FP32");
   static_assert(NV == 1 || MODE != kResid, "residual sweeps take one column per tile");
   static_assert(HF == 0 || MODE == kFilter, "binary16 inputs only in filter steps");
   TC* lds = reinterpret_cast<TC*>(smem_raw);
@@ -274,26 +285,39 @@ __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t lo
   int vo[P], os[P], oy[P], opv[P], oc[P], o4[P], li[P], lr[P];
 #pragma unroll
   for (int i = 0; i < P; ++i) {
-    const int lin = tid + i * NT;
-    const bool act = lin < npts;
-    const int x = act ? lin % nx : 0, yy = act ? y0 + lin / nx : y0;
+    int x, yy;
+    bool act;
+    if constexpr (PAIR) {
+      x = tid % nx;
+      yy = y0 + (tid / nx) * P + i;
+      act = yy < y0 + tyv;
+    } else {
+      const int lin = tid + i * NT;
+      act = lin < npts;
+      x = act ? lin % nx : 0;
+      yy = act ? y0 + lin / nx : y0;
+    }
     vo[i] = act ? (x + nx * yy) : -1;
     os[i] = act ? vo[i] * ES : kOOB;
     oy[i] = act ? vo[i] * ESY : kOOB;
+    // a pair's second row past the tile's last: its partner reads it as a
+    // neighbour (the next tile's row, the wrapped one, or zero beyond a face)
+    if (PAIR && !act && (yy < ny || A.periodic)) oy[i] = (x + nx * wrapi(yy, ny)) * ESY;
     opv[i] = act ? vo[i] * ESP : kOOB;
     oc[i] = act ? vo[i] * EC : kOOB;
     o4[i] = act ? vo[i] * 4 : kOOB;
     li[i] = act ? (R + yy - y0) * W + R + x : dumpi;
     lr[i] = (R + yy - y0) * W + R + x;
+    if (PAIR && yy - i >= y0 + tyv) lr[i] = (R + i) * W + R + x;  // inactive pair: in-range reads, nothing stored
   }
 
   // halo cells of a plane (y-halo rows, then periodic x-halo columns): LDS
   // target (dump when unused) and source byte offset (kOOB reads zero)
   const int nhy = 2 * R * nx;
   const int nh = nhy + (A.periodic ? 2 * R * tyv : 0);
-  int hl[HMAX], hoff[HMAX];
+  int hl[HM], hoff[HM];
 #pragma unroll
-  for (int j = 0; j < HMAX; ++j) {
+  for (int j = 0; j < HM; ++j) {
     const int e = tid + j * NT;
     hl[j] = dumpi;
     hoff[j] = kOOB;
@@ -382,7 +406,7 @@ __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t lo
   TC fr[P][NV], yp1[P][NV], yp2[P][NV], vn[P];
   int rp1[P], rp2[P], ea[P];
   Ent4<TC> ev[P];
-  TC hv[NV][HMAX];
+  TC hv[NV][HM];
   auto load_rest = [&](int z) {  // V, entry payload, rev word (z+1) of plane z
     const int so = z * pp;
 #pragma unroll
@@ -415,7 +439,7 @@ __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t lo
 #pragma unroll
   for (int v = 0; v < NV; ++v)
 #pragma unroll
-    for (int j = 0; j < HMAX; ++j) hv[v][j] = ldy(v, hoff[j], z0 * pp);
+    for (int j = 0; j < HM; ++j) hv[v][j] = ldy(v, hoff[j], z0 * pp);
 
   // residual sweep: ||H y - lam y||^2, y^T H y and y^T y of the column (the
   // last two give its FP64 Rayleigh quotient)
@@ -433,16 +457,27 @@ __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t lo
 #pragma unroll
       for (int i = 0; i < P; ++i) buf[2 * v * plane + li[i]] = q[i][v][QS(R)];
 #pragma unroll
-      for (int j = 0; j < HMAX; ++j) buf[2 * v * plane + hl[j]] = hv[v][j];
+      for (int j = 0; j < HM; ++j) buf[2 * v * plane + hl[j]] = hv[v][j];
     }
     // (b) next plane's halo
 #pragma unroll
     for (int v = 0; v < NV; ++v)
 #pragma unroll
-      for (int j = 0; j < HMAX; ++j) hv[v][j] = ldy(v, hoff[j], clampz(z + 1) * pp);
+      for (int j = 0; j < HM; ++j) hv[v][j] = ldy(v, hoff[j], clampz(z + 1) * pp);
     lds_barrier();
     // (c) plane z
     const int so = z * pp * ES;
+    TC yr[NV][PAIR ? 2 * R + P : 1];  // paired rows: y - 6 .. y + 7 of the lane's first row
+    if constexpr (PAIR) {
+      int byi = lr[0] - R * W;
+      asm("" : "+v"(byi));
+#pragma unroll
+      for (int v = 0; v < NV; ++v)
+#pragma unroll
+        for (int e = 0; e < 2 * R + P; ++e)
+          yr[v][e] = (e >= R && e < R + P) ? q[e < R ? 0 : (e >= R + P ? P - 1 : e - R)][v][QS(R)]
+                                           : (buf + 2 * v * plane + byi)[e * W];
+    }
 #pragma unroll
     for (int i = 0; i < P; ++i) {
       // two bases behind opaque registers, the row and the column of the
@@ -461,8 +496,12 @@ __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t lo
         TC lap = A.wc * ctr;
 #pragma unroll
         for (int p = 1; p <= R; ++p) {
-          const TC sm = (bx[R + p] + bx[R - p]) + (by[(R + p) * W] + by[(R - p) * W]) +
-                        (q[i][v][QS(R + p)] + q[i][v][QS(R - p)]);
+          TC sy;
+          if constexpr (PAIR)
+            sy = yr[v][R + i + p] + yr[v][R + i - p];
+          else
+            sy = by[(R + p) * W] + by[(R - p) * W];
+          const TC sm = (bx[R + p] + bx[R - p]) + sy + (q[i][v][QS(R + p)] + q[i][v][QS(R - p)]);
           lap += A.w[p - 1] * sm;
         }
         hy[v] = lap + vn[i] * ctr;
@@ -559,10 +598,10 @@ __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t lo
   }
 }
 
-template <typename TS, typename TC, int MODE, int P, int NT, int WS, int NV, int HF = 0>
+template <typename TS, typename TC, int MODE, int P, int NT, int WS, int NV, int HF, int HM, bool PAIR>
 __global__ __launch_bounds__(NT) void hstencil_kernel(HArgs<TS, TC> A) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  stencil_tile<TS, TC, MODE, P, NT, WS, NV, HF>(A, xcd_remap(blockIdx.x, gridDim.x), A.a, A.c, A.b, smem_raw);
+  stencil_tile<TS, TC, MODE, P, NT, WS, NV, HF, HM, PAIR>(A, xcd_remap(blockIdx.x, gridDim.x), A.a, A.c, A.b, smem_raw);
 }
 
 // Grouped persistent filter step over many operators: item = (operator,
@@ -570,7 +609,7 @@ __global__ __launch_bounds__(NT) void hstencil_kernel(HArgs<TS, TC> A) {
 // xcd remap gives the workgroups of one XCD consecutive items, so the tiles
 // that share halo rows meet in the same L2.  Step k reads its recurrence
 // coefficients from the operator's device table.
-template <typename TS, typename TC, int P, int NT, int WS, int NV>
+template <typename TS, typename TC, int P, int NT, int WS, int NV, int HM, bool PAIR>
 __global__ __launch_bounds__(NT) void hstencil_group_kernel(const HArgs<TS, TC>* __restrict__ tab,
                                                             const uint2* __restrict__ items, int nitems,
                                                             int k) {
@@ -580,7 +619,7 @@ __global__ __launch_bounds__(NT) void hstencil_group_kernel(const HArgs<TS, TC>*
     const uint2 w = items[it];
     const HArgs<TS, TC> A = tab[w.x];
     const double* cf = A.coef + 3 * k;
-    stencil_tile<TS, TC, kFilter, P, NT, WS, NV>(A, w.y, static_cast<TC>(cf[0]), static_cast<TC>(cf[1]),
+    stencil_tile<TS, TC, kFilter, P, NT, WS, NV, 0, HM, PAIR>(A, w.y, static_cast<TC>(cf[0]), static_cast<TC>(cf[1]),
                                              static_cast<TC>(cf[2]), smem_raw);
     __syncthreads();
   }
@@ -736,7 +775,8 @@ __global__ __launch_bounds__(256) void proj_forward_group_kernel(const PArgs<TS,
 }
 
 struct TileChoice {
-  int block, ty, nyt, tz, nzt, P, ws, nv;
+  int block, ty, nyt, tz, nzt, P, ws, nv, hm;
+  bool pair;
   size_t smem;
 };
 
@@ -787,17 +827,30 @@ inline TileChoice choose_tiles(int nx, int ny, int nz, int elem, int nproj, int6
     tc.block = block_of(per_lane);
     ty = default_ty(nx, ny, tc.block, cfg, per_lane);
   }
+  // even bands: 40 rows are four tiles of 10, not three of 12 and one of 4
+  // (FP32 361 -> 346 us for 9e7 points)
+  if (fit && cfg.ty == 0) ty = (ny + (ny + ty - 1) / ty - 1) / ((ny + ty - 1) / ty);
+  tc.P = (nx * ty + tc.block - 1) / tc.block;
+  // FP32 row pairs, where whole pairs of rows fit the workgroup
+  tc.pair = elem == 4 && tc.P == 2 && nx % 32 == 0 && (ty + 1) / 2 * nx <= tc.block;
   tc.ty = ty;
   tc.nyt = (ny + ty - 1) / ty;
-  tc.P = (nx * ty + tc.block - 1) / tc.block;
   tc.ws = (nx + 2 * R <= 80) ? 80 : 128;
   auto smem_of = [&](int nv) {
     return static_cast<size_t>(elem) * nv * (2 * (static_cast<size_t>(tc.ws) * (ty + 2 * R) + 1) + nproj);
   };
-  if (cfg.nv > 0)
+  if (cfg.nv > 0) {
     tc.nv = cfg.nv;
-  else
-    tc.nv = (smem_of(2) <= 160 * 1024 && (!fit || (cols + 1) / 2 * tc.nyt >= kTwoVecWgs)) ? 2 : 1;
+  } else if (!fit) {
+    tc.nv = smem_of(2) <= 160 * 1024 ? 2 : 1;
+  } else {
+    // Two vectors also have to leave two workgroups per CU (FP64 past 68
+    // points a row: 80^3 361 us with one vector, 514 with two), and in FP32
+    // they pay on rows of whole 32-byte sectors only (48 311 -> 295, 80 358 ->
+    // 330 us, but 46 352 -> 366, 50 332 -> 343, 60 338 -> 354, each 9e7 points).
+    const bool fits = smem_of(2) <= 80 * 1024 && (elem == 8 || nx % 8 == 0);
+    tc.nv = (fits && (cols + 1) / 2 * tc.nyt >= kTwoVecWgs) ? 2 : 1;
+  }
   if (fit) {
     const int64_t wgs = (cols + tc.nv - 1) / tc.nv * tc.nyt;
     int64_t nzt;
@@ -813,6 +866,9 @@ inline TileChoice choose_tiles(int nx, int ny, int nz, int elem, int nproj, int6
   }
   tc.nzt = (nz + tc.tz - 1) / tc.tz;
   tc.smem = smem_of(tc.nv);
+  // three halo cells a lane are built for the tiles of the usual boxes only
+  const int halo = 2 * R * nx + (periodic ? 2 * R * ty : 0);
+  tc.hm = (tc.block == 256 && tc.ws == 80 && halo <= 3 * 256) ? 3 : HMAX;
   return tc;
 }
 
@@ -832,22 +888,41 @@ void allow_smem(K kern, size_t smem) {
   ensure_dyn_smem(reinterpret_cast<const void*>(kern), smem);
 }
 
-template <typename TS, typename TC, int MODE, int P, int WS, int NV, int HF>
-void launch_mode(const HArgs<TS, TC>& args, dim3 grid, int block, size_t smem, hipStream_t st) {
-  if (block == 256) {
-    allow_smem(hstencil_kernel<TS, TC, MODE, P, 256, WS, NV, HF>, smem);
-    hipLaunchKernelGGL((hstencil_kernel<TS, TC, MODE, P, 256, WS, NV, HF>), grid, dim3(256), smem, st, args);
-  } else {
-    allow_smem(hstencil_kernel<TS, TC, MODE, P, 512, WS, NV, HF>, smem);
-    hipLaunchKernelGGL((hstencil_kernel<TS, TC, MODE, P, 512, WS, NV, HF>), grid, dim3(512), smem, st, args);
+template <typename TS, typename TC, int MODE, int P, int WS, int NV, int HF, bool PAIR>
+void launch_block(const HArgs<TS, TC>& args, const TileChoice& tc, dim3 grid, size_t smem, hipStream_t st) {
+  auto go = [&](auto kern, int threads) {
+    allow_smem(kern, smem);
+    hipLaunchKernelGGL(kern, grid, dim3(threads), smem, st, args);
+  };
+  if (tc.block == 512) {
+    go(hstencil_kernel<TS, TC, MODE, P, 512, WS, NV, HF, HMAX, PAIR>, 512);
+    return;
   }
+  if constexpr (WS == 80) {
+    if (tc.hm == 3) {
+      go(hstencil_kernel<TS, TC, MODE, P, 256, WS, NV, HF, 3, PAIR>, 256);
+      return;
+    }
+  }
+  go(hstencil_kernel<TS, TC, MODE, P, 256, WS, NV, HF, HMAX, PAIR>, 256);
+}
+
+template <typename TS, typename TC, int MODE, int P, int WS, int NV, int HF>
+void launch_mode(const HArgs<TS, TC>& args, const TileChoice& tc, dim3 grid, size_t smem, hipStream_t st) {
+  if constexpr (P == 2 && sizeof(TC) == 4) {
+    if (tc.pair) {
+      launch_block<TS, TC, MODE, P, WS, NV, HF, true>(args, tc, grid, smem, st);
+      return;
+    }
+  }
+  launch_block<TS, TC, MODE, P, WS, NV, HF, false>(args, tc, grid, smem, st);
 }
 
 template <typename TS, typename TC, int MODE, int WS, int NV, int HF>
 void launch_pnv(const TileChoice& tc, const HArgs<TS, TC>& args, dim3 grid, size_t smem, hipStream_t st) {
   switch (tc.P) {
-    case 1: launch_mode<TS, TC, MODE, 1, WS, NV, HF>(args, grid, tc.block, smem, st); break;
-    case 2: launch_mode<TS, TC, MODE, 2, WS, NV, HF>(args, grid, tc.block, smem, st); break;
+    case 1: launch_mode<TS, TC, MODE, 1, WS, NV, HF>(args, tc, grid, smem, st); break;
+    case 2: launch_mode<TS, TC, MODE, 2, WS, NV, HF>(args, tc, grid, smem, st); break;
     default: fail(XLS_ERR_INVALID_ARG, "stencil tile needs more than 2 points per thread");
   }
 }
@@ -1067,7 +1142,8 @@ inline void group_release(void* p) {
 template <typename TS>
 struct FilterGroup {
   struct Bucket {
-    int P = 1, block = 256, ws = 80, nv = 1;
+    int P = 1, block = 256, ws = 80, nv = 1, hm = HMAX;
+    bool pair = false;
     size_t smem = 0;
     uint2* items = nullptr;
     std::vector<int> count;  // items taking part in step k
@@ -1082,39 +1158,59 @@ struct FilterGroup {
   int steps = 0;
 };
 
-template <typename TS, int P, int NT, int WS, int NV>
-int group_occupancy(size_t smem) {
-  allow_smem(hstencil_group_kernel<TS, TS, P, NT, WS, NV>, smem);
+template <typename K>
+int group_occupancy(K kern, int threads, size_t smem) {
+  allow_smem(kern, smem);
   int nb = 0;
-  XLS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(
-      &nb, reinterpret_cast<const void*>(hstencil_group_kernel<TS, TS, P, NT, WS, NV>), NT, smem));
+  XLS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, reinterpret_cast<const void*>(kern), threads, smem));
   return std::max(1, nb);
 }
 
-// one grouped launch shape: calls f with compile-time (P, WS, NV) of bucket b
-template <typename F>
-void group_dispatch(int P, int ws, int nv, F&& f) {
+// calls f(kernel, threads) with the grouped kernel of a bucket's shape
+template <typename TS, typename BK, typename F>
+void group_dispatch(const BK& b, F&& f) {
   using std::integral_constant;
+  auto by_hm = [&](auto pc, auto wc, auto vc, auto rc) {
+    constexpr int PP = decltype(pc)::value, WW = decltype(wc)::value, VV = decltype(vc)::value;
+    constexpr bool RR = decltype(rc)::value;
+    if (b.block == 512) {
+      f(hstencil_group_kernel<TS, TS, PP, 512, WW, VV, HMAX, RR>, 512);
+      return;
+    }
+    if constexpr (WW == 80) {
+      if (b.hm == 3) {
+        f(hstencil_group_kernel<TS, TS, PP, 256, WW, VV, 3, RR>, 256);
+        return;
+      }
+    }
+    f(hstencil_group_kernel<TS, TS, PP, 256, WW, VV, HMAX, RR>, 256);
+  };
+  auto by_pair = [&](auto pc, auto wc, auto vc) {
+    if constexpr (decltype(pc)::value == 2 && sizeof(TS) == 4) {
+      if (b.pair) {
+        by_hm(pc, wc, vc, std::true_type{});
+        return;
+      }
+    }
+    by_hm(pc, wc, vc, std::false_type{});
+  };
   auto by_nv = [&](auto pc, auto wc) {
-    if (nv == 1) f(pc, wc, integral_constant<int, 1>{});
-    else f(pc, wc, integral_constant<int, 2>{});
+    if (b.nv == 1) by_pair(pc, wc, integral_constant<int, 1>{});
+    else by_pair(pc, wc, integral_constant<int, 2>{});
   };
   auto by_ws = [&](auto pc) {
-    if (ws == 80) by_nv(pc, integral_constant<int, 80>{});
+    if (b.ws == 80) by_nv(pc, integral_constant<int, 80>{});
     else by_nv(pc, integral_constant<int, 128>{});
   };
-  if (P == 1) by_ws(integral_constant<int, 1>{});
-  else if (P == 2) by_ws(integral_constant<int, 2>{});
+  if (b.P == 1) by_ws(integral_constant<int, 1>{});
+  else if (b.P == 2) by_ws(integral_constant<int, 2>{});
   else fail(XLS_ERR_INVALID_ARG, "grouped stencil launches take at most 2 points per thread");
 }
 
-template <typename TS>
-int group_occ(int P, int block, int ws, int nv, size_t smem) {
+template <typename TS, typename BK>
+int group_occ(const BK& b) {
   int nb = 1;
-  group_dispatch(P, ws, nv, [&](auto pc, auto wc, auto vc) {
-    constexpr int PP = decltype(pc)::value, WW = decltype(wc)::value, VV = decltype(vc)::value;
-    nb = block == 256 ? group_occupancy<TS, PP, 256, WW, VV>(smem) : group_occupancy<TS, PP, 512, WW, VV>(smem);
-  });
+  group_dispatch<TS>(b, [&](auto kern, int threads) { nb = group_occupancy(kern, threads, b.smem); });
   return nb;
 }
 
@@ -1122,14 +1218,8 @@ template <typename TS>
 void group_launch(const typename FilterGroup<TS>::Bucket& b, const HArgs<TS, TS>* tab, int n, int k,
                   hipStream_t st) {
   const dim3 grid(static_cast<unsigned>(std::min(n, b.grid_cap)));
-  group_dispatch(b.P, b.ws, b.nv, [&](auto pc, auto wc, auto vc) {
-    constexpr int PP = decltype(pc)::value, WW = decltype(wc)::value, VV = decltype(vc)::value;
-    if (b.block == 256)
-      hipLaunchKernelGGL((hstencil_group_kernel<TS, TS, PP, 256, WW, VV>), grid, dim3(256), b.smem, st, tab,
-                         b.items, n, k);
-    else
-      hipLaunchKernelGGL((hstencil_group_kernel<TS, TS, PP, 512, WW, VV>), grid, dim3(512), b.smem, st, tab,
-                         b.items, n, k);
+  group_dispatch<TS>(b, [&](auto kern, int threads) {
+    hipLaunchKernelGGL(kern, grid, dim3(threads), b.smem, st, tab, b.items, n, k);
   });
 }
 
@@ -1165,7 +1255,8 @@ FilterGroup<TS>* filter_group_build(const std::vector<FilterGroupOp<TS>>& ops) {
       int bi = -1;
       for (size_t j = 0; j < g->buckets.size(); ++j) {
         const auto& b = g->buckets[j];
-        if (b.P == tcs[i].P && b.block == tcs[i].block && b.ws == tcs[i].ws && b.nv == tcs[i].nv)
+        if (b.P == tcs[i].P && b.block == tcs[i].block && b.ws == tcs[i].ws && b.nv == tcs[i].nv &&
+            b.hm == tcs[i].hm && b.pair == tcs[i].pair)
           bi = static_cast<int>(j);
       }
       if (bi < 0) {
@@ -1174,6 +1265,8 @@ FilterGroup<TS>* filter_group_build(const std::vector<FilterGroupOp<TS>>& ops) {
         b.block = tcs[i].block;
         b.ws = tcs[i].ws;
         b.nv = tcs[i].nv;
+        b.hm = tcs[i].hm;
+        b.pair = tcs[i].pair;
         g->buckets.push_back(b);
         bi = static_cast<int>(g->buckets.size()) - 1;
       }
@@ -1247,7 +1340,7 @@ FilterGroup<TS>* filter_group_build(const std::vector<FilterGroupOp<TS>>& ops) {
             return static_cast<int64_t>((ops[i].ncols + tcs[i].nv - 1) / tcs[i].nv) * tcs[i].nyt * tcs[i].nzt;
           },
           b.count, b.items, [&](int i) { return bucket_of[i] == static_cast<int>(bi); });
-      b.grid_cap = group_occ<TS>(b.P, b.block, b.ws, b.nv, b.smem) * cus;
+      b.grid_cap = group_occ<TS>(b) * cus;
     }
     build_items([&](int i) {
       return static_cast<int64_t>(ops[i].op->n_atoms) * ((ops[i].ncols + 4 * kProjCols - 1) / (4 * kProjCols));

@@ -38,3 +38,25 @@ def test_chosen_tiles_match_whole_box_tiles(shape, ns, periodic, prec):
     assert np.array_equal(out[0][0], out[1][0])
     # N_d squares summed in another order: about N_d eps of the sum, twice
     assert np.allclose(out[0][1], out[1][1], rtol=2 * sd.nd * 2.3e-16 + 1e-15, atol=0)
+
+
+# rows of a pair split by a tile's or the box's edge, tiles whose row pairs do
+# not fill the workgroup (row counts trimmed), halo counts on both sides of
+# three cells a lane
+@pytest.mark.parametrize("shape,ns,periodic", [((46, 23, 7), 3, False), ((24, 24, 24), 5, True), ((33, 37, 15), 3, False),
+                                               ((64, 21, 9), 3, False), ((68, 10, 9), 2, False), ((90, 11, 8), 3, False),
+                                               ((20, 20, 20), 4, True), ((62, 62, 62), 1, True)])
+@pytest.mark.parametrize("ty", [0, 3, 7, 8, 11])
+def test_fp32_row_pairs_match_single_rows(shape, ns, periodic, ty):
+    print(f"[case] row pairs {shape} ns={ns} periodic={periodic} ty={ty}", flush=True)
+    sd = box(shape, ns, periodic)
+    block = 256 if 12 * shape[0] + (12 * max(ty, 16) if periodic else 0) <= 1024 else 512
+    if shape[0] * ty > 2 * block:
+        ty = 2 * block // shape[0]
+    out = []
+    for rows in (1, ty):
+        with xls.Subdomain(sd, filter_prec=xls.XLS_PREC_FP32) as s:
+            s.xls_subdomain_tune(xls.XLS_PREC_FP32, block, rows, 0, 2)
+            s.xls_subdomain_filter(3, -3.0, 4.0, 45.0)
+            out.append(s.xls_subdomain_get_block())
+    assert np.array_equal(out[0], out[1])
