@@ -1,0 +1,43 @@
+"""The large-tile products against NumPy, at the edges of their tiles.
+
+Row tiles of 64 and 128, column tiles of 96 and 128, a k slab that ends short
+(odd orders and odd point counts) and orders just past a tile."""
+import numpy as np
+import pytest
+
+from paper_2609_13115_amd import xls
+from test_gpu_tiles import box
+
+pytestmark = pytest.mark.gpu
+
+
+def rel_err(a, b):
+    return float(np.max(np.abs(a - b)) / np.max(np.abs(b)))
+
+
+# 8211 points: 64-row tiles; 33759 points with 190 or 250 columns: 128-row
+# tiles.  The sums have K terms of either sign, so their rounding is about
+# sqrt(K) eps of the largest entry and K eps in the worst case; an FP32 block
+# stores the rotated block in FP32.
+@pytest.mark.parametrize("shape,ns", [((17, 21, 23), 64), ((17, 21, 23), 97), ((17, 21, 23), 129),
+                                      ((33, 33, 31), 190), ((33, 33, 31), 250)])
+@pytest.mark.parametrize("prec,gprec", [(xls.XLS_PREC_FP64, xls.XLS_PREC_FP64), (xls.XLS_PREC_FP32, xls.XLS_PREC_FP64),
+                                        (xls.XLS_PREC_FP32, xls.XLS_PREC_FP32)])
+def test_large_tile_products(shape, ns, prec, gprec):
+    print(f"[case] large tile products {shape} ns={ns} prec={prec} gemm={gprec}", flush=True)
+    sd = box(shape, ns, False)
+    rng = np.random.default_rng(11)
+    X = rng.standard_normal((sd.nd, ns))
+    if prec == xls.XLS_PREC_FP32:
+        X = X.astype(np.float32).astype(np.float64)
+    Q = rng.standard_normal((ns, ns)) / np.sqrt(ns)
+    eps_in = 2.0 ** -24 if gprec == xls.XLS_PREC_FP32 else 2.0 ** -53
+    eps_out = 2.0 ** -24 if prec == xls.XLS_PREC_FP32 else 2.0 ** -53
+    with xls.Subdomain(sd, filter_prec=prec) as s:
+        s.xls_subdomain_set_block(X)
+        M, _ = s.xls_subdomain_project(gprec)
+        s.xls_subdomain_set_block(X)
+        s.xls_subdomain_rotate(Q, gprec)
+        out = s.xls_subdomain_get_block()
+    assert rel_err(M, X.T @ X) <= 16 * np.sqrt(sd.nd) * eps_in
+    assert rel_err(out, X @ Q) <= 16 * np.sqrt(ns) * eps_in + 4 * eps_out
