@@ -305,13 +305,14 @@ int xls_subdomain_tune(xls_subdomain_t s, int32_t prec, int32_t block, int32_t t
  * CU with 128 x 128 tiles, three with 96 x 96; at least 16 k-slabs per
  * split); k in [1, 64] scales it by k/2 (still bounded by K and the
  * workspace).  tile_tn (projection): 0 takes the large-tile MFMA kernel
- * when the shapes allow, with 96 x 96 tiles where they issue at least 10 %
- * less padded and redundant work than 128 x 128 (an order of 480, say) and
- * 128 x 128 otherwise; 1 the 64 x 64 tiles; 2 and 3 force the 128 and 96
- * edges of the large kernel (FP64 products of FP32 blocks always take
- * 128).  tile_nn (rotation): 0 and 3 take the large-tile kernel with
- * 64 x 128 tiles when the shapes allow, 1 the 64 x 64 tiles, 2 the large
- * kernel with 64 x 256 tiles.  A plan changes the
+ * when the shapes allow, with 96 x 96 or 128 x 128 tiles, whichever leaves
+ * the busiest compute unit less to multiply; 1 the 64 x 64 tiles; 2 and 3
+ * force the 128 and 96 edges of the large kernel (FP64 products of FP32
+ * blocks always take 128).  tile_nn (rotation): 0 takes the large-tile
+ * kernel when the shapes allow, 128 rows (64 for short blocks) by 128 or,
+ * where that pads the order less, 96 columns; 3 keeps 128 columns; 1 the
+ * 64 x 64 tiles; 2 the large kernel with 64 x 256 tiles (the split-BF16 form
+ * has 64 x 128 and 64 x 256 only).  A plan changes the
  * order of the split-K partial sums (results stay deterministic per plan),
  * never a product.  INVALID_ARG outside those ranges. */
 int xls_subdomain_tune_gemm(xls_subdomain_t s, int32_t split_scale, int32_t tile_tn, int32_t tile_nn);

@@ -725,8 +725,8 @@ __global__ __launch_bounds__(256, 2) void gemm_tn_big_kernel(const TIN* __restri
 // operand is B (rows of the accumulator = columns of C), so each lane's
 // results for one column are rows m .. m + 15 across lanes (coalesced
 // stores).  TB is the B operand as stored: double (FP64), float (FP32) or
-// bf16 hi/lo pairs (BF; Bh/Bl).  The 128-column tile pads an order such as
-// 300 to 384 instead of 512 and is the default width.
+// bf16 hi/lo pairs (BF; Bh/Bl).  The split-BF16 form takes it at either
+// width; FP64 and FP32 only where a plan forces 256 columns.
 template <typename TIN, typename TB, typename TOUT, int MF, int TN>
 __global__ __launch_bounds__(256, 2) void gemm_nn_big_kernel(const TIN* __restrict__ A, int64_t lda,
                                                           const TB* __restrict__ Bh, const TB* __restrict__ Bl,

@@ -162,10 +162,11 @@ size_t stencil_partial_elems(const OpTables<double>& op, int ncols, const Stenci
 // many workgroups as are resident at once, at least 16 k-slabs per split;
 // the rotation's tiles do not split), k > 0 scales it
 // by k/2; tile_tn 0 takes the large-tile projection kernel when shapes
-// allow (edge 96 or 128, whichever issues less padded work by 10 %), 1 the
+// allow (edge 96 or 128 by the work of the busiest compute unit), 1 the
 // 64 x 64 tiles, 2 and 3 force the 128 and 96 edges; tile_nn 0 takes the
-// large rotation kernel with 64 x 128 tiles when shapes allow (3 too), 1
-// the 64 x 64 tiles, 2 the large kernel with 64 x 256 tiles.
+// large rotation kernel when shapes allow (64 or 128 rows, 96 or 128
+// columns; 3 keeps 128 columns), 1 the 64 x 64 tiles, 2 the large kernel
+// with 64 x 256 tiles.
 // A plan changes the order of the split sums, never a product.
 struct GemmPlan {
   int split_scale = 0;
