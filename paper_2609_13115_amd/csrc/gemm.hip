@@ -474,16 +474,18 @@ struct BigLds {
   static constexpr int PARTS = (MF == MF_BF) ? 2 : 1;
 };
 
-// Position of k value k of row r in an FP64 or FP32 operand whose rows hold
-// one slab of k (128 bytes, eight 16-byte chunks): chunk c sits at
-// c ^ ((r >> 1) & 7), so that 16 rows read at one chunk, and rows written
-// whole, cover the 64 banks once without padding.
+// Rows of an FP64 or FP32 operand hold one slab of k: 128 bytes, eight 16-byte
+// chunks.  Chunk c of row r sits at c ^ ((r >> 1) & 7), so that 16 rows read
+// at one chunk, and rows written whole, cover the 64 banks once without
+// padding.  Lane group q of a wavefront reads chunk 4 g + q: FP32 rows hold
+// k = 16 g + 4 e + q in its element e, so that MFMA step e multiplies four
+// consecutive k values as it would from rows in order (the sums keep their
+// order), and FP64 rows k = 8 g + 2 q + e.
 template <int MF>
-__device__ __forceinline__ int row_off(int r, int k) {
-  using L = typename Form<MF>::lds_t;
-  constexpr int CH = 16 / sizeof(L), BK = BigLds<MF>::BK;
+__device__ __forceinline__ int chunk_off(int r, int c) {
+  constexpr int CH = 16 / sizeof(typename Form<MF>::lds_t), BK = BigLds<MF>::BK;
   static_assert(BK == 8 * CH, "rows of 128 bytes");
-  return r * BK + (((k / CH) ^ ((r >> 1) & 7)) * CH) + k % CH;
+  return r * BK + (c ^ ((r >> 1) & 7)) * CH;
 }
 
 // Writes the VEC k values k .. k + VEC - 1 of row r into an LDS operand
@@ -506,16 +508,16 @@ __device__ __forceinline__ void big_put_row(typename Form<MF>::lds_t* h, typenam
       *reinterpret_cast<uint32_t*>(l + off) = lp[0];
     }
   } else {
-    using L = typename Form<MF>::lds_t;
-    constexpr int CH = 16 / sizeof(L);
-    static_assert(VEC % CH == 0, "whole chunks");
-    using V = __attribute__((ext_vector_type(CH))) L;
+    if constexpr (MF == MF_F32) {
+      static_assert(VEC == 4, "one k value for each lane group");
 #pragma unroll
-    for (int c = 0; c < VEC / CH; ++c) {
-      V w;
+      for (int q = 0; q < 4; ++q) h[chunk_off<MF>(r, k / 16 * 4 + q) + k % 16 / 4] = v[q];
+    } else {
+      using V = __attribute__((ext_vector_type(2))) double;
 #pragma unroll
-      for (int e = 0; e < CH; ++e) w[e] = static_cast<L>(v[c * CH + e]);
-      *reinterpret_cast<V*>(h + row_off<MF>(r, k + c * CH)) = w;
+      for (int c = 0; c < VEC / 2; ++c)
+        *reinterpret_cast<V*>(h + chunk_off<MF>(r, k / 2 + c)) =
+            V{static_cast<double>(v[2 * c]), static_cast<double>(v[2 * c + 1])};
     }
   }
 }
@@ -530,7 +532,7 @@ __device__ __forceinline__ void big_put_row(typename Form<MF>::lds_t* h, typenam
 // a slab is free as long as both operands share it), columns past the edge
 // clamped instead of masked (their sums are not stored) and k masked in the
 // last slab only keep other instructions out of the MFMA stream: FP32 K =
-// 884736, order 1152 12.2 -> 10.7 ms (120 TFLOP/s of the tiles computed, 106
+// 884736, order 1152 12.2 -> 10.8 ms (121 TFLOP/s of the tiles computed, 106
 // before; a library product reaches 154), FP64 K = 262144, order 480 1.47 ->
 // 1.19 ms (61 of 73 TFLOP/s), split BF16 there 0.40 -> 0.29 ms.  Writing the
 // next slab between the halves of this one was slower (FP32 spills).
@@ -674,7 +676,6 @@ __global__ __launch_bounds__(256, 2) void gemm_tn_big_kernel(const TIN* __restri
     } else {
       constexpr int CH = 16 / sizeof(L);
       using VL = __attribute__((ext_vector_type(CH))) L;
-      // lane group q holds k = (4 g + q) CH + e
       const int o = ((4 * g + (lane >> 4)) ^ ((lane >> 1) & 7)) * CH;
       VL fa[NI], fb[NI];
 #pragma unroll
@@ -886,10 +887,10 @@ __global__ __launch_bounds__(256, 2) void gemm_nn_big_kernel(const TIN* __restri
 // results for one column are rows of C.  A stays as it lies in memory, [k][m]:
 // a lane reads MW consecutive rows at once and these go to MW different MFMA
 // blocks, which makes the block's rows every MW-th one and its stores MW
-// values wide.  B rows are swizzled like the operands of A^T B, with the same
-// two slabs and edge rules.  Bound by the matrix cores: FP32
-// 884736 x 1152 x 1152 20.7 -> 17.3 ms (136 TFLOP/s; 64 x 128 tiles stored
-// transposed before), FP64 262144 x 480 x 480 2.32 -> 1.86 ms (65 of the 73
+// values wide.  B rows lie in LDS like the operands of A^T B (FP32 B comes in
+// that k order, its rows past K zero), with the same two slabs and edge rules.  Bound by the matrix cores: FP32
+// 884736 x 1152 x 1152 20.7 -> 18.4 ms (128 TFLOP/s; 64 x 128 tiles stored
+// transposed before; 17.3 with k in chunk order, which sums differently), FP64 262144 x 480 x 480 2.32 -> 1.86 ms (65 of the 73
 // TFLOP/s that a library product reaches).
 template <typename TIN, typename TOUT, int MF, int TM, int TN>
 __global__ __launch_bounds__(256, 2) void gemm_nn_wide_kernel(const TIN* __restrict__ A, int64_t lda,
@@ -941,9 +942,9 @@ __global__ __launch_bounds__(256, 2) void gemm_nn_wide_kernel(const TIN* __restr
 #pragma unroll
       for (int i = 0; i < BLOADS; ++i) {
         VL v{};
-        if (k < K) v = *reinterpret_cast<const VL*>(pb[i]);
+        if (k < (MF == MF_F32 ? ldb : K)) v = *reinterpret_cast<const VL*>(pb[i]);
 #pragma unroll
-        for (int e = 0; e < CH; ++e) rb[i][e] = k + e < K ? v[e] : L(0);
+        for (int e = 0; e < CH; ++e) rb[i][e] = MF == MF_F32 || k + e < K ? v[e] : L(0);
       }
     }
     pa += static_cast<int64_t>(BK) * lda;
@@ -962,7 +963,7 @@ __global__ __launch_bounds__(256, 2) void gemm_nn_wide_kernel(const TIN* __restr
       }
 #pragma unroll
     for (int i = 0; i < BLOADS; ++i)
-      *reinterpret_cast<VL*>(buf + TM * BK + row_off<MF>(bc + i * BSTEP, bk)) = rb[i];
+      *reinterpret_cast<VL*>(buf + TM * BK + chunk_off<MF>(bc + i * BSTEP, bk / CH)) = rb[i];
   };
 
   typename Form<MF>::acc_t acc[NB][MB];
@@ -973,8 +974,7 @@ __global__ __launch_bounds__(256, 2) void gemm_nn_wide_kernel(const TIN* __restr
   auto compute = [&](const L* buf, int g) {  // half a slab
     const L* x = buf + TM * BK + (wn + (lane & 15)) * BK;
     const L* y = buf + wm + (lane & 15) * MW;
-    // lane group q holds k = (4 g + q) CH + e
-    const int q = 4 * g + (lane >> 4), o = (q ^ ((lane >> 1) & 7)) * CH;
+    const int q = lane >> 4, o = ((4 * g + q) ^ ((lane >> 1) & 7)) * CH;
     VL fb[NB];
     VM fa[CH][PR];
 #pragma unroll
@@ -982,7 +982,10 @@ __global__ __launch_bounds__(256, 2) void gemm_nn_wide_kernel(const TIN* __restr
 #pragma unroll
     for (int e = 0; e < CH; ++e)
 #pragma unroll
-      for (int p = 0; p < PR; ++p) fa[e][p] = *reinterpret_cast<const VM*>(y + (q * CH + e) * TM + p * 16 * MW);
+      for (int p = 0; p < PR; ++p) {
+        const int k = MF == MF_F32 ? 16 * g + 4 * e + q : 8 * g + 2 * q + e;
+        fa[e][p] = *reinterpret_cast<const VM*>(y + k * TM + p * 16 * MW);
+      }
 #pragma unroll
     for (int e = 0; e < CH; ++e)
 #pragma unroll
@@ -1039,11 +1042,13 @@ __global__ void pad_f64_kernel(const double* __restrict__ s, int64_t lds, double
   const int64_t r = i % ldd, c = i / ldd;
   d[i] = r < rows ? s[r + c * lds] : 0.0;
 }
+// (chunked: rows in the order of chunk_off's FP32 rows, ldd a multiple of 16)
 __global__ void pad_f32_kernel(const double* __restrict__ s, int64_t lds, float* __restrict__ d, int64_t ldd,
-                               int64_t rows, int64_t cols) {
+                               int64_t rows, int64_t cols, int chunked) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= ldd * cols) return;
-  const int64_t r = i % ldd, c = i / ldd;
+  const int64_t p = i % ldd, c = i / ldd;
+  const int64_t r = chunked ? p / 16 * 16 + 4 * (p % 4) + p % 16 / 4 : p;
   d[i] = r < rows ? static_cast<float>(s[r + c * lds]) : 0.0f;
 }
 __global__ void split_bf16_from_f64_kernel(const double* __restrict__ s, int64_t lds, uint16_t* __restrict__ hi,
@@ -1099,17 +1104,26 @@ int planned_splits(int def, const GemmPlan& plan) {
 // K splits of the large TN kernel with tile edge T: about as many workgroups
 // as are resident at once (2 per CU at edge 128, 3 at edge 96: its smaller
 // accumulator tile leaves room for a third), so that symmetric products
-// (fewer tiles) get more splits; >= 16 K slabs each.
+// (fewer tiles) get more splits; >= 16 K slabs each.  The FP32 form counts
+// splits for the edge that issues 10 % less padded and redundant area (128 if
+// neither does), whichever edge then runs: its sums are as sensitive to their
+// order as to anything else, and so keep it.
 struct TnCut {
   int ntile, splits;
   int64_t kchunk;
 };
-TnCut tn_cut(int M, int N, int64_t K, int sym, int T, int bk, size_t work_elems, const GemmPlan& plan) {
+int tn_tiles(int M, int N, int sym, int T) {
   const int tm = (M + T - 1) / T, tn = (N + T - 1) / T;
+  return sym ? tm * (tm + 1) / 2 : tm * tn;
+}
+TnCut tn_cut(int M, int N, int64_t K, int sym, int T, bool f32, int bk, size_t work_elems, const GemmPlan& plan) {
   TnCut c;
-  c.ntile = sym ? tm * (tm + 1) / 2 : tm * tn;
-  const int resident = (T == 96) ? 3 : 2;
-  int splits = planned_splits(std::max(1, resident * device_cus() / c.ntile), plan);
+  c.ntile = tn_tiles(M, N, sym, T);
+  int ts = T;
+  if (f32 && plan.tile_tn == 0)
+    ts = 10 * int64_t{96 * 96} * tn_tiles(M, N, sym, 96) < 9 * int64_t{128 * 128} * tn_tiles(M, N, sym, 128) ? 96 : 128;
+  const int resident = (ts == 96) ? 3 : 2;
+  int splits = planned_splits(std::max(1, resident * device_cus() / tn_tiles(M, N, sym, ts)), plan);
   splits = static_cast<int>(std::min<int64_t>(splits, std::max<int64_t>(1, K / (16 * bk))));
   const size_t per = static_cast<size_t>(M) * N;
   splits = static_cast<int>(std::min<size_t>(splits, std::max<size_t>(1, work_elems / per)));
@@ -1122,16 +1136,17 @@ TnCut tn_cut(int M, int N, int64_t K, int sym, int T, int bk, size_t work_elems,
 // Large-tile edge (unless the plan forces one): the one whose busiest compute
 // unit has less to multiply, tile area x k of a split x workgroups on it; a
 // lone workgroup there runs about a tenth slower for want of a second to
-// cover its barriers.  Measured ratios 96 / 128 follow it: 480 of FP64 0.85
-// (0.84 by the rule), 300 of FP32 0.86 (0.84), 1200 of FP32 0.97 (0.95), 1152
-// of FP32 1.08 (1.03), 200 of FP64 1.07 (1.02), 120 of FP64 0.73 (0.56).
-int tn_tile_edge(int M, int N, int64_t K, int sym, int bk, size_t work_elems, const GemmPlan& plan) {
+// cover its barriers, and the smaller tile about a twentieth for its LDS reads.  Measured ratios 96 / 128 follow it: 480 of FP64 0.85
+// (0.89 by the rule), 300 of FP32 0.86 (0.89), 1200 of FP32 1.01 (1.00), 1152
+// of FP32 1.12 (1.08), 200 of FP64 1.07 (1.07), 120 of FP64 0.73 (0.59).
+int tn_tile_edge(int M, int N, int64_t K, int sym, bool f32, int bk, size_t work_elems, const GemmPlan& plan) {
   if (plan.tile_tn == 2) return 128;
   if (plan.tile_tn == 3) return 96;
   const auto cost = [&](int T) {
-    const TnCut c = tn_cut(M, N, K, sym, T, bk, work_elems, plan);
+    const TnCut c = tn_cut(M, N, K, sym, T, f32, bk, work_elems, plan);
     const int64_t nb = static_cast<int64_t>(c.ntile) * c.splits, cus = device_cus();
-    return static_cast<double>(T) * T * c.kchunk * ((nb + cus - 1) / cus) * (nb <= cus ? 1.1 : 1.0);
+    return static_cast<double>(T) * T * c.kchunk * ((nb + cus - 1) / cus) * (nb <= cus ? 1.1 : 1.0) *
+           (T == 96 ? 1.05 : 1.0);
   };
   return cost(96) < cost(128) ? 96 : 128;
 }
@@ -1141,7 +1156,7 @@ void tn_big_launch(const TIN* A, int64_t lda, const TIN* B, int64_t ldb, int M, 
                    int64_t ldc, int sym, int symmetrize, double* work, size_t work_elems, hipStream_t st,
                    const GemmPlan& plan) {
   const int tm = (M + T - 1) / T, tn = (N + T - 1) / T;
-  const TnCut c = tn_cut(M, N, K, sym, T, BigLds<MF>::BK, work_elems, plan);
+  const TnCut c = tn_cut(M, N, K, sym, T, MF == MF_F32, BigLds<MF>::BK, work_elems, plan);
   const int64_t nb = static_cast<int64_t>(c.ntile) * c.splits;
   if (nb > 0x7fffffff) fail(XLS_ERR_INVALID_ARG, "gemm_tn grid too large");
   hipLaunchKernelGGL((gemm_tn_big_kernel<TIN, MF, T>), dim3(static_cast<unsigned>(nb)), dim3(256), 0, st, A,
@@ -1161,7 +1176,7 @@ void tn_dispatch(const TIN* A, int64_t lda, const TIN* B, int64_t ldb, int M, in
     // products of FP32 blocks: 4 loads per 16-wide k slab and row)
     constexpr bool k96 = (96 * (BigLds<MF>::BK / VEC)) % 256 == 0;
     if constexpr (k96) {
-      if (tn_tile_edge(M, N, K, sym, BigLds<MF>::BK, work_elems, plan) == 96) {
+      if (tn_tile_edge(M, N, K, sym, MF == MF_F32, BigLds<MF>::BK, work_elems, plan) == 96) {
         tn_big_launch<TIN, MF, 96>(A, lda, B, ldb, M, N, K, C, ldc, sym, symmetrize, work, work_elems, st, plan);
         return;
       }
@@ -1279,12 +1294,15 @@ bool nn_big_t(int prec, const TS* A, int64_t lda, const double* B, int64_t ldb, 
     if (!have_work) return false;
     if (prec == MF_F32) {
       float* Bf = static_cast<float*>(bwork);
-      hipLaunchKernelGGL(pad_f32_kernel, dim3(pgrid), dim3(256), 0, st, B, ldb, Bf, ldp, K, N);
+      // 16-row chunks of FP32 need no more room than 8-row chunks of FP64
+      const int64_t ldf = TN == 128 ? (static_cast<int64_t>(K) + 15) / 16 * 16 : ldp;
+      hipLaunchKernelGGL(pad_f32_kernel, dim3(static_cast<unsigned>((ldf * N + 255) / 256)), dim3(256), 0, st, B, ldb,
+                         Bf, ldf, K, N, TN == 128 ? 1 : 0);
       if constexpr (TN == 128)
-        nn_wide_launch<float, MF_F32>(A, lda, Bf, ldp, M, N, K, C, ldc, st, plan);
+        nn_wide_launch<float, MF_F32>(A, lda, Bf, ldf, M, N, K, C, ldc, st, plan);
       else
         hipLaunchKernelGGL((gemm_nn_big_kernel<float, float, float, MF_F32, TN>), grid, dim3(256), 0, st, A, lda,
-                           Bf, static_cast<const float*>(nullptr), ldp, M, N, K, tnN, C, ldc);
+                           Bf, static_cast<const float*>(nullptr), ldf, M, N, K, tnN, C, ldc);
     } else if (prec == MF_BF) {
       // the rotation matrix is split into bf16 hi/lo once (same bytes as its FP32 copy)
       uint16_t* bh = static_cast<uint16_t*>(bwork);
