@@ -626,31 +626,32 @@ __global__ __launch_bounds__(NT) void hstencil_group_kernel(const HArgs<TS, TC>*
 }
 
 // alpha[col][4a+l] = gamma_{a,l} h^3 sum_s chi_{a,l}(s) y(idx(s), col).  One
-// wavefront per (atom, kProjCols columns): lanes stride over the atom's
-// support and load each point's index and projector values once for all its
-// columns; per column, FP64 partial sums per lane then a fixed xor-shuffle
-// reduction (deterministic).  Four columns per wave: eight were measured no
-// faster (the gathered column values, not the index and payload reads, set
-// its time).
+// wavefront per (atom, NC columns): lanes stride over the atom's support and
+// load each point's index and projector values once for all its columns; per
+// column, FP64 partial sums per lane then a fixed xor-shuffle reduction
+// (deterministic, and the same for every NC and D).
+// Large launches take four columns and two support points per lane and
+// iteration, and read the block at the rate of HBM (5 TB/s; eight columns were
+// measured no faster).  Small ones are a chain of gather latencies in a few
+// wavefronts: one column and eight points per iteration give more wavefronts
+// and a chain a quarter as long (24^3 x 20 FP64 7.2 -> 4.6 us).
 constexpr int kProjCols = 4;
-constexpr int kProjSums = 4 * kProjCols;  // one sum per (column, projector)
-static_assert(kProjSums == 16, "the reduction below halves 16 sums over 4 lane bits");
-template <typename TS, typename TC>
+template <typename TS, typename TC, int NC, int D>
 __device__ __forceinline__ void proj_forward_wave(const TS* __restrict__ y, int64_t ld, int ncols, int cbase,
                                                   const int32_t* __restrict__ sup_off,
                                                   const int32_t* __restrict__ sup_idx, const TC* __restrict__ val,
                                                   const double* __restrict__ gamma, double h3,
                                                   TC* __restrict__ alpha, int nproj, int a, int lane) {
   const int s0 = sup_off[a], s1 = sup_off[a + 1];
-  const int nc = min(kProjCols, ncols - cbase);
-  double acc[kProjCols][4];
+  const int nc = min(NC, ncols - cbase);
+  double acc[NC][4];
 #pragma unroll
-  for (int c = 0; c < kProjCols; ++c)
+  for (int c = 0; c < NC; ++c)
 #pragma unroll
     for (int l = 0; l < 4; ++l) acc[c][l] = 0.0;
-  // Two support points per lane and iteration (s and s + 64, added in that
+  // D support points per lane and iteration (s, s + 64, ..., added in that
   // order, so each lane's order is that of a one-point loop): their column
-  // loads are in flight together.  The next pair's indices and values load
+  // loads are in flight together.  The next points' indices and values load
   // one iteration ahead.  Every load is unconditional from a clamped,
   // in-range entry (a guarded load becomes a branch that waits for it);
   // products of entries past the support are skipped.
@@ -667,47 +668,51 @@ __device__ __forceinline__ void proj_forward_wave(const TS* __restrict__ y, int6
     for (int l = 0; l < 4; ++l) e.v[l] = v4[l];
     return e;
   };
-  const TS* yc[kProjCols];
+  const TS* yc[NC];
 #pragma unroll
-  for (int c = 0; c < kProjCols; ++c) yc[c] = y + static_cast<int64_t>(cbase + min(c, nc - 1)) * ld;
+  for (int c = 0; c < NC; ++c) yc[c] = y + static_cast<int64_t>(cbase + min(c, nc - 1)) * ld;
   if (s0 + lane < s1) {
-    Ent na = fetch(s0 + lane), nb = fetch(s0 + lane + 64);
-    for (int s = s0 + lane; s < s1; s += 128) {
-      const Ent ea = na, eb = nb;
-      na = fetch(s + 128);
-      nb = fetch(s + 192);
-      TS ya[kProjCols], yb[kProjCols];
+    Ent next[D];
 #pragma unroll
-      for (int c = 0; c < kProjCols; ++c) {
-        ya[c] = yc[c][ea.g];
-        yb[c] = yc[c][eb.g];
-      }
+    for (int d = 0; d < D; ++d) next[d] = fetch(s0 + lane + 64 * d);
+    for (int s = s0 + lane; s < s1; s += 64 * D) {
+      Ent e[D];
+      TS yv[D][NC];
 #pragma unroll
-      for (int c = 0; c < kProjCols; ++c)
+      for (int d = 0; d < D; ++d) e[d] = next[d];
 #pragma unroll
-        for (int l = 0; l < 4; ++l) acc[c][l] += static_cast<double>(ea.v[l]) * static_cast<double>(ya[c]);
-      if (s + 64 < s1) {
+      for (int d = 0; d < D; ++d) next[d] = fetch(s + 64 * (D + d));
 #pragma unroll
-        for (int c = 0; c < kProjCols; ++c)
+      for (int c = 0; c < NC; ++c)
 #pragma unroll
-          for (int l = 0; l < 4; ++l) acc[c][l] += static_cast<double>(eb.v[l]) * static_cast<double>(yb[c]);
-      }
+        for (int d = 0; d < D; ++d) yv[d][c] = yc[c][e[d].g];
+#pragma unroll
+      for (int d = 0; d < D; ++d)
+        if (d == 0 || s + 64 * d < s1) {
+#pragma unroll
+          for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int l = 0; l < 4; ++l) acc[c][l] += static_cast<double>(e[d].v[l]) * static_cast<double>(yv[d][c]);
+        }
     }
   }
-  // Reduction of the 16 sums by recursive halving: at offsets 32, 16, 8, 4 a
-  // lane keeps half of its values, each added to its partner's copy (the
-  // pairs and operand order of a full xor-shuffle tree, so every sum is
-  // bit-identical to it, in 32 shuffles instead of 96); offsets 2 and 1
-  // finish, and lane 4 v holds sum v = 4 c + l.  Both halves are shuffled
-  // and the kept sum selected, so no register array is indexed at run time.
-  double r[kProjSums];
+  // Reduction of the 4 NC sums by recursive halving: at offsets 32, 16 (and 8,
+  // 4 with 16 sums) a lane keeps half of its values, each added to its
+  // partner's copy (the pairs and operand order of a full xor-shuffle tree, so
+  // every sum is bit-identical to it, in far fewer shuffles); the remaining
+  // offsets finish, and the lanes of sum v = 4 c + l hold it.  Both halves are
+  // shuffled and the kept sum selected, so no register array is indexed at run
+  // time.
+  constexpr int NS = 4 * NC, LEV = NS == 16 ? 4 : 2, SH = 6 - LEV;
+  static_assert(NS == 1 << LEV, "one or four columns");
+  double r[NS];
 #pragma unroll
-  for (int c = 0; c < kProjCols; ++c)
+  for (int c = 0; c < NC; ++c)
 #pragma unroll
     for (int l = 0; l < 4; ++l) r[4 * c + l] = acc[c][l];
 #pragma unroll
-  for (int lev = 0; lev < 4; ++lev) {
-    const int off = 32 >> lev, half = (kProjSums / 2) >> lev;
+  for (int lev = 0; lev < LEV; ++lev) {
+    const int off = 32 >> lev, half = (NS / 2) >> lev;
     const bool up = (lane & off) != 0;
 #pragma unroll
     for (int j = 0; j < half; ++j) {
@@ -717,14 +722,14 @@ __device__ __forceinline__ void proj_forward_wave(const TS* __restrict__ y, int6
     }
   }
   double t = r[0];
-  t += __shfl_xor(t, 2, 64);
-  t += __shfl_xor(t, 1, 64);
-  const int vi = lane >> 2, c = vi >> 2, l = vi & 3;
-  if ((lane & 3) == 0 && c < nc)
+#pragma unroll
+  for (int off = 32 >> LEV; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+  const int vi = lane >> SH, c = vi >> 2, l = vi & 3;
+  if ((lane & ((1 << SH) - 1)) == 0 && c < nc)
     alpha[static_cast<int64_t>(cbase + c) * nproj + 4 * a + l] = static_cast<TC>(gamma[4 * a + l] * h3 * t);
 }
 
-template <typename TS, typename TC>
+template <typename TS, typename TC, int NC, int D>
 __global__ __launch_bounds__(256) void proj_forward_kernel(const TS* __restrict__ y, int64_t ld,
                                                            int ncols, const int32_t* __restrict__ sup_off,
                                                            const int32_t* __restrict__ sup_idx,
@@ -738,9 +743,9 @@ __global__ __launch_bounds__(256) void proj_forward_kernel(const TS* __restrict_
   // gather from the same cache lines, which then meet in that XCD's L2
   const uint32_t lb = xcd_remap(blockIdx.x, gridDim.x);
   const int a = static_cast<int>(lb % static_cast<uint32_t>(n_atoms));
-  const int cbase = (static_cast<int>(lb / static_cast<uint32_t>(n_atoms)) * 4 + wave) * kProjCols;
+  const int cbase = (static_cast<int>(lb / static_cast<uint32_t>(n_atoms)) * 4 + wave) * NC;
   if (cbase >= ncols) return;
-  proj_forward_wave<TS, TC>(y, ld, ncols, cbase, sup_off, sup_idx, val, gamma, h3, alpha, nproj, a, lane);
+  proj_forward_wave<TS, TC, NC, D>(y, ld, ncols, cbase, sup_off, sup_idx, val, gamma, h3, alpha, nproj, a, lane);
 }
 
 // Grouped forward projection: item = (operator, atom + n_atoms * column group).
@@ -769,7 +774,7 @@ __global__ __launch_bounds__(256) void proj_forward_group_kernel(const PArgs<TS,
     const int a = static_cast<int>(w.y % static_cast<uint32_t>(A.n_atoms));
     const int cbase = (static_cast<int>(w.y / static_cast<uint32_t>(A.n_atoms)) * 4 + wave) * kProjCols;
     if (cbase >= A.ncols) continue;
-    proj_forward_wave<TS, TC>(A.y, A.ld, A.ncols, cbase, A.sup_off, A.sup_idx, A.val, A.gamma, A.h3, A.alpha,
+    proj_forward_wave<TS, TC, kProjCols, 2>(A.y, A.ld, A.ncols, cbase, A.sup_off, A.sup_idx, A.val, A.gamma, A.h3, A.alpha,
                               A.nproj, a, lane);
   }
 }
@@ -1117,11 +1122,19 @@ template <typename TS, typename TC>
 void launch_proj_forward(const OpTables<TC>& op, const TS* y, int64_t ld, int ncols, TC* alpha,
                          hipStream_t st) {
   if (op.n_atoms == 0 || ncols <= 0) return;
-  const int64_t nb = static_cast<int64_t>(op.n_atoms) * ((ncols + 4 * kProjCols - 1) / (4 * kProjCols));
-  if (nb > 0x7fffffff) fail(XLS_ERR_INVALID_ARG, "too many projection blocks");
   const double h3 = op.h * op.h * op.h;
-  hipLaunchKernelGGL((proj_forward_kernel<TS, TC>), dim3(static_cast<unsigned>(nb)), dim3(256), 0, st, y, ld, ncols,
-                     op.sup_off, op.sup_idx, op.slot_val, op.gamma, h3, alpha, 4 * op.n_atoms, op.n_atoms);
+  const auto go = [&](auto kern, int nc) {
+    const int64_t nb = static_cast<int64_t>(op.n_atoms) * ((ncols + 4 * nc - 1) / (4 * nc));
+    if (nb > 0x7fffffff) fail(XLS_ERR_INVALID_ARG, "too many projection blocks");
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(nb)), dim3(256), 0, st, y, ld, ncols, op.sup_off, op.sup_idx,
+                       op.slot_val, op.gamma, h3, alpha, 4 * op.n_atoms, op.n_atoms);
+  };
+  // one column per wavefront while all of them are resident at once (two of
+  // that kernel per SIMD)
+  if (static_cast<int64_t>(op.n_atoms) * ncols <= 2048)
+    go(proj_forward_kernel<TS, TC, 1, 8>, 1);
+  else
+    go(proj_forward_kernel<TS, TC, kProjCols, 2>, kProjCols);
   XLS_LAUNCH_CHECK("proj_forward_kernel");
 }
 
