@@ -233,7 +233,6 @@ void lanczos_run(xls_subdomain_s* s, int k) {
   TS* w = V + ld * (k + 1);
   double* al = s->vsmall;         // [k]
   double* be = s->vsmall + 64;    // [k]
-  double* coef = s->vsmall + 128; // [k]
   double* nrm = s->vsmall + 192;
   double* part = s->vsmall + 256;  // [256]
   const int nblocks = 256;
@@ -246,43 +245,29 @@ void lanczos_run(xls_subdomain_s* s, int k) {
     XLS_HIP(hipMemcpyAsync(w, hv.data(), s->nd * sizeof(TS), hipMemcpyHostToDevice, s->st));
     XLS_HIP(hipStreamSynchronize(s->st));  // hv is released at scope exit
   }
-  launch_dot<TS>(w, w, s->nd, part, nblocks, nrm, 1, s->st);
-  launch_scale_to<TS>(V, w, nrm, s->nd, s->st);
+  launch_norm_partial<TS>(w, s->nd, part, nblocks, s->st);
+  launch_lanczos_scale<TS>(V, w, part, nblocks, nrm, s->nd, s->st);
   TS* alph = static_cast<TS*>(s->alpha);
-  std::vector<double> ha, hb;
-  int keff = k;
+  // every step is launched; the ends of the spectrum are taken from the steps
+  // before the first that meets an invariant Krylov space
   for (int j = 0; j < k; ++j) {
     TS* vj = V + j * ld;
     apply_H<TS>(s, vj, w, 1, alph);
-    launch_dot<TS>(vj, w, s->nd, part, nblocks, al + j, 0, s->st);
-    launch_lanczos_update<TS>(w, vj, j > 0 ? vj - ld : nullptr, al + j, j > 0 ? be + j - 1 : nullptr, s->nd,
-                              s->st);
-    // coef = V_{0..j}^T w (full reorthogonalisation): a skinny product
+    // u = w - alpha v - beta v_prev waits in the place of the next vector; full
+    // reorthogonalisation against V_{0..j} brings it back into w
+    TS* u = vj + ld;
     const int rb = static_cast<int>(std::max<size_t>(1, std::min<size_t>(256, s->gwork_elems / (j + 1))));
-    launch_multi_dot<TS>(V, ld, j + 1, w, s->nd, s->gwork, rb, coef, s->st);
-    launch_reorth<TS>(w, V, ld, coef, j + 1, s->nd, s->st);
-    launch_dot<TS>(w, w, s->nd, part, nblocks, be + j, 1, s->st);
-    double ab[2];
-    XLS_HIP(hipMemcpyAsync(&ab[0], al + j, 8, hipMemcpyDeviceToHost, s->st));
-    XLS_HIP(hipMemcpyAsync(&ab[1], be + j, 8, hipMemcpyDeviceToHost, s->st));
-    XLS_HIP(hipStreamSynchronize(s->st));
-    ha.push_back(ab[0]);
-    hb.push_back(ab[1]);
-    double scale = 0;
-    for (double x : ha) scale = std::max(scale, std::fabs(x));
-    for (double x : hb) scale = std::max(scale, x);
-    if (ab[1] <= 1e-12 * scale) {  // invariant Krylov space
-      keff = j + 1;
-      break;
-    }
-    launch_scale_to<TS>(V + (j + 1) * ld, w, be + j, s->nd, s->st);
+    launch_lanczos_dots<TS>(w, vj, j > 0 ? vj - ld : nullptr, part, nblocks, al + j, j > 0 ? be + j - 1 : nullptr, V,
+                            ld, j + 1, s->nd, u, s->gwork, rb, s->st);
+    launch_lanczos_reorth<TS>(u, V, ld, s->gwork, rb, j + 1, s->nd, w, part, nblocks, s->st);
+    launch_lanczos_scale<TS>(u, w, part, nblocks, be + j, s->nd, s->st);
   }
-  launch_tridiag_extremes(al, be, keff, nrm, s->st);
-  double ext[2];
-  XLS_HIP(hipMemcpyAsync(ext, nrm, 16, hipMemcpyDeviceToHost, s->st));
+  launch_tridiag_extremes(al, be, k, nrm, s->st);
+  double ext[3];
+  XLS_HIP(hipMemcpyAsync(ext, nrm, sizeof(ext), hipMemcpyDeviceToHost, s->st));
   XLS_HIP(hipStreamSynchronize(s->st));
   s->lz_lo = ext[0];
-  s->lz_up = ext[1] + std::fabs(hb[keff - 1]);
+  s->lz_up = ext[1] + ext[2];
   s->lz_k = k;
   s->have_lanczos = true;
 }

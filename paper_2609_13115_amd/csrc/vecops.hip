@@ -14,16 +14,21 @@ namespace {
 
 inline unsigned nblk(int64_t n, int b) { return static_cast<unsigned>((n + b - 1) / b); }
 
-// One wave per column: lane l adds entries l, l + 64, ... in order, then a
-// fixed xor-shuffle tree (the order never depends on scheduling).
+// Sum of p[0..n) in every lane of a wave: lane l adds entries l, l + 64, ... in
+// order, then a fixed xor-shuffle tree (the order never depends on scheduling).
+__device__ __forceinline__ double wave_sum(const double* __restrict__ p, int n, int lane) {
+  double s = 0.0;
+  for (int i = lane; i < n; i += 64) s += p[i];
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+  return s;
+}
+
+// One wave per column.
 __global__ __launch_bounds__(256) void reduce_cols_kernel(const double* __restrict__ partial, int nper, int ncols,
                                                           double* __restrict__ out, int take_sqrt) {
   const int c = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (c >= ncols) return;
-  double s = 0.0;
-  const double* p = partial + static_cast<int64_t>(c) * nper;
-  for (int i = lane; i < nper; i += 64) s += p[i];
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+  const double s = wave_sum(partial + static_cast<int64_t>(c) * nper, nper, lane);
   if (lane == 0) out[c] = take_sqrt ? sqrt(s) : s;
 }
 
@@ -407,54 +412,107 @@ __global__ __launch_bounds__(256) void dot_partial_kernel(const TS* __restrict__
   if (threadIdx.x == 0) partial[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// partial[i nblocks + b] = block b's share of sum_g V[i ldv + g] y[g]; grid
-// (nblocks, m), the layout of dot_partial_kernel per row i
+// The Lanczos recurrence, three kernels a step besides H v and v.w.  On a box
+// of a few thousand points a kernel is its launch and one latency, so each
+// starts by summing the partial sums that the one before it left (every wave
+// for itself, in reduce_cols_kernel's order) instead of waiting for a kernel
+// that does, and the host is not asked anything until the last step: a step of
+// 17 x 21 x 14 points takes 30 us, where ten kernels, two copies and a wait for
+// the host took about 88.
+
+// u = w - alpha_j v - beta_{j-1} v_prev (vp may be null; alpha_j is the sum of
+// apart, written to *alpha) and partial[i nblocks + b] = block b's share of
+// V_i . u for the kDotRows rows of blockIdx.y; grid (nblocks, rows / kDotRows).
+constexpr int kDotRows = 4;
 template <typename TS>
-__global__ __launch_bounds__(256) void multi_dot_partial_kernel(const TS* __restrict__ V, int64_t ldv,
-                                                                const TS* __restrict__ y, int64_t n, int nblocks,
-                                                                double* __restrict__ partial) {
-  __shared__ double red[4];
-  const TS* __restrict__ x = V + static_cast<int64_t>(blockIdx.y) * ldv;
+__global__ __launch_bounds__(256) void lanczos_dots_kernel(const TS* __restrict__ w, const TS* __restrict__ v,
+                                                           const TS* __restrict__ vp,
+                                                           const double* __restrict__ apart, int na,
+                                                           double* __restrict__ alpha,
+                                                           const double* __restrict__ beta, const TS* __restrict__ V,
+                                                           int64_t ldv, int m, int64_t n, int nblocks,
+                                                           TS* __restrict__ u, double* __restrict__ partial) {
+  __shared__ double red[kDotRows][4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const double al = wave_sum(apart, na, lane);
+  const double be = vp ? *beta : 0.0;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *alpha = al;
+  const int row0 = blockIdx.y * kDotRows;
   const int64_t per = (n + nblocks - 1) / nblocks;
   const int64_t i0 = blockIdx.x * per, i1 = min(n, i0 + per);
-  double s = 0.0;
-  for (int64_t i = i0 + threadIdx.x; i < i1; i += 256)
-    s += static_cast<double>(x[i]) * static_cast<double>(y[i]);
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  const TS* x[kDotRows];
+#pragma unroll
+  for (int q = 0; q < kDotRows; ++q) x[q] = V + static_cast<int64_t>(min(row0 + q, m - 1)) * ldv;
+  double s[kDotRows] = {};
+  for (int64_t i = i0 + threadIdx.x; i < i1; i += 256) {
+    double r = static_cast<double>(w[i]) - al * static_cast<double>(v[i]);
+    if (vp) r -= be * static_cast<double>(vp[i]);
+    const TS t = static_cast<TS>(r);
+    if (blockIdx.y == 0) u[i] = t;
+#pragma unroll
+    for (int q = 0; q < kDotRows; ++q) s[q] += static_cast<double>(x[q][i]) * static_cast<double>(t);
+  }
+  for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+    for (int q = 0; q < kDotRows; ++q) s[q] += __shfl_xor(s[q], off, 64);
+#pragma unroll
+  for (int q = 0; q < kDotRows; ++q)
+    if (lane == 0) red[q][wave] = s[q];
   __syncthreads();
-  if (threadIdx.x == 0) partial[static_cast<int64_t>(blockIdx.y) * nblocks + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+  const int q = threadIdx.x;
+  if (q < kDotRows && row0 + q < m)
+    partial[static_cast<int64_t>(row0 + q) * nblocks + blockIdx.x] = (red[q][0] + red[q][1]) + (red[q][2] + red[q][3]);
 }
 
-// w <- w - alpha_j v - beta_{j-1} v_prev  (beta_prev may be null)
+// w = u - V coef (classical Gram-Schmidt against the m columns of V, coef the
+// sums of partial's rows) and npart[b] = block b's share of w . w.
+constexpr int kMaxDots = 64;
 template <typename TS>
-__global__ void lanczos_update_kernel(TS* __restrict__ w, const TS* __restrict__ v, const TS* __restrict__ vp,
-                                      const double* __restrict__ alpha, const double* __restrict__ beta,
-                                      int64_t n) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  double r = static_cast<double>(w[i]) - (*alpha) * static_cast<double>(v[i]);
-  if (vp) r -= (*beta) * static_cast<double>(vp[i]);
-  w[i] = static_cast<TS>(r);
+__global__ __launch_bounds__(256) void lanczos_reorth_kernel(const TS* __restrict__ u, const TS* __restrict__ V,
+                                                             int64_t ldv, const double* __restrict__ partial,
+                                                             int nper, int m, int64_t n, int nblocks,
+                                                             TS* __restrict__ w, double* __restrict__ npart) {
+  __shared__ double coef[kMaxDots], red[4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int j0 = wave; j0 < m; j0 += 16) {  // four rows' loads in flight
+    double c[4] = {};
+    for (int i = lane; i < nper; i += 64)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) c[q] += partial[static_cast<int64_t>(min(j0 + 4 * q, m - 1)) * nper + i];
+    for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) c[q] += __shfl_xor(c[q], off, 64);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (lane == 0 && j0 + 4 * q < m) coef[j0 + 4 * q] = c[q];
+  }
+  __syncthreads();
+  const int64_t per = (n + nblocks - 1) / nblocks;
+  const int64_t i0 = blockIdx.x * per, i1 = min(n, i0 + per);
+  double s2 = 0.0;
+  for (int64_t i = i0 + threadIdx.x; i < i1; i += 256) {
+    double s = 0.0;
+#pragma unroll 8
+    for (int j = 0; j < m; ++j) s += static_cast<double>(V[i + j * ldv]) * coef[j];
+    const TS t = static_cast<TS>(static_cast<double>(u[i]) - s);
+    w[i] = t;
+    s2 += static_cast<double>(t) * static_cast<double>(t);
+  }
+  for (int off = 32; off > 0; off >>= 1) s2 += __shfl_xor(s2, off, 64);
+  if (lane == 0) red[wave] = s2;
+  __syncthreads();
+  if (threadIdx.x == 0) npart[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// w <- w - V coef  (classical Gram-Schmidt against k columns of V)
+// dst = src / norm, norm the square root of the sum of npart, written to *norm
 template <typename TS>
-__global__ void reorth_kernel(TS* __restrict__ w, const TS* __restrict__ V, int64_t ldv,
-                              const double* __restrict__ coef, int k, int64_t n) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  double s = 0.0;
-  for (int j = 0; j < k; ++j) s += static_cast<double>(V[i + j * ldv]) * coef[j];
-  w[i] = static_cast<TS>(static_cast<double>(w[i]) - s);
-}
-
-template <typename TS>
-__global__ void scale_to_kernel(TS* __restrict__ dst, const TS* __restrict__ src, const double* __restrict__ nrm,
-                                int64_t n) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  dst[i] = static_cast<TS>(static_cast<double>(src[i]) / (*nrm));
+__global__ __launch_bounds__(256) void lanczos_scale_kernel(TS* __restrict__ dst, const TS* __restrict__ src,
+                                                            const double* __restrict__ npart, int nper,
+                                                            double* __restrict__ norm, int64_t n) {
+  const double nrm = sqrt(wave_sum(npart, nper, threadIdx.x & 63));
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (i == 0) *norm = nrm;
+  if (i < n) dst[i] = static_cast<TS>(static_cast<double>(src[i]) / nrm);
 }
 
 __global__ void fill_i32_kernel(int32_t* __restrict__ p, int32_t v, int64_t n) {
@@ -463,35 +521,60 @@ __global__ void fill_i32_kernel(int32_t* __restrict__ p, int32_t v, int64_t n) {
 }
 
 // Smallest and largest eigenvalue of the k x k symmetric tridiagonal T
-// (diagonal alpha, off-diagonal beta[0..k-2]) by Sturm-count bisection; one
-// thread per end, 200 halvings of the Gershgorin interval (exact to the last
-// bits in FP64).
-__global__ void tridiag_extremes_kernel(const double* __restrict__ alpha, const double* __restrict__ beta,
-                                        int k, double* __restrict__ out) {
-  const int which = threadIdx.x;  // 0: min, 1: max
-  if (which > 1) return;
-  double lo = alpha[0], hi = alpha[0];
-  for (int i = 0; i < k; ++i) {
-    const double r = (i > 0 ? fabs(beta[i - 1]) : 0.0) + (i < k - 1 ? fabs(beta[i]) : 0.0);
-    lo = fmin(lo, alpha[i] - r);
-    hi = fmax(hi, alpha[i] + r);
+// (diagonal alpha, off-diagonal beta[0..k-2]) by Sturm counts, cut at the first
+// step whose beta is within 1e-12 of the largest entry so far (an invariant
+// Krylov space; what follows it is not used).  One wave per end: every round
+// counts at 63 interior points of the interval, which shrinks it 64-fold, to
+// the last bits of FP64 (one lane halving it took 105 us for k = 20).  out[2]
+// is |beta| of the last step used.
+__global__ __launch_bounds__(128) void tridiag_extremes_kernel(const double* __restrict__ alpha,
+                                                               const double* __restrict__ beta, int k,
+                                                               double* __restrict__ out) {
+  __shared__ double al[kMaxDots], be[kMaxDots];
+  const int lane = threadIdx.x & 63, which = threadIdx.x >> 6;  // 0: min, 1: max
+  for (int i = threadIdx.x; i < k; i += 128) {
+    al[i] = alpha[i];
+    be[i] = beta[i];
   }
-  const double target = which == 0 ? 1.0 : static_cast<double>(k);  // count of eigenvalues <= x
-  for (int it = 0; it < 200; ++it) {
+  __syncthreads();
+  double sa = 0.0, sb = 0.0;  // largest entries; a NaN is passed over
+  for (int j = 0; j < k; ++j) {
+    const double x = fabs(al[j]);
+    if (sa < x) sa = x;
+    if (sb < be[j]) sb = be[j];
+    if (be[j] <= 1e-12 * (sa < sb ? sb : sa)) {
+      k = j + 1;
+      break;
+    }
+  }
+  double lo = al[0], hi = al[0];
+  for (int i = 0; i < k; ++i) {
+    const double r = (i > 0 ? fabs(be[i - 1]) : 0.0) + (i < k - 1 ? fabs(be[i]) : 0.0);
+    lo = fmin(lo, al[i] - r);
+    hi = fmax(hi, al[i] + r);
+  }
+  const int target = which == 0 ? 1 : k;  // count of eigenvalues <= x
+  for (int it = 0; it < 64; ++it) {
     const double mid = 0.5 * (lo + hi);
     if (mid <= lo || mid >= hi) break;
-    // number of eigenvalues < mid
-    int cnt = 0;
-    double q = alpha[0] - mid;
+    // lane 31 takes the midpoint itself, so that every round shrinks [lo, hi]
+    const double x = lane == 31 ? mid : lo + (hi - lo) * ((lane + 1) * 0.015625);
+    int cnt = 0;  // number of eigenvalues < x
+    double q = al[0] - x;
     if (q < 0) ++cnt;
     for (int i = 1; i < k; ++i) {
       const double qq = (q != 0.0) ? q : 1e-300;
-      q = alpha[i] - mid - beta[i - 1] * beta[i - 1] / qq;
+      q = al[i] - x - be[i - 1] * be[i - 1] / qq;
       if (q < 0) ++cnt;
     }
-    if (cnt >= target) hi = mid; else lo = mid;
+    const uint64_t above = __ballot(lane < 63 && cnt >= target);
+    const int f = above ? __builtin_ctzll(above) : 63;  // first point at or past the eigenvalue
+    const double nhi = __shfl(x, f, 64), nlo = __shfl(x, f > 0 ? f - 1 : 0, 64);
+    if (f < 63) hi = nhi;
+    if (f > 0) lo = nlo;
   }
-  out[which] = 0.5 * (lo + hi);
+  if (lane == 0) out[which] = 0.5 * (lo + hi);
+  if (threadIdx.x == 0) out[2] = fabs(be[k - 1]);
 }
 
 template <typename TS>
@@ -639,52 +722,48 @@ void launch_dos(const double* lam, const double* c, int64_t n, const double* edg
   XLS_LAUNCH_CHECK("dos_kernel");
 }
 
-template <typename TS>
-void launch_dot(const TS* x, const TS* y, int64_t n, double* partial, int nblocks, double* out,
-                int take_sqrt, hipStream_t st) {
-  hipLaunchKernelGGL(dot_partial_kernel<TS>, dim3(nblocks), dim3(256), 0, st, x, y, n, nblocks, partial);
-  launch_reduce_cols(partial, nblocks, 1, out, take_sqrt, st);
-}
-
-template <typename TS>
-void launch_multi_dot(const TS* V, int64_t ldv, int m, const TS* y, int64_t n, double* partial, int nblocks,
-                      double* out, hipStream_t st) {
-  if (m <= 0) return;
-  hipLaunchKernelGGL(multi_dot_partial_kernel<TS>, dim3(nblocks, m), dim3(256), 0, st, V, ldv, y, n, nblocks,
-                     partial);
-  XLS_LAUNCH_CHECK("multi_dot_partial_kernel");
-  launch_reduce_cols(partial, nblocks, m, out, 0, st);
-}
-
 void launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t st) {
   hipLaunchKernelGGL(fill_i32_kernel, dim3(nblk(n, 256)), dim3(256), 0, st, p, v, n);
   XLS_LAUNCH_CHECK("fill_i32_kernel");
 }
 
 template <typename TS>
-void launch_lanczos_update(TS* w, const TS* v, const TS* vprev, const double* alpha_j,
-                           const double* beta_prev, int64_t n, hipStream_t st) {
-  hipLaunchKernelGGL(lanczos_update_kernel<TS>, dim3(nblk(n, 256)), dim3(256), 0, st, w, v, vprev, alpha_j,
-                     beta_prev, n);
-  XLS_LAUNCH_CHECK("lanczos_update_kernel");
+void launch_lanczos_dots(const TS* w, const TS* v, const TS* vprev, double* part, int nblocks, double* alpha_j,
+                         const double* beta_prev, const TS* V, int64_t ldv, int m, int64_t n, TS* u, double* dots,
+                         int ndots, hipStream_t st) {
+  if (m > kMaxDots) fail(XLS_ERR_INVALID_ARG, "too many Lanczos vectors");
+  hipLaunchKernelGGL(dot_partial_kernel<TS>, dim3(nblocks), dim3(256), 0, st, v, w, n, nblocks, part);
+  hipLaunchKernelGGL(lanczos_dots_kernel<TS>, dim3(ndots, nblk(m, kDotRows)), dim3(256), 0, st, w, v, vprev, part,
+                     nblocks, alpha_j, beta_prev, V, ldv, m, n, ndots, u, dots);
+  XLS_LAUNCH_CHECK("lanczos_dots_kernel");
 }
 
 template <typename TS>
-void launch_reorth(TS* w, const TS* V, int64_t ldv, const double* coef, int k, int64_t n,
-                   hipStream_t st) {
-  hipLaunchKernelGGL(reorth_kernel<TS>, dim3(nblk(n, 256)), dim3(256), 0, st, w, V, ldv, coef, k, n);
-  XLS_LAUNCH_CHECK("reorth_kernel");
+void launch_lanczos_reorth(const TS* u, const TS* V, int64_t ldv, const double* dots, int ndots, int m, int64_t n,
+                           TS* w, double* part, int nblocks, hipStream_t st) {
+  if (m > kMaxDots) fail(XLS_ERR_INVALID_ARG, "too many Lanczos vectors");
+  hipLaunchKernelGGL(lanczos_reorth_kernel<TS>, dim3(nblocks), dim3(256), 0, st, u, V, ldv, dots, ndots, m, n,
+                     nblocks, w, part);
+  XLS_LAUNCH_CHECK("lanczos_reorth_kernel");
 }
 
 template <typename TS>
-void launch_scale_to(TS* dst, const TS* src, const double* norm2, int64_t n, hipStream_t st) {
-  hipLaunchKernelGGL(scale_to_kernel<TS>, dim3(nblk(n, 256)), dim3(256), 0, st, dst, src, norm2, n);
-  XLS_LAUNCH_CHECK("scale_to_kernel");
+void launch_norm_partial(const TS* x, int64_t n, double* part, int nblocks, hipStream_t st) {
+  hipLaunchKernelGGL(dot_partial_kernel<TS>, dim3(nblocks), dim3(256), 0, st, x, x, n, nblocks, part);
+  XLS_LAUNCH_CHECK("dot_partial_kernel");
+}
+
+template <typename TS>
+void launch_lanczos_scale(TS* dst, const TS* src, const double* part, int nblocks, double* norm, int64_t n,
+                          hipStream_t st) {
+  hipLaunchKernelGGL(lanczos_scale_kernel<TS>, dim3(nblk(n, 256)), dim3(256), 0, st, dst, src, part, nblocks, norm, n);
+  XLS_LAUNCH_CHECK("lanczos_scale_kernel");
 }
 
 void launch_tridiag_extremes(const double* alpha, const double* beta, int k, double* out,
                              hipStream_t st) {
-  hipLaunchKernelGGL(tridiag_extremes_kernel, dim3(1), dim3(64), 0, st, alpha, beta, k, out);
+  if (k < 1 || k > kMaxDots) fail(XLS_ERR_INVALID_ARG, "bad number of Lanczos steps");
+  hipLaunchKernelGGL(tridiag_extremes_kernel, dim3(1), dim3(128), 0, st, alpha, beta, k, out);
   XLS_LAUNCH_CHECK("tridiag_extremes_kernel");
 }
 
@@ -709,13 +788,13 @@ void launch_block_to_double(const TS* src, int64_t lds_, double* dst, int64_t ld
 }
 
 #define XLS_INST_VEC(TS)                                                                            \
-  template void launch_dot<TS>(const TS*, const TS*, int64_t, double*, int, double*, int, hipStream_t); \
-  template void launch_multi_dot<TS>(const TS*, int64_t, int, const TS*, int64_t, double*, int, double*,  \
-                                     hipStream_t);                                                       \
-  template void launch_lanczos_update<TS>(TS*, const TS*, const TS*, const double*, const double*,  \
-                                          int64_t, hipStream_t);                                    \
-  template void launch_reorth<TS>(TS*, const TS*, int64_t, const double*, int, int64_t, hipStream_t); \
-  template void launch_scale_to<TS>(TS*, const TS*, const double*, int64_t, hipStream_t);           \
+  template void launch_lanczos_dots<TS>(const TS*, const TS*, const TS*, double*, int, double*,     \
+                                        const double*, const TS*, int64_t, int, int64_t, TS*, double*, int, \
+                                        hipStream_t);                                               \
+  template void launch_lanczos_reorth<TS>(const TS*, const TS*, int64_t, const double*, int, int, int64_t, TS*, \
+                                          double*, int, hipStream_t);                               \
+  template void launch_norm_partial<TS>(const TS*, int64_t, double*, int, hipStream_t);             \
+  template void launch_lanczos_scale<TS>(TS*, const TS*, const double*, int, double*, int64_t, hipStream_t); \
   template void launch_convert_block<TS>(const double*, int64_t, TS*, int64_t, int64_t, int,        \
                                          hipStream_t);                                              \
   template void launch_block_to_double<TS>(const TS*, int64_t, double*, int64_t, int64_t, int,      \

@@ -280,24 +280,25 @@ void launch_scatter_core(const double* rho, const uint8_t* mask, const int64_t* 
 // dos[b] = 2 sum c over lam in bin b of edges[0..nbins]
 void launch_dos(const double* lam, const double* c, int64_t n, const double* edges, int nbins, double* dos,
                 hipStream_t st);
-// Lanczos helpers
+// Lanczos steps.  part holds nblocks partial sums; dots ndots per row of V.
+// *alpha_j = v.w, u = w - alpha_j v - beta_prev vprev (vprev may be null),
+// dots = partial sums of V_i . u for i < m
 template <typename TS>
-void launch_dot(const TS* x, const TS* y, int64_t n, double* partial, int nblocks, double* out,
-                int take_sqrt, hipStream_t st);
-// out[i] = sum_g V[i ldv + g] y[g] for i < m: nblocks partial sums per i
-// (partial holds m * nblocks doubles), then a fixed-order reduction
+void launch_lanczos_dots(const TS* w, const TS* v, const TS* vprev, double* part, int nblocks, double* alpha_j,
+                         const double* beta_prev, const TS* V, int64_t ldv, int m, int64_t n, TS* u, double* dots,
+                         int ndots, hipStream_t st);
+// w = u - sum_i (V_i . u) V_i, part = partial sums of w . w
 template <typename TS>
-void launch_multi_dot(const TS* V, int64_t ldv, int m, const TS* y, int64_t n, double* partial, int nblocks,
-                      double* out, hipStream_t st);
+void launch_lanczos_reorth(const TS* u, const TS* V, int64_t ldv, const double* dots, int ndots, int m, int64_t n,
+                           TS* w, double* part, int nblocks, hipStream_t st);
 template <typename TS>
-void launch_lanczos_update(TS* w, const TS* v, const TS* vprev, const double* alpha_j,
-                           const double* beta_prev, int64_t n, hipStream_t st);
+void launch_norm_partial(const TS* x, int64_t n, double* part, int nblocks, hipStream_t st);
+// *norm = sqrt of the sum of part, dst = src / *norm
 template <typename TS>
-void launch_reorth(TS* w, const TS* V, int64_t ldv, const double* coef, int k, int64_t n,
-                   hipStream_t st);
-template <typename TS>
-void launch_scale_to(TS* dst, const TS* src, const double* norm, int64_t n, hipStream_t st);
+void launch_lanczos_scale(TS* dst, const TS* src, const double* part, int nblocks, double* norm, int64_t n,
+                          hipStream_t st);
 void launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t st);
+// out = (smallest and largest eigenvalue, |beta| of the last step used)
 void launch_tridiag_extremes(const double* alpha, const double* beta, int k, double* out,
                              hipStream_t st);
 
