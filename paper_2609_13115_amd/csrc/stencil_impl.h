@@ -147,6 +147,30 @@ __device__ __forceinline__ void bstore_p(double v, __amdgpu_buffer_rsrc_t r, int
   typedef unsigned int u2 __attribute__((ext_vector_type(2)));
   __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, voff, soff, AUX);
 }
+// two consecutive elements
+template <int AUX, typename T>
+__device__ __forceinline__ void bload2(__amdgpu_buffer_rsrc_t r, int voff, int soff, T (&d)[2]) {
+  typedef T t2 __attribute__((ext_vector_type(2)));
+  t2 v;
+  if constexpr (sizeof(T) == 4)
+    v = __builtin_bit_cast(t2, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, AUX));
+  else
+    v = __builtin_bit_cast(t2, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, AUX));
+  d[0] = v[0];
+  d[1] = v[1];
+}
+template <int AUX, typename T>
+__device__ __forceinline__ void bstore2(T a, T b, __amdgpu_buffer_rsrc_t r, int voff, int soff) {
+  typedef T t2 __attribute__((ext_vector_type(2)));
+  const t2 v = {a, b};
+  if constexpr (sizeof(T) == 4) {
+    typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, voff, soff, AUX);
+  } else {
+    typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), r, voff, soff, AUX);
+  }
+}
 // binary16 stream element (a warm start kept in half precision), widened
 template <typename TC, int AUX>
 __device__ __forceinline__ TC bload_h(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
@@ -211,24 +235,40 @@ __device__ __forceinline__ Ent4<double> load_ent<double>(__amdgpu_buffer_rsrc_t 
 // HM: halo cells a lane loads and stages per plane (3 where the tile's halo
 // fits, else 4: the fourth would be an unused load and LDS write; FP64 64^3 x
 // 480 855 -> 822 us with it gone).
-// PAIR (FP32 arithmetic, two points a lane, rows of whole 128-byte lines): the
-// lane's points are consecutive rows, whose y neighbours overlap: 12 LDS reads
-// serve both points, own rows come from registers, where separate rows take 24
-// (the LDS pipe is the busiest one in FP32: 64^3 x 480 424 -> 374 us).  With
-// other row lengths the pairs break up the lanes' contiguous loads (43^3 360
-// -> 423 us, 80^3 323 -> 335 for 9e7 points), and in FP64 the shared run costs
-// 56 registers and spills: there lanes own points one workgroup apart.
-template <typename TS, typename TC, int MODE, int P, int NT, int WS, int NV, int HF, int HM, bool PAIR>
+// PK, how a lane's two points lie:
+// 0: one workgroup apart (any row length; also one point a lane).
+// kRowPairs (FP32, rows of whole 128-byte lines): consecutive rows, whose y
+//   neighbours overlap: 12 LDS reads serve both points, own rows come from
+//   registers, where separate rows take 24 (the LDS pipe is the busiest one in
+//   FP32: 64^3 x 480 424 -> 374 us).  With other row lengths the pairs break up
+//   the lanes' contiguous loads (43^3 360 -> 423 us, 80^3 323 -> 335 for 9e7
+//   points).
+// kXPairs (FP64): neighbours in x.  Every stream of the grid (Y_k, Y_{k-1}, V,
+//   the reverse-CSR words, the output, the halo, of which HM then counts
+//   pairs) moves two values per instruction, and the star of both points is 18
+//   reads of 16 bytes where two single points take 48 of 8; 16-byte reads
+//   also have twice the LDS rate: 4.5e7 points of 64^3 330 -> 285 us, 48^3 317
+//   -> 284, 80^3 362 -> 335, 43^3 354 -> 340.  In FP32 the reads are of 8 bytes,
+//   at half the rate of single ones (64^3 297 -> 370 us for 9e7 points).
+// kXHalf: kXPairs for rows of odd length in Dirichlet boxes.  A row ends in half
+//   a pair, whose second value (the next row's first) is loaded but counts as
+//   the zero halo cell and is neither staged nor stored: those writes are single.
+constexpr int kRowPairs = 1, kXPairs = 2, kXHalf = 3;
+template <typename TS, typename TC, int MODE, int P, int NT, int WS, int NV, int HF, int HM, int PK>
 __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t logical, TC ca, TC cc, TC cb,
                                              unsigned char* smem_raw) {
-  static_assert(!PAIR || (P == 2 && sizeof(TC) == 4), "row pairs: two points a lane, FP32");
+  constexpr bool ROWS = PK == kRowPairs, PAIR = PK == kXPairs || PK == kXHalf, HALF = PK == kXHalf;
+  static_assert(PK == 0 || P == 2, "pairs: two points a lane");
+  static_assert(!ROWS || sizeof(TC) == 4, "row pairs: FP32");
+  static_assert(!PAIR || (sizeof(TC) == 8 && NV == 1), "x pairs: FP64, one column");
+  using TC2 = TC __attribute__((ext_vector_type(2)));
   static_assert(NV == 1 || MODE != kResid, "residual sweeps take one column per tile");
   static_assert(HF == 0 || MODE == kFilter, "binary16 inputs only in filter steps");
   TC* lds = reinterpret_cast<TC*>(smem_raw);
   const int nx = A.nx, ny = A.ny, nz = A.nz;
   constexpr int W = WS;
-  const int dumpi = W * (A.ty + 2 * R);  // spare slot at the end of each plane buffer
-  const int plane = dumpi + 1;
+  const int dumpi = W * (A.ty + 2 * R);  // spare slots at the end of each plane buffer
+  const int plane = dumpi + 2;           // even: pairs stay aligned in every buffer
   TC* alds = lds + 2 * NV * plane;     // the columns' projection coefficients
 
   // Logical order: z chunk, then column group, then y band.  The xcd remap
@@ -250,6 +290,7 @@ __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t lo
   const int z0 = zt * A.tz;
   const int z1 = min(z0 + A.tz, nz);
   const int npts = nx * tyv;
+  const int hx = (nx + 1) / 2;  // pairs of a row
   const int tid = threadIdx.x;
   const int pp = nx * ny;  // points per plane
   constexpr int ES = sizeof(TS), EC = sizeof(TC);
@@ -287,10 +328,15 @@ __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t lo
   for (int i = 0; i < P; ++i) {
     int x, yy;
     bool act;
-    if constexpr (PAIR) {
+    if constexpr (ROWS) {
       x = tid % nx;
       yy = y0 + (tid / nx) * P + i;
       act = yy < y0 + tyv;
+    } else if constexpr (PAIR) {
+      const bool lane_act = tid < hx * tyv;
+      x = (lane_act ? 2 * (tid % hx) : 0) + i;
+      yy = lane_act ? y0 + tid / hx : y0;
+      act = lane_act && x < nx;
     } else {
       const int lin = tid + i * NT;
       act = lin < npts;
@@ -300,21 +346,23 @@ __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t lo
     vo[i] = act ? (x + nx * yy) : -1;
     os[i] = act ? vo[i] * ES : kOOB;
     oy[i] = act ? vo[i] * ESY : kOOB;
-    // a pair's second row past the tile's last: its partner reads it as a
-    // neighbour (the next tile's row, the wrapped one, or zero beyond a face)
-    if (PAIR && !act && (yy < ny || A.periodic)) oy[i] = (x + nx * wrapi(yy, ny)) * ESY;
     opv[i] = act ? vo[i] * ESP : kOOB;
     oc[i] = act ? vo[i] * EC : kOOB;
     o4[i] = act ? vo[i] * 4 : kOOB;
+    // a pair's second row past the tile's last: its partner reads it as a
+    // neighbour (the next tile's row, the wrapped one, or zero beyond a face)
+    if (ROWS && !act && (yy < ny || A.periodic)) oy[i] = (x + nx * wrapi(yy, ny)) * ESY;
     li[i] = act ? (R + yy - y0) * W + R + x : dumpi;
     lr[i] = (R + yy - y0) * W + R + x;
-    if (PAIR && yy - i >= y0 + tyv) lr[i] = (R + i) * W + R + x;  // inactive pair: in-range reads, nothing stored
+    if (ROWS && yy - i >= y0 + tyv) lr[i] = (R + i) * W + R + x;  // inactive pair: in-range reads, nothing stored
   }
 
   // halo cells of a plane (y-halo rows, then periodic x-halo columns): LDS
   // target (dump when unused) and source byte offset (kOOB reads zero)
-  const int nhy = 2 * R * nx;
-  const int nh = nhy + (A.periodic ? 2 * R * tyv : 0);
+  constexpr int HW = PAIR ? 2 : 1;  // cells of a halo entry, neighbours in x
+  const int hrow = PAIR ? hx : nx;  // entries of a y-halo row
+  const int nhy = 2 * R * hrow;
+  const int nh = nhy + (A.periodic ? 2 * R / HW * tyv : 0);
   int hl[HM], hoff[HM];
 #pragma unroll
   for (int j = 0; j < HM; ++j) {
@@ -324,13 +372,13 @@ __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t lo
     if (e < nh) {
       int x, yy;
       if (e < nhy) {
-        const int r = e / nx;
-        x = e % nx;
+        const int r = e / hrow;
+        x = e % hrow * HW;
         yy = r < R ? y0 - R + r : y0 + tyv + (r - R);
         hl[j] = (r < R ? r : R + tyv + (r - R)) * W + R + x;
       } else {
         const int e2 = e - nhy;
-        const int row = e2 / (2 * R), c2 = e2 % (2 * R);
+        const int row = e2 / (2 * R / HW), c2 = e2 % (2 * R / HW) * HW;
         x = c2 < R ? c2 - R : nx + (c2 - R);
         yy = y0 + row;
         hl[j] = (R + row) * W + (c2 < R ? c2 : nx + c2);
@@ -371,20 +419,67 @@ __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t lo
   // in a register merge whose copy waits for the load at once, which drains
   // every prefetch in flight.
   auto clampz = [&](int zz) { return min(zz, nz - 1); };
-  // one element of the y stream (plane offset in elements), and of yprev
+  // the lane's elements of the y stream (plane offset in elements) at a byte
+  // offset per element (pairs: the first one's), and of yprev
+  struct Pts {
+    TC e[P];
+  };
+  auto pair_of = [&](auto tag, auto aux, __amdgpu_buffer_rsrc_t r, int voff, int soff) {
+    using T = decltype(tag);
+    T d[2];
+    bload2<decltype(aux)::value>(r, voff, soff, d);
+    Pts o{};
+    o.e[0] = static_cast<TC>(d[0]);
+    if constexpr (P == 2) o.e[1] = static_cast<TC>(d[1]);
+    return o;
+  };
+  using std::integral_constant;
   auto ldy = [&](int v, int voff, int splane) -> TC {
     if constexpr ((HF & 1) != 0)
       return bload_h<TC, 0>(ry[v], voff, splane * 2);
     else
       return static_cast<TC>(bload<TS>(ry[v], voff, splane * ES));
   };
-  auto ldp = [&](int i, int v, int splane) -> TC {
-    if constexpr ((HF & 2) != 0)
-      return bload_h<TC, kPrevAux>(rp[v], opv[i], splane * 2);
-    else
-      return static_cast<TC>(bload_p<kPrevAux>(rp[v], opv[i], splane * ES, (TS*)nullptr));
+  auto ldy2 = [&](int v, int voff, int splane) -> TC2 {  // a pair
+    if constexpr ((HF & 1) != 0) {
+      return TC2{bload_h<TC, 0>(ry[v], voff, splane * 2), bload_h<TC, 0>(ry[v], voff + 2, splane * 2)};
+    } else {
+      TS d[2];
+      bload2<0>(ry[v], voff, splane * ES, d);
+      return TC2{static_cast<TC>(d[0]), static_cast<TC>(d[1])};
+    }
   };
-  auto ldq = [&](int i, int v, int zq) -> TC { return ldy(v, zq < 0 ? kOOB : oy[i], max(zq, 0) * pp); };
+  auto ldp = [&](int v, int splane) -> Pts {
+    Pts o;
+    if constexpr ((HF & 2) != 0) {
+#pragma unroll
+      for (int i = 0; i < P; ++i) o.e[i] = bload_h<TC, kPrevAux>(rp[v], opv[i], splane * 2);
+    } else if constexpr (PAIR) {
+      o = pair_of(TS{}, integral_constant<int, kPrevAux>{}, rp[v], opv[0], splane * ES);
+    } else {
+#pragma unroll
+      for (int i = 0; i < P; ++i)
+        o.e[i] = static_cast<TC>(bload_p<kPrevAux>(rp[v], opv[i], splane * ES, (TS*)nullptr));
+    }
+    return o;
+  };
+  auto ldq = [&](int v, int zq) -> Pts {
+    Pts o;
+    if constexpr (PAIR) {
+      const TC2 d = ldy2(v, zq < 0 ? kOOB : oy[0], max(zq, 0) * pp);
+      o.e[0] = d[0];
+      o.e[P - 1] = d[1];
+    } else {
+#pragma unroll
+      for (int i = 0; i < P; ++i) o.e[i] = ldy(v, zq < 0 ? kOOB : oy[i], max(zq, 0) * pp);
+    }
+    return o;
+  };
+  using HT = std::conditional_t<PAIR, TC2, TC>;
+  auto ldh = [&](int v, int j, int splane) -> HT {
+    if constexpr (PAIR) return ldy2(v, hoff[j], splane);
+    else return ldy(v, hoff[j], splane);
+  };
 
   // register queue: q[i][v][slot] holds plane z - R + ((slot - ph) mod Q)
   // while plane z is computed at phase ph = (z - z0) mod Q, so the queue
@@ -395,9 +490,11 @@ __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t lo
   for (int s = 0; s < Q - 1; ++s) {
     const int zq = qplane(z0 - R + s);
 #pragma unroll
-    for (int i = 0; i < P; ++i)
+    for (int v = 0; v < NV; ++v) {
+      const Pts o = ldq(v, zq);
 #pragma unroll
-      for (int v = 0; v < NV; ++v) q[i][v][s] = ldq(i, v, zq);
+      for (int i = 0; i < P; ++i) q[i][v][s] = o.e[i];
+    }
   }
 
   // prefetch registers.  Two planes ahead: the queue front fr (plane z+1+R
@@ -406,40 +503,61 @@ __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t lo
   TC fr[P][NV], yp1[P][NV], yp2[P][NV], vn[P];
   int rp1[P], rp2[P], ea[P];
   Ent4<TC> ev[P];
-  TC hv[NV][HM];
+  HT hv[NV][HM];
+  auto ldrev = [&](int z) {  // reverse-CSR words of plane z
+    if constexpr (PAIR) {
+      int d[2];
+      bload2<0>(rk, o4[0], z * pp * 4, d);
+      rp2[0] = d[0];
+      rp2[P - 1] = d[1];
+    } else {
+#pragma unroll
+      for (int i = 0; i < P; ++i) rp2[i] = bload<int>(rk, o4[i], z * pp * 4);
+    }
+  };
   auto load_rest = [&](int z) {  // V, entry payload, rev word (z+1) of plane z
     const int so = z * pp;
+    if constexpr (PAIR) {
+      const Pts o = pair_of(TC{}, integral_constant<int, 0>{}, rv, oc[0], so * EC);
+#pragma unroll
+      for (int i = 0; i < P; ++i) vn[i] = o.e[i];
+    }
 #pragma unroll
     for (int i = 0; i < P; ++i) {
-      vn[i] = bload<TC>(rv, oc[i], so * EC);
+      if constexpr (!PAIR) vn[i] = bload<TC>(rv, oc[i], so * EC);
       rp1[i] = rp2[i];
       const int e0 = rp1[i] & EMASK;  // points without projectors name the zero sentinel
       ev[i] = load_ent<TC>(re, e0 * 4 * EC);
       ea[i] = bload<int>(ra, e0 * 4, 0);
-      rp2[i] = bload<int>(rk, o4[i], clampz(z + 1) * pp * 4);  // unused past the chunk
     }
+    ldrev(clampz(z + 1));  // unused past the chunk
   };
   {
     const int zq0 = qplane(z0 + R), zq1 = qplane(z0 + 1 + R);
 #pragma unroll
-    for (int i = 0; i < P; ++i) {
+    for (int v = 0; v < NV; ++v) {
+      const Pts o = ldq(v, zq0), f = ldq(v, zq1);
 #pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        q[i][v][Q - 1] = ldq(i, v, zq0);
-        fr[i][v] = ldq(i, v, zq1);
-        if (MODE == kFilter) {
-          yp1[i][v] = ldp(i, v, z0 * pp);
-          yp2[i][v] = ldp(i, v, clampz(z0 + 1) * pp);
+      for (int i = 0; i < P; ++i) {
+        q[i][v][Q - 1] = o.e[i];
+        fr[i][v] = f.e[i];
+      }
+      if (MODE == kFilter) {
+        const Pts a = ldp(v, z0 * pp), b = ldp(v, clampz(z0 + 1) * pp);
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+          yp1[i][v] = a.e[i];
+          yp2[i][v] = b.e[i];
         }
       }
-      rp2[i] = bload<int>(rk, o4[i], z0 * pp * 4);
     }
+    ldrev(z0);
   }
   load_rest(z0);
 #pragma unroll
   for (int v = 0; v < NV; ++v)
 #pragma unroll
-    for (int j = 0; j < HM; ++j) hv[v][j] = ldy(v, hoff[j], z0 * pp);
+    for (int j = 0; j < HM; ++j) hv[v][j] = ldh(v, j, z0 * pp);
 
   // residual sweep: ||H y - lam y||^2, y^T H y and y^T y of the column (the
   // last two give its FP64 Rayleigh quotient)
@@ -454,21 +572,28 @@ __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t lo
     // (a) centre plane and its halo into LDS
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
+      if constexpr (PAIR && !HALF) {
+        *reinterpret_cast<TC2*>(buf + 2 * v * plane + li[0]) = TC2{q[0][v][QS(R)], q[P - 1][v][QS(R)]};
+      } else {
 #pragma unroll
-      for (int i = 0; i < P; ++i) buf[2 * v * plane + li[i]] = q[i][v][QS(R)];
+        for (int i = 0; i < P; ++i) buf[2 * v * plane + li[i]] = q[i][v][QS(R)];
+      }
 #pragma unroll
-      for (int j = 0; j < HM; ++j) buf[2 * v * plane + hl[j]] = hv[v][j];
+      for (int j = 0; j < HM; ++j) *reinterpret_cast<HT*>(buf + 2 * v * plane + hl[j]) = hv[v][j];
     }
     // (b) next plane's halo
 #pragma unroll
     for (int v = 0; v < NV; ++v)
 #pragma unroll
-      for (int j = 0; j < HM; ++j) hv[v][j] = ldy(v, hoff[j], clampz(z + 1) * pp);
+      for (int j = 0; j < HM; ++j) hv[v][j] = ldh(v, j, clampz(z + 1) * pp);
     lds_barrier();
     // (c) plane z
     const int so = z * pp * ES;
-    TC yr[NV][PAIR ? 2 * R + P : 1];  // paired rows: y - 6 .. y + 7 of the lane's first row
-    if constexpr (PAIR) {
+    // star sums: pairs first, for both points at once (the order per point is
+    // that of single points)
+    TC lapp[P][NV];
+    TC yr[NV][ROWS ? 2 * R + P : 1];  // paired rows: y - 6 .. y + 7 of the lane's first row
+    if constexpr (ROWS) {
       int byi = lr[0] - R * W;
       asm("" : "+v"(byi));
 #pragma unroll
@@ -478,6 +603,38 @@ __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t lo
           yr[v][e] = (e >= R && e < R + P) ? q[e < R ? 0 : (e >= R + P ? P - 1 : e - R)][v][QS(R)]
                                            : (buf + 2 * v * plane + byi)[e * W];
     }
+    if constexpr (PAIR) {
+      int bxi = lr[0] - R, byi = lr[0] - R * W;
+      asm("" : "+v"(bxi));
+      asm("" : "+v"(byi));
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        const TC* bx = buf + 2 * v * plane + bxi;
+        const TC* by = buf + 2 * v * plane + byi;
+        TC xw[2 * R + 2];  // x - 6 .. x + 7 of the first point
+#pragma unroll
+        for (int e = 0; e < R + 1; ++e) {
+          const TC2 d = e != R / 2                ? *reinterpret_cast<const TC2*>(bx + 2 * e)
+                        : HALF && vo[P - 1] < 0 ? TC2{q[0][v][QS(R)], TC(0)}
+                                                : TC2{q[0][v][QS(R)], q[P - 1][v][QS(R)]};
+          xw[2 * e] = d[0];
+          xw[2 * e + 1] = d[1];
+        }
+#pragma unroll
+        for (int i = 0; i < P; ++i) lapp[i][v] = A.wc * q[i][v][QS(R)];
+#pragma unroll
+        for (int p = 1; p <= R; ++p) {
+          const TC2 yu = *reinterpret_cast<const TC2*>(by + (R + p) * W);
+          const TC2 yd = *reinterpret_cast<const TC2*>(by + (R - p) * W);
+#pragma unroll
+          for (int i = 0; i < P; ++i) {
+            const TC sm = (xw[R + i + p] + xw[R + i - p]) + (yu[i] + yd[i]) + (q[i][v][QS(R + p)] + q[i][v][QS(R - p)]);
+            lapp[i][v] += A.w[p - 1] * sm;
+          }
+        }
+      }
+    }
+    TS first[NV];  // results of a pair's first point
 #pragma unroll
     for (int i = 0; i < P; ++i) {
       // two bases behind opaque registers, the row and the column of the
@@ -485,29 +642,41 @@ __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t lo
       // row's pair up in ds_read2; with W a multiple of 64 the column's pair
       // up in ds_read2st64), so no per-read address arithmetic remains
       int bxi = lr[i] - R, byi = lr[i] - R * W;
-      asm("" : "+v"(bxi));
-      asm("" : "+v"(byi));
+      if constexpr (!PAIR) {
+        asm("" : "+v"(bxi));
+        asm("" : "+v"(byi));
+      }
       TC hy[NV];
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
-        const TC* bx = buf + 2 * v * plane + bxi;
-        const TC* by = buf + 2 * v * plane + byi;
         const TC ctr = q[i][v][QS(R)];
-        TC lap = A.wc * ctr;
+        TC lap;
+        if constexpr (PAIR) {
+          lap = lapp[i][v];
+        } else {
+          const TC* bx = buf + 2 * v * plane + bxi;
+          const TC* by = buf + 2 * v * plane + byi;
+          lap = A.wc * ctr;
 #pragma unroll
-        for (int p = 1; p <= R; ++p) {
-          TC sy;
-          if constexpr (PAIR)
-            sy = yr[v][R + i + p] + yr[v][R + i - p];
-          else
-            sy = by[(R + p) * W] + by[(R - p) * W];
-          const TC sm = (bx[R + p] + bx[R - p]) + sy + (q[i][v][QS(R + p)] + q[i][v][QS(R - p)]);
-          lap += A.w[p - 1] * sm;
+          for (int p = 1; p <= R; ++p) {
+            TC sy;
+            if constexpr (ROWS)
+              sy = yr[v][R + i + p] + yr[v][R + i - p];
+            else
+              sy = by[(R + p) * W] + by[(R - p) * W];
+            const TC sm = (bx[R + p] + bx[R - p]) + sy + (q[i][v][QS(R + p)] + q[i][v][QS(R - p)]);
+            lap += A.w[p - 1] * sm;
+          }
         }
         hy[v] = lap + vn[i] * ctr;
         // one projector set per point is prefetched (absent: zero payload)
         const TC* al = alds + v * A.nproj + ea[i];
-        hy[v] += ev[i].v[0] * al[0] + ev[i].v[1] * al[1] + ev[i].v[2] * al[2] + ev[i].v[3] * al[3];
+        if constexpr (PAIR) {
+          const TC2 al01 = *reinterpret_cast<const TC2*>(al), al23 = *reinterpret_cast<const TC2*>(al + 2);
+          hy[v] += ev[i].v[0] * al01[0] + ev[i].v[1] * al01[1] + ev[i].v[2] * al23[0] + ev[i].v[3] * al23[1];
+        } else {
+          hy[v] += ev[i].v[0] * al[0] + ev[i].v[1] * al[1] + ev[i].v[2] * al[2] + ev[i].v[3] * al[3];
+        }
       }
       const int ne = static_cast<int>(static_cast<uint32_t>(rp1[i]) >> 27);
       if (ne > 1) {  // rare: overlapping projector sets
@@ -524,11 +693,15 @@ __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t lo
       }
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
-        if (MODE == kApply) {
-          bstore(static_cast<TS>(hy[v]), ro[v], os[i], so);
-        } else if (MODE == kFilter) {
-          const TC r = ca * (hy[v] - cc * q[i][v][QS(R)]) - cb * yp1[i][v];
-          bstore_p<kOutAux>(static_cast<TS>(r), ro[v], os[i], so);
+        if (MODE == kApply || MODE == kFilter) {
+          const TC r = MODE == kApply ? hy[v] : ca * (hy[v] - cc * q[i][v][QS(R)]) - cb * yp1[i][v];
+          constexpr int AUX = MODE == kApply ? 0 : kOutAux;
+          if constexpr (!PAIR || HALF)
+            bstore_p<AUX>(static_cast<TS>(r), ro[v], os[i], so);
+          else if (i == 0)
+            first[v] = static_cast<TS>(r);
+          else
+            bstore2<AUX>(first[v], static_cast<TS>(r), ro[v], os[0], so);
         } else if (vo[i] >= 0) {
           const double hv = static_cast<double>(hy[v]), yv = static_cast<double>(q[i][v][QS(R)]);
           const double d = hv - lamc * yv;
@@ -550,17 +723,20 @@ __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t lo
     {
       const int zq = qplane(z + 2 + R);
 #pragma unroll
-      for (int i = 0; i < P; ++i)
+      for (int v = 0; v < NV; ++v) {
+        const Pts f = ldq(v, zq);
 #pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          fr[i][v] = ldq(i, v, zq);
-          if (MODE == kFilter) yp2[i][v] = ldp(i, v, clampz(z + 2) * pp);
+        for (int i = 0; i < P; ++i) fr[i][v] = f.e[i];
+        if (MODE == kFilter) {
+          const Pts b = ldp(v, clampz(z + 2) * pp);
+#pragma unroll
+          for (int i = 0; i < P; ++i) yp2[i][v] = b.e[i];
         }
+      }
       load_rest(clampz(z + 1));
     }
   };
 
-  using std::integral_constant;
   for (int z = z0; z < z1; z += Q) {
     step(integral_constant<int, 0>{}, z);
     if (z + 1 < z1) step(integral_constant<int, 1>{}, z + 1); else break;
@@ -598,10 +774,10 @@ __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t lo
   }
 }
 
-template <typename TS, typename TC, int MODE, int P, int NT, int WS, int NV, int HF, int HM, bool PAIR>
+template <typename TS, typename TC, int MODE, int P, int NT, int WS, int NV, int HF, int HM, int PK>
 __global__ __launch_bounds__(NT) void hstencil_kernel(HArgs<TS, TC> A) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  stencil_tile<TS, TC, MODE, P, NT, WS, NV, HF, HM, PAIR>(A, xcd_remap(blockIdx.x, gridDim.x), A.a, A.c, A.b, smem_raw);
+  stencil_tile<TS, TC, MODE, P, NT, WS, NV, HF, HM, PK>(A, xcd_remap(blockIdx.x, gridDim.x), A.a, A.c, A.b, smem_raw);
 }
 
 // Grouped persistent filter step over many operators: item = (operator,
@@ -609,7 +785,7 @@ __global__ __launch_bounds__(NT) void hstencil_kernel(HArgs<TS, TC> A) {
 // xcd remap gives the workgroups of one XCD consecutive items, so the tiles
 // that share halo rows meet in the same L2.  Step k reads its recurrence
 // coefficients from the operator's device table.
-template <typename TS, typename TC, int P, int NT, int WS, int NV, int HM, bool PAIR>
+template <typename TS, typename TC, int P, int NT, int WS, int NV, int HM, int PK>
 __global__ __launch_bounds__(NT) void hstencil_group_kernel(const HArgs<TS, TC>* __restrict__ tab,
                                                             const uint2* __restrict__ items, int nitems,
                                                             int k) {
@@ -619,7 +795,7 @@ __global__ __launch_bounds__(NT) void hstencil_group_kernel(const HArgs<TS, TC>*
     const uint2 w = items[it];
     const HArgs<TS, TC> A = tab[w.x];
     const double* cf = A.coef + 3 * k;
-    stencil_tile<TS, TC, kFilter, P, NT, WS, NV, 0, HM, PAIR>(A, w.y, static_cast<TC>(cf[0]), static_cast<TC>(cf[1]),
+    stencil_tile<TS, TC, kFilter, P, NT, WS, NV, 0, HM, PK>(A, w.y, static_cast<TC>(cf[0]), static_cast<TC>(cf[1]),
                                              static_cast<TC>(cf[2]), smem_raw);
     __syncthreads();
   }
@@ -781,7 +957,7 @@ __global__ __launch_bounds__(256) void proj_forward_group_kernel(const PArgs<TS,
 
 struct TileChoice {
   int block, ty, nyt, tz, nzt, P, ws, nv, hm;
-  bool pair;
+  int pk;
   size_t smem;
 };
 
@@ -834,18 +1010,27 @@ inline TileChoice choose_tiles(int nx, int ny, int nz, int elem, int nproj, int6
   }
   // even bands: 40 rows are four tiles of 10, not three of 12 and one of 4
   // (FP32 361 -> 346 us for 9e7 points)
-  if (fit && cfg.ty == 0) ty = (ny + (ny + ty - 1) / ty - 1) / ((ny + ty - 1) / ty);
+  if (fit && cfg.ty == 0) {
+    if (elem == 8 && per_lane == 2 && (nx % 2 == 0 || !periodic)) ty = std::max(1, std::min(ty, tc.block / ((nx + 1) / 2)));
+    ty = (ny + (ny + ty - 1) / ty - 1) / ((ny + ty - 1) / ty);
+  }
   tc.P = (nx * ty + tc.block - 1) / tc.block;
-  // FP32 row pairs, where whole pairs of rows fit the workgroup
-  tc.pair = elem == 4 && tc.P == 2 && nx % 32 == 0 && (ty + 1) / 2 * nx <= tc.block;
+  // pairs: FP32 rows of whole lines where whole pairs of rows fit the
+  // workgroup; FP64 in x unless a periodic row would end in half a pair
+  const int hx = (nx + 1) / 2;
+  tc.pk = 0;
+  if (tc.P == 2 && elem == 4 && nx % 32 == 0 && (ty + 1) / 2 * nx <= tc.block) tc.pk = kRowPairs;
+  if (tc.P == 2 && elem == 8 && cfg.nv <= 1 && (nx % 2 == 0 || !periodic) && hx * ty <= tc.block &&
+      2 * R * hx + (periodic ? R * ty : 0) <= HMAX / 2 * tc.block)
+    tc.pk = nx % 2 == 0 ? kXPairs : kXHalf;
   tc.ty = ty;
   tc.nyt = (ny + ty - 1) / ty;
   tc.ws = (nx + 2 * R <= 80) ? 80 : 128;
   auto smem_of = [&](int nv) {
-    return static_cast<size_t>(elem) * nv * (2 * (static_cast<size_t>(tc.ws) * (ty + 2 * R) + 1) + nproj);
+    return static_cast<size_t>(elem) * nv * (2 * (static_cast<size_t>(tc.ws) * (ty + 2 * R) + 2) + nproj);
   };
-  if (cfg.nv > 0) {
-    tc.nv = cfg.nv;
+  if (cfg.nv > 0 || tc.pk >= kXPairs) {
+    tc.nv = std::max(cfg.nv, 1);
   } else if (!fit) {
     tc.nv = smem_of(2) <= 160 * 1024 ? 2 : 1;
   } else {
@@ -858,8 +1043,23 @@ inline TileChoice choose_tiles(int nx, int ny, int nz, int elem, int nproj, int6
   }
   if (fit) {
     const int64_t wgs = (cols + tc.nv - 1) / tc.nv * tc.nyt;
-    int64_t nzt;
-    if (tc.nv == 2)
+    int64_t nzt = 1;
+    if (tc.pk >= kXPairs) {
+      // Eight waves of these kernels are resident per CU, and a workgroup costs
+      // its planes and about four more for its start: the z range is cut where
+      // that shortens the rounds (64^3 x 480 7.5 rounds of 64 planes 781 us, 15
+      // of 32 765; 48^3 x 200 142 and 146; 53 x 61 x 47 x 229 279 and 267;
+      // 32 x 30 x 34 x 60 four cuts 20 us, two 23).
+      const int64_t slots = 256 * (tc.block == 256 ? 2 : 1);
+      int64_t best = INT64_MAX;
+      for (int64_t c = 1; c == 1 || c <= nz / 4; ++c) {
+        const int64_t cost = (wgs * c + slots - 1) / slots * ((nz + c - 1) / c + 4);
+        if (cost < best) {
+          best = cost;
+          nzt = c;
+        }
+      }
+    } else if (tc.nv == 2)
       nzt = nz >= 56 ? 2 : 1;  // a shorter last round: 64^3 x 480 -2 % in both precisions, 80^3 x 702 equal
     else
       nzt = std::max(std::min<int64_t>((3 * kTileSlots + wgs - 1) / wgs, nz / 20),
@@ -893,34 +1093,49 @@ void allow_smem(K kern, size_t smem) {
   ensure_dyn_smem(reinterpret_cast<const void*>(kern), smem);
 }
 
-template <typename TS, typename TC, int MODE, int P, int WS, int NV, int HF, bool PAIR>
-void launch_block(const HArgs<TS, TC>& args, const TileChoice& tc, dim3 grid, size_t smem, hipStream_t st) {
+template <typename TS, typename TC, int MODE, int P, int WS, int NV, int HF>
+void launch_mode(const HArgs<TS, TC>& args, const TileChoice& tc, dim3 grid, size_t smem, hipStream_t st) {
   auto go = [&](auto kern, int threads) {
     allow_smem(kern, smem);
     hipLaunchKernelGGL(kern, grid, dim3(threads), smem, st, args);
   };
-  if (tc.block == 512) {
-    go(hstencil_kernel<TS, TC, MODE, P, 512, WS, NV, HF, HMAX, PAIR>, 512);
-    return;
-  }
-  if constexpr (WS == 80) {
-    if (tc.hm == 3) {
-      go(hstencil_kernel<TS, TC, MODE, P, 256, WS, NV, HF, 3, PAIR>, 256);
+  auto single = [&](auto pk) {
+    constexpr int PK = decltype(pk)::value;
+    if (tc.block == 512) {
+      go(hstencil_kernel<TS, TC, MODE, P, 512, WS, NV, HF, HMAX, PK>, 512);
       return;
     }
-  }
-  go(hstencil_kernel<TS, TC, MODE, P, 256, WS, NV, HF, HMAX, PAIR>, 256);
-}
-
-template <typename TS, typename TC, int MODE, int P, int WS, int NV, int HF>
-void launch_mode(const HArgs<TS, TC>& args, const TileChoice& tc, dim3 grid, size_t smem, hipStream_t st) {
-  if constexpr (P == 2 && sizeof(TC) == 4) {
-    if (tc.pair) {
-      launch_block<TS, TC, MODE, P, WS, NV, HF, true>(args, tc, grid, smem, st);
-      return;
+    if constexpr (WS == 80) {
+      if (tc.hm == 3) {
+        go(hstencil_kernel<TS, TC, MODE, P, 256, WS, NV, HF, 3, PK>, 256);
+        return;
+      }
+    }
+    go(hstencil_kernel<TS, TC, MODE, P, 256, WS, NV, HF, HMAX, PK>, 256);
+  };
+  if constexpr (P == 2) {
+    if constexpr (sizeof(TC) == 4) {
+      if (tc.pk == kRowPairs) {
+        single(std::integral_constant<int, kRowPairs>{});
+        return;
+      }
+    } else if constexpr (NV == 1) {
+      auto pairs = [&](auto pk) {
+        constexpr int PK = decltype(pk)::value;
+        if (tc.block == 512) go(hstencil_kernel<TS, TC, MODE, P, 512, WS, NV, HF, HMAX / 2, PK>, 512);
+        else go(hstencil_kernel<TS, TC, MODE, P, 256, WS, NV, HF, HMAX / 2, PK>, 256);
+      };
+      if (tc.pk == kXPairs) {
+        pairs(std::integral_constant<int, kXPairs>{});
+        return;
+      }
+      if (tc.pk == kXHalf) {
+        pairs(std::integral_constant<int, kXHalf>{});
+        return;
+      }
     }
   }
-  launch_block<TS, TC, MODE, P, WS, NV, HF, false>(args, tc, grid, smem, st);
+  single(std::integral_constant<int, 0>{});
 }
 
 template <typename TS, typename TC, int MODE, int WS, int NV, int HF>
@@ -1156,7 +1371,7 @@ template <typename TS>
 struct FilterGroup {
   struct Bucket {
     int P = 1, block = 256, ws = 80, nv = 1, hm = HMAX;
-    bool pair = false;
+    int pk = 0;
     size_t smem = 0;
     uint2* items = nullptr;
     std::vector<int> count;  // items taking part in step k
@@ -1183,29 +1398,44 @@ int group_occupancy(K kern, int threads, size_t smem) {
 template <typename TS, typename BK, typename F>
 void group_dispatch(const BK& b, F&& f) {
   using std::integral_constant;
-  auto by_hm = [&](auto pc, auto wc, auto vc, auto rc) {
+  auto by_hm = [&](auto pc, auto wc, auto vc, auto kc) {
     constexpr int PP = decltype(pc)::value, WW = decltype(wc)::value, VV = decltype(vc)::value;
-    constexpr bool RR = decltype(rc)::value;
+    constexpr int KK = decltype(kc)::value;
     if (b.block == 512) {
-      f(hstencil_group_kernel<TS, TS, PP, 512, WW, VV, HMAX, RR>, 512);
+      f(hstencil_group_kernel<TS, TS, PP, 512, WW, VV, HMAX, KK>, 512);
       return;
     }
     if constexpr (WW == 80) {
       if (b.hm == 3) {
-        f(hstencil_group_kernel<TS, TS, PP, 256, WW, VV, 3, RR>, 256);
+        f(hstencil_group_kernel<TS, TS, PP, 256, WW, VV, 3, KK>, 256);
         return;
       }
     }
-    f(hstencil_group_kernel<TS, TS, PP, 256, WW, VV, HMAX, RR>, 256);
+    f(hstencil_group_kernel<TS, TS, PP, 256, WW, VV, HMAX, KK>, 256);
   };
   auto by_pair = [&](auto pc, auto wc, auto vc) {
-    if constexpr (decltype(pc)::value == 2 && sizeof(TS) == 4) {
-      if (b.pair) {
-        by_hm(pc, wc, vc, std::true_type{});
+    constexpr int PP = decltype(pc)::value, WW = decltype(wc)::value, VV = decltype(vc)::value;
+    if constexpr (PP == 2 && sizeof(TS) == 4) {
+      if (b.pk == kRowPairs) {
+        by_hm(pc, wc, vc, integral_constant<int, kRowPairs>{});
+        return;
+      }
+    } else if constexpr (PP == 2 && VV == 1) {
+      auto pairs = [&](auto kc) {
+        constexpr int KK = decltype(kc)::value;
+        if (b.block == 512) f(hstencil_group_kernel<TS, TS, PP, 512, WW, VV, HMAX / 2, KK>, 512);
+        else f(hstencil_group_kernel<TS, TS, PP, 256, WW, VV, HMAX / 2, KK>, 256);
+      };
+      if (b.pk == kXPairs) {
+        pairs(integral_constant<int, kXPairs>{});
+        return;
+      }
+      if (b.pk == kXHalf) {
+        pairs(integral_constant<int, kXHalf>{});
         return;
       }
     }
-    by_hm(pc, wc, vc, std::false_type{});
+    by_hm(pc, wc, vc, integral_constant<int, 0>{});
   };
   auto by_nv = [&](auto pc, auto wc) {
     if (b.nv == 1) by_pair(pc, wc, integral_constant<int, 1>{});
@@ -1269,7 +1499,7 @@ FilterGroup<TS>* filter_group_build(const std::vector<FilterGroupOp<TS>>& ops) {
       for (size_t j = 0; j < g->buckets.size(); ++j) {
         const auto& b = g->buckets[j];
         if (b.P == tcs[i].P && b.block == tcs[i].block && b.ws == tcs[i].ws && b.nv == tcs[i].nv &&
-            b.hm == tcs[i].hm && b.pair == tcs[i].pair)
+            b.hm == tcs[i].hm && b.pk == tcs[i].pk)
           bi = static_cast<int>(j);
       }
       if (bi < 0) {
@@ -1279,7 +1509,7 @@ FilterGroup<TS>* filter_group_build(const std::vector<FilterGroupOp<TS>>& ops) {
         b.ws = tcs[i].ws;
         b.nv = tcs[i].nv;
         b.hm = tcs[i].hm;
-        b.pair = tcs[i].pair;
+        b.pk = tcs[i].pk;
         g->buckets.push_back(b);
         bi = static_cast<int>(g->buckets.size()) - 1;
       }

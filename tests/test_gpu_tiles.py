@@ -60,3 +60,27 @@ def test_fp32_row_pairs_match_single_rows(shape, ns, periodic, ty):
             s.xls_subdomain_filter(3, -3.0, 4.0, 45.0)
             out.append(s.xls_subdomain_get_block())
     assert np.array_equal(out[0], out[1])
+
+
+# rows of even and odd length, three points a row, a half pair at the end of
+# the last row of the box, periodic rows, halo entries past one per lane, tiles
+# that fill their lanes and a short last tile
+@pytest.mark.parametrize("shape,ns,periodic", [((46, 23, 7), 3, False), ((47, 23, 7), 3, False), ((3, 100, 5), 2, False),
+                                               ((17, 21, 14), 4, False), ((24, 24, 24), 3, True), ((64, 16, 9), 2, False),
+                                               ((67, 13, 15), 2, False), ((90, 11, 8), 3, False), ((101, 9, 6), 2, False)])
+@pytest.mark.parametrize("rows", [0, 1])
+def test_fp64_x_pairs_match_single_points(shape, ns, periodic, rows):
+    print(f"[case] x pairs {shape} ns={ns} periodic={periodic} rows={rows}", flush=True)
+    sd = box(shape, ns, periodic)
+    block = 256 if shape[0] <= 80 else 512
+    ty = min(shape[1], block // ((shape[0] + 1) // 2)) - rows
+    X = np.random.default_rng(6).standard_normal((sd.nd, ns))
+    out = []
+    for band in (min(ty, max(1, block // shape[0])), ty):  # at most one point a lane, then pairs
+        with xls.Subdomain(sd) as s:
+            s.xls_subdomain_set_block(X)
+            s.xls_subdomain_tune(xls.XLS_PREC_FP64, block, band, 4, 1)
+            s.xls_subdomain_filter(3, -3.0, 4.0, 45.0)
+            out.append((s.xls_subdomain_get_block(), s.xls_hamiltonian_apply(X)))
+    assert np.array_equal(out[0][0], out[1][0])
+    assert np.array_equal(out[0][1], out[1][1])
