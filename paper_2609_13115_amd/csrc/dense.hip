@@ -311,6 +311,83 @@ __global__ __launch_bounds__(256) void trinv_kernel(const double* __restrict__ R
   for (int t = threadIdx.x; t < n; t += blockDim.x) out[t] = (t <= j) ? b[t] : 0.0;
 }
 
+// The same for n <= 64 RB, one wavefront for C columns: the columns live in
+// registers (lane l holds rows l, l + 64, ...), x_i is broadcast from its lane
+// and column i of R, loaded U steps ahead, updates the rows above, so a step is
+// a few dependent FP64 operations instead of two barriers and two LDS trips
+// (n = 480 215 -> 61 us, 1201 1005 -> 300).  The latency of R's columns bounds
+// it: U steps of loads in flight count for more than columns that share them
+// (480 with two columns and four steps 70 us, 1201 with four and two 388).
+// The quotient is corrected once by its remainder.
+template <int I, typename F>
+__device__ __forceinline__ void count_down(F& f) {
+  f(std::integral_constant<int, I>{});
+  if constexpr (I > 0) count_down<I - 1>(f);
+}
+
+template <int RB, int C, int U>
+__global__ __launch_bounds__(64) void trinv_wave_kernel(const double* __restrict__ R, int n,
+                                                        double* __restrict__ Rinv, const int32_t* __restrict__ flag) {
+  if (*flag) return;
+  const int lane = threadIdx.x, j0 = blockIdx.x * C, jl = min(j0 + C, n) - 1;
+  double b[RB][C], d[RB], inv[RB];
+#pragma unroll
+  for (int r = 0; r < RB; ++r) {
+    const int t = r * 64 + lane, tc = min(t, n - 1);
+    d[r] = R[tc + static_cast<int64_t>(tc) * n];
+    inv[r] = 1.0 / d[r];
+#pragma unroll
+    for (int c = 0; c < C; ++c) b[r][c] = t == j0 + c ? 1.0 : 0.0;
+  }
+  auto solve = [&](auto blkc) {  // rows 64 BL .. 64 BL + 63
+    constexpr int BL = decltype(blkc)::value;
+    const int top = min(jl - BL * 64, 63);
+    if (top < 0) return;
+    const double* Rb = R + static_cast<int64_t>(BL) * 64 * n;
+    double cur[U][BL + 1], nxt[U][BL + 1];
+    auto load = [&](double (&v)[U][BL + 1], int l) {  // steps l, l - 1, ..., clamped to the block
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int r = 0; r <= BL; ++r)
+          v[u][r] = Rb[min(r * 64 + lane, n - 1) + static_cast<int64_t>(max(l - u, 0)) * n];
+    };
+    load(cur, top);
+    for (int l = top; l >= 0; l -= U) {
+      load(nxt, l - U);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int ll = l - u;
+        if (ll >= 0) {
+          const double dd = lane_value(d[BL], ll), iv = lane_value(inv[BL], ll);
+#pragma unroll
+          for (int c = 0; c < C; ++c) {
+            const double bb = lane_value(b[BL][c], ll);
+            double x = bb * iv;
+            x = fma(fma(-x, dd, bb), iv, x);
+#pragma unroll
+            for (int r = 0; r < BL; ++r) b[r][c] = fma(-cur[u][r], x, b[r][c]);
+            const double up = fma(-cur[u][BL], x, b[BL][c]);
+            b[BL][c] = lane < ll ? up : (lane == ll ? x : b[BL][c]);
+          }
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int r = 0; r <= BL; ++r) cur[u][r] = nxt[u][r];
+    }
+  };
+  count_down<RB - 1>(solve);
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+      const int t = r * 64 + lane, j = j0 + c;
+      if (t < n && j < n) Rinv[t + static_cast<int64_t>(j) * n] = t <= j ? b[r][c] : 0.0;
+    }
+}
+
 __global__ void symmetrize_kernel(const double* __restrict__ A, int n, double* __restrict__ B) {
   const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (e >= static_cast<int64_t>(n) * n) return;
@@ -1548,9 +1625,26 @@ int dense_geneig(DenseWork& w, const double* Hs, const double* M, double* Y, hip
     if (hflag) return XLS_ERR_NOT_SPD;
   }
   // --- Rinv ---
-  const size_t trinv_smem = static_cast<size_t>(n) * sizeof(double);
-  set_smem(reinterpret_cast<const void*>(trinv_kernel), trinv_smem);
-  hipLaunchKernelGGL(trinv_kernel, dim3(n), dim3(256), trinv_smem, st, w.R, n, w.Rinv, w.flag);
+  auto trinv = [&](auto kern, int cols) {
+    hipLaunchKernelGGL(kern, dim3(nblk(n, cols)), dim3(64), 0, st, w.R, n, w.Rinv, w.flag);
+  };
+  if (n <= 64) {
+    trinv(trinv_wave_kernel<1, 1, 8>, 1);
+  } else if (n <= 128) {
+    trinv(trinv_wave_kernel<2, 1, 8>, 1);
+  } else if (n <= 256) {
+    trinv(trinv_wave_kernel<4, 1, 8>, 1);
+  } else if (n <= 512) {
+    trinv(trinv_wave_kernel<8, 1, 8>, 1);
+  } else if (n <= 768) {
+    trinv(trinv_wave_kernel<12, 2, 4>, 2);
+  } else if (n <= 1280) {
+    trinv(trinv_wave_kernel<20, 2, 4>, 2);
+  } else {  // past the registers
+    const size_t trinv_smem = static_cast<size_t>(n) * sizeof(double);
+    set_smem(reinterpret_cast<const void*>(trinv_kernel), trinv_smem);
+    hipLaunchKernelGGL(trinv_kernel, dim3(n), dim3(256), trinv_smem, st, w.R, n, w.Rinv, w.flag);
+  }
   XLS_LAUNCH_CHECK("trinv_kernel");
   // --- C = Rinv^T Hs Rinv, symmetrised ---
   gemm_tn<double>(XLS_PREC_FP64, w.Rinv, n, Hs, n, n, n, n, w.T, n, 0, 0, w.gemm_work,

@@ -36,6 +36,13 @@ def test_sizes(n):
     check(n, np.sort(np.random.default_rng(n).uniform(-0.4, 0.7, n)), 0.2, n)
 
 
+# both sides of the widths at which the inverse of the Cholesky factor changes
+# its columns per wavefront or leaves the registers
+@pytest.mark.parametrize("n", [256, 257, 768, 769, 1280, 1281])
+def test_inverse_widths(n):
+    test_sizes(n)
+
+
 @pytest.mark.parametrize("gap", [0.0, 1e-15, 1e-13, 1e-10, 1e-7, 1e-5])
 def test_groups_of_close_eigenvalues(gap):
     print(f"[case] dense edges groups gap={gap}", flush=True)
