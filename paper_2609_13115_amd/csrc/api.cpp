@@ -362,7 +362,7 @@ void chefsi_loop(xls_subdomain_s* s, const xls_chefsi_params_t* p, int gprec, in
   // free of the GEMMs' rounding).  The next filter's bounds always come from
   // the projected eigenvalues.
   const bool use_rq = !std::is_same<TS, double>::value || gprec != XLS_PREC_FP64;
-  std::vector<double> hq(ns);
+  std::vector<double> hq(ns), res(3 * static_cast<size_t>(ns) + 1);
   for (int it = 0; it < p->max_iter;) {
     StageTimer tm(profiling_on(), s->st);
     tm.mark();
@@ -381,19 +381,18 @@ void chefsi_loop(xls_subdomain_s* s, const xls_chefsi_params_t* p, int gprec, in
     }
     tm.mark();
     dense_stage(s);
-    XLS_HIP(hipMemcpyAsync(s->lam_dev, s->dw.lam(), ns * 8, hipMemcpyDeviceToDevice, s->st));
+    launch_take_results(s->dw.lam(), s->dw.flag, ns, s->lam_dev, s->st);
     tm.mark();
     rotate_block<TS>(s, pprec, s->Ydev);
     tm.mark();
     residual_block<TS>(s, s->lam_dev, s->resid_dev, use_rq ? s->rq_dev : nullptr);
     tm.mark();
-    int32_t spd_flag = 0;
-    XLS_HIP(hipMemcpyAsync(hl.data(), s->lam_dev, ns * 8, hipMemcpyDeviceToHost, s->st));
-    if (use_rq) XLS_HIP(hipMemcpyAsync(hq.data(), s->rq_dev, ns * 8, hipMemcpyDeviceToHost, s->st));
-    XLS_HIP(hipMemcpyAsync(hr.data(), s->resid_dev, ns * 8, hipMemcpyDeviceToHost, s->st));
-    XLS_HIP(hipMemcpyAsync(&spd_flag, s->dw.flag, 4, hipMemcpyDeviceToHost, s->st));
+    XLS_HIP(hipMemcpyAsync(res.data(), s->lam_dev, res.size() * 8, hipMemcpyDeviceToHost, s->st));
     XLS_HIP(hipStreamSynchronize(s->st));
-    if (spd_flag) {
+    std::copy(res.begin(), res.begin() + ns, hl.begin());
+    if (use_rq) std::copy(res.begin() + ns, res.begin() + 2 * ns, hq.begin());
+    std::copy(res.begin() + 2 * ns, res.begin() + 3 * ns, hr.begin());
+    if (res[3 * static_cast<size_t>(ns)] != 0.0) {
       ++total;
       fail(XLS_ERR_NOT_SPD, "overlap matrix M_s is not positive definite");
     }
@@ -644,9 +643,9 @@ void subdomain_tables(xls_subdomain_s* s, const xls_subdomain_desc_t* d, bool ke
     s->atom_core[a] = in ? 1 : 0;
   }
   // small per-state buffers (kept for the handle's lifetime)
-  s->lam_dev = dalloc<double>(s->ns);
-  s->resid_dev = dalloc<double>(s->ns);
-  s->rq_dev = dalloc<double>(s->ns);
+  s->lam_dev = dalloc<double>(3 * static_cast<size_t>(s->ns) + 1);
+  s->rq_dev = s->lam_dev + s->ns;
+  s->resid_dev = s->rq_dev + s->ns;
   s->vsmall = dalloc<double>(1024);
   s->cpart = dalloc<double>(static_cast<size_t>(s->ns) * 64);
   s->gocc = dalloc<double>(s->ns);

@@ -190,7 +190,7 @@ void tail_stages(xls_subdomain_s* s, const SubState& ss, int cur_f, double* coef
   gemm_tn<TS>(ss.pprec, Bc, s->ld, Bc, s->ld, ns, ns, s->nd, s->Mdev, ns, 1, 0, s->gwork, s->gwork_elems, s->st, s->gplan);
   gemm_tn<TS>(ss.pprec, Bc, s->ld, W, s->ld, ns, ns, s->nd, s->Hsdev, ns, 1, 1, s->gwork, s->gwork_elems, s->st, s->gplan);
   (void)dense_geneig(s->dw, s->Hsdev, s->Mdev, s->Ydev, s->st, /*check_spd=*/false);
-  XLS_HIP(hipMemcpyAsync(s->lam_dev, s->dw.lam(), ns * 8, hipMemcpyDeviceToDevice, s->st));
+  launch_take_results(s->dw.lam(), s->dw.flag, ns, s->lam_dev, s->st);
   // Psi <- Psi_f Y into the other buffer
   gemm_nn<TS>(ss.pprec, Bc, s->ld, s->Ydev, ns, static_cast<int>(s->nd), ns, ns, W, s->ld, s->bwork, s->st, s->gplan);
   launch_proj_forward<TS, double>(s->op64, W, s->ld, ns, s->alpha64, s->st);
@@ -429,23 +429,18 @@ std::vector<int> iterate_once(xls_batch_s* b, bool use_graph, std::vector<std::v
     if (b->st[i].active) act.push_back(i);
   if (act.empty()) return ended;
   b->max_active = std::max(b->max_active, static_cast<int>(act.size()));
-  std::vector<int32_t> hflag(b->n), hspd(b->n);
-  std::vector<std::vector<double>> hq(b->n);
+  std::vector<int32_t> hflag(b->n);
+  std::vector<std::vector<double>> res(b->n);  // as the handles lay them out
   // reported Ritz values as in a single run: FP64 Rayleigh quotients unless
   // the block and the projection are FP64
   auto use_rq = [&](int i) { return !std::is_same<TS, double>::value || b->st[i].gprec != XLS_PREC_FP64; };
   run_iteration<TS>(b, act, use_graph);
   for (int i : act) {
     xls_subdomain_s* s = b->subs[i];
-    XLS_HIP(hipMemcpyAsync(hl[i].data(), s->lam_dev, s->ns * 8, hipMemcpyDeviceToHost, b->main));
-    if (use_rq(i)) {
-      hq[i].resize(s->ns);
-      XLS_HIP(hipMemcpyAsync(hq[i].data(), s->rq_dev, s->ns * 8, hipMemcpyDeviceToHost, b->main));
-    }
-    XLS_HIP(hipMemcpyAsync(hr[i].data(), s->resid_dev, s->ns * 8, hipMemcpyDeviceToHost, b->main));
-    XLS_HIP(hipMemcpyAsync(&hspd[i], s->dw.flag, 4, hipMemcpyDeviceToHost, b->main));
-    XLS_HIP(hipMemcpyAsync(&hflag[i], b->flags + i, 4, hipMemcpyDeviceToHost, b->main));
+    res[i].resize(3 * static_cast<size_t>(s->ns) + 1);
+    XLS_HIP(hipMemcpyAsync(res[i].data(), s->lam_dev, res[i].size() * 8, hipMemcpyDeviceToHost, b->main));
   }
+  XLS_HIP(hipMemcpyAsync(hflag.data(), b->flags, hflag.size() * 4, hipMemcpyDeviceToHost, b->main));
   XLS_HIP(hipStreamSynchronize(b->main));
   float ms = 0.0f;
   XLS_HIP(hipEventElapsedTime(&ms, b->t0, b->t1));
@@ -460,9 +455,12 @@ std::vector<int> iterate_once(xls_batch_s* b, bool use_graph, std::vector<std::v
     ++ss.total_iters;
     s->last_iters = ss.total_iters;
     s->happly += static_cast<int64_t>(ss.degree + 1) * s->ns;  // filter + residual (H Psi_f counted by apply_H)
-    s->ritz = use_rq(i) ? hq[i] : hl[i];
+    const auto r = res[i].begin();
+    std::copy(r, r + s->ns, hl[i].begin());
+    std::copy(r + 2 * s->ns, r + 3 * s->ns, hr[i].begin());
+    s->ritz.assign(r + (use_rq(i) ? s->ns : 0), r + (use_rq(i) ? 2 : 1) * s->ns);
     s->have_ritz = true;
-    if (hspd[i]) {
+    if (res[i].back() != 0.0) {
       ss.status = XLS_ERR_NOT_SPD;
       ss.active = false;
     } else if (hflag[i]) {  // degenerate bounds for the next filter: stop with what we have

@@ -52,9 +52,12 @@ struct xls_subdomain_s {
   double* alpha64 = nullptr;  // [ns][nproj] FP64 (residuals of FP32 blocks)
   double* partial = nullptr;
   size_t partial_elems = 0;
+  // results of an iteration in one allocation, so that the host takes them in
+  // one copy: eigenvalues, FP64 Rayleigh quotients of the block's columns
+  // (residual sweep), residuals, the dense stage's status flag
   double* lam_dev = nullptr;
-  double* resid_dev = nullptr;
-  double* rq_dev = nullptr;  // FP64 Rayleigh quotients of the block's columns (residual sweep)
+  double* rq_dev = nullptr;     // lam_dev + ns
+  double* resid_dev = nullptr;  // lam_dev + 2 ns
   double* Mdev = nullptr;
   double* Hsdev = nullptr;
   double* Ydev = nullptr;
@@ -117,7 +120,7 @@ struct xls_subdomain_s {
 
   ~xls_subdomain_s() {
     void* ps[] = {v64, v32, val64, val32, rev_pk, rev_aoff, rev_val64, rev_val32, sup_off, sup_idx, gamma, mask,
-                  blk[0], blk[1], alpha, alpha64, partial, lam_dev, resid_dev, rq_dev, Mdev, Hsdev, Ydev, bwork,
+                  blk[0], blk[1], alpha, alpha64, partial, lam_dev, Mdev, Hsdev, Ydev, bwork,
                   vsmall, rho_dev, cpart, gocc, lz, backup, orb_off, orb_idx, orb_val, orb_gamma, orb_alpha,
                   orb_P, orb_D, orb_edges, orb_core};
     for (void* p : ps) xls::dfree(p);

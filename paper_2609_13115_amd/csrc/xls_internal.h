@@ -280,6 +280,8 @@ void launch_scatter_core(const double* rho, const uint8_t* mask, const int64_t* 
 // dos[b] = 2 sum c over lam in bin b of edges[0..nbins]
 void launch_dos(const double* lam, const double* c, int64_t n, const double* edges, int nbins, double* dos,
                 hipStream_t st);
+// out[0..n) = lam, out[3 n] = *flag (the slot behind two more rows of n)
+void launch_take_results(const double* lam, const int32_t* flag, int n, double* out, hipStream_t st);
 // Lanczos steps.  part holds nblocks partial sums; dots ndots per row of V.
 // *alpha_j = v.w, u = w - alpha_j v - beta_prev vprev (vprev may be null),
 // dots = partial sums of V_i . u for i < m
