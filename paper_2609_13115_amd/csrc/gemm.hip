@@ -190,18 +190,31 @@ __global__ __launch_bounds__(256) void gemm_tn_kernel(const TIN* __restrict__ A,
 #pragma unroll
     for (int j = 0; j < WB; ++j) acc[i][j] = typename F::acc_t{};
 
-  for (int64_t kb = kb0; kb < kend; kb += BK) {
+  // A split of a small order is a dozen slabs, each a load latency: two are in
+  // flight while a third is multiplied (unconditional loads from clamped
+  // addresses; what lies outside is zeroed on its way into LDS).
+  constexpr int IT = TILE * BK / 256;
+  struct Slab {
+    TIN a[IT], b[IT];
+  };
+  auto load = [&](Slab& v, int64_t kb) {
 #pragma unroll
-    for (int it = 0; it < (TILE * BK) / 256; ++it) {
-      const int l = tid + it * 256;
-      const int k = l % BK, r = l / BK;
-      const int64_t kk = kb + k;
-      const bool kin = kk < kend;
-      const TIN av = (kin && m0 + r < M) ? A[kk + static_cast<int64_t>(m0 + r) * lda] : TIN(0);
-      const TIN bv = (kin && n0 + r < N) ? B[kk + static_cast<int64_t>(n0 + r) * ldb] : TIN(0);
-      F::put(xh, xl, r * ST + k, av);
-      F::put(yh, yl, r * ST + k, bv);
+    for (int it = 0; it < IT; ++it) {
+      const int l = tid + it * 256, r = l / BK;
+      const int64_t kk = min(kb + l % BK, K - 1);
+      v.a[it] = A[kk + static_cast<int64_t>(min(m0 + r, M - 1)) * lda];
+      v.b[it] = B[kk + static_cast<int64_t>(min(n0 + r, N - 1)) * ldb];
     }
+  };
+  auto slab = [&](Slab& v, int64_t kb) {  // multiplies slab kb and starts slab kb + 2 BK
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const int l = tid + it * 256, k = l % BK, r = l / BK;
+      const bool kin = kb + k < kend;
+      F::put(xh, xl, r * ST + k, kin && m0 + r < M ? v.a[it] : TIN(0));
+      F::put(yh, yl, r * ST + k, kin && n0 + r < N ? v.b[it] : TIN(0));
+    }
+    load(v, kb + 2 * BK);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < BK; k += F::KS)
@@ -212,6 +225,13 @@ __global__ __launch_bounds__(256) void gemm_tn_kernel(const TIN* __restrict__ A,
           F::step(acc[bi][bj], xh, xl, yh, yl, wr * (TILE / 2) + bi * 16 + (lane & 15),
                   wc * (TILE / 2) + bj * 16 + (lane & 15), ST, k, lane);
     __syncthreads();
+  };
+  Slab s0, s1;
+  load(s0, kb0);
+  load(s1, kb0 + BK);
+  for (int64_t kb = kb0; kb < kend; kb += 2 * BK) {
+    slab(s0, kb);
+    if (kb + BK < kend) slab(s1, kb + BK);
   }
   double* Ps = P + static_cast<int64_t>(split) * M * N;
 #pragma unroll
@@ -283,7 +303,14 @@ __global__ __launch_bounds__(256) void tn_reduce_pairs_kernel(const double* __re
 #pragma unroll
       for (int u = 0; u < kRedU; ++u) s += v[u];
     }
-    for (; sp < splits; ++sp) s += src[sp * MN];
+    if (sp < splits) {  // the rest, also at once
+      double v[kRedU];
+#pragma unroll
+      for (int u = 0; u < kRedU; ++u) v[u] = src[min(sp + u, splits - 1) * MN];
+#pragma unroll
+      for (int u = 0; u < kRedU; ++u)
+        if (sp + u < splits) s += v[u];
+    }
     return s;
   };
   const double sa = va ? sum(P + ai + static_cast<int64_t>(aj) * M) : 0.0;
