@@ -268,7 +268,7 @@ __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t lo
   const int nx = A.nx, ny = A.ny, nz = A.nz;
   constexpr int W = WS;
   const int dumpi = W * (A.ty + 2 * R);  // spare slots at the end of each plane buffer
-  const int plane = dumpi + 2;           // even: pairs stay aligned in every buffer
+  const int plane = dumpi + (PAIR ? 2 : 1);  // even for pairs: aligned in every buffer
   TC* alds = lds + 2 * NV * plane;     // the columns' projection coefficients
 
   // Logical order: z chunk, then column group, then y band.  The xcd remap
@@ -1027,8 +1027,10 @@ inline TileChoice choose_tiles(int nx, int ny, int nz, int elem, int nproj, int6
   tc.nyt = (ny + ty - 1) / ty;
   tc.ws = (nx + 2 * R <= 80) ? 80 : 128;
   auto smem_of = [&](int nv) {
-    return static_cast<size_t>(elem) * nv * (2 * (static_cast<size_t>(tc.ws) * (ty + 2 * R) + 2) + nproj);
+    const size_t plane = static_cast<size_t>(tc.ws) * (ty + 2 * R) + (tc.pk >= kXPairs ? 2 : 1);
+    return static_cast<size_t>(elem) * nv * (2 * plane + nproj);
   };
+  if (tc.pk >= kXPairs && smem_of(1) > 160 * 1024) tc.pk = 0;
   if (cfg.nv > 0 || tc.pk >= kXPairs) {
     tc.nv = std::max(cfg.nv, 1);
   } else if (!fit) {
