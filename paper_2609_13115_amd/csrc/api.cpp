@@ -1225,6 +1225,7 @@ int xls_subdomain_tune(xls_subdomain_t s, int32_t prec, int32_t block, int32_t t
         dfree(s->partial);
         s->partial = np;
         s->partial_elems = need;
+        ++s->ws_gen;
       }
       s->cfg64 = c;
     } else {

@@ -242,18 +242,20 @@ void record_iteration(xls_batch_s* b, FilterGroup<TS>* g, const std::vector<int>
 
 // Everything a captured iteration bakes in: the active set, each block's
 // parity, degree, GEMM precision, lam_max (a kernel argument of the
-// coefficient update) and stencil launch shape.
+// coefficient update), the stencil launch shapes of the filter and of the FP64
+// residual sweep, and the handle's buffers (ws_gen counts their moves).
 std::string graph_key(xls_batch_s* b, const std::vector<int>& act) {
   std::ostringstream k;
   k << std::hexfloat;
   for (int i : act) {
     const xls_subdomain_s* s = b->subs[i];
-    // the launch shape too: a handle re-tuned through xls_subdomain_tune
-    // must not replay a graph of its old tiles
-    const StencilLaunch& c = s->prec == XLS_PREC_FP32 ? s->cfg32 : s->cfg64;
     k << i << (s->cur ? 'b' : 'a') << b->st[i].degree << 'p' << b->st[i].gprec << 'q' << b->st[i].pprec << 'l'
-      << b->st[i].lmax << 's' << c.block << '.' << c.ty << '.' << c.tz << '.' << c.nv << 'g'
-      << s->gplan.split_scale << '.' << s->gplan.tile_tn << '.' << s->gplan.tile_nn << ',';
+      << b->st[i].lmax;
+    // the launch shapes too: a handle re-tuned through xls_subdomain_tune
+    // must not replay a graph of its old tiles
+    for (const StencilLaunch& c : {s->cfg64, s->cfg32})
+      k << 's' << c.block << '.' << c.ty << '.' << c.tz << '.' << c.nv;
+    k << 'w' << s->ws_gen << 'g' << s->gplan.split_scale << '.' << s->gplan.tile_tn << '.' << s->gplan.tile_nn << ',';
   }
   return k.str();
 }

@@ -52,6 +52,9 @@ struct xls_subdomain_s {
   double* alpha64 = nullptr;  // [ns][nproj] FP64 (residuals of FP32 blocks)
   double* partial = nullptr;
   size_t partial_elems = 0;
+  // grows when a buffer of the working set moves: what was captured or tabled
+  // with the old addresses (a batch's graphs) is then no longer run
+  int64_t ws_gen = 0;
   // results of an iteration in one allocation, so that the host takes them in
   // one copy: eigenvalues, FP64 Rayleigh quotients of the block's columns
   // (residual sweep), residuals, the dense stage's status flag

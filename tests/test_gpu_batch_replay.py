@@ -1,0 +1,47 @@
+"""Captured batch iterations after something they baked in has changed: a
+replay must give what the same calls give eagerly."""
+import numpy as np
+import pytest
+
+from paper_2609_13115_amd import workloads, xls
+
+pytestmark = pytest.mark.gpu
+
+
+def boxes():
+    return [workloads.small_dirichlet(ns=10, index=1, shape=(13, 9, 20), h=0.6),
+            workloads.small_periodic(n=12, ns=8, index=3)]
+
+
+# odd degrees keep the block's parity from one iteration to the next, so that
+# every iteration after the first of a call has the key of a captured one
+PARAMS = [xls.chefsi_params(d, 4, xls.XLS_BOUNDS_LANCZOS) for d in (7, 11)]
+
+
+def results(b, use_graph):
+    ritz, resid, iters, _ = b.xls_batch_chefsi(PARAMS, use_graph=use_graph)
+    return ritz, resid, iters, [b.xls_batch_subdomain(i).xls_subdomain_get_block() for i in range(len(PARAMS))]
+
+
+# One row and one plane a tile: more residual partial sums than any chosen
+# shape, so the FP64 tune moves their buffer.  Then the first shape again, whose
+# graph would write to the buffer that is gone.
+@pytest.mark.parametrize("prec", [xls.XLS_PREC_FP32, xls.XLS_PREC_FP64])
+def test_replay_after_retuning_the_fp64_sweep(prec):
+    shapes = [(256, 0, 5, 1), (256, 1, 1, 1), (256, 0, 5, 1)]
+    out = []
+    for use_graph in (False, True):
+        print(f"[case] replay after retune prec={prec} graph={use_graph}", flush=True)
+        with xls.Batch(boxes(), filter_prec=prec) as b:
+            runs = []
+            for shape in shapes:
+                for i in range(len(PARAMS)):
+                    b.xls_batch_subdomain(i).xls_subdomain_tune(xls.XLS_PREC_FP64, *shape)
+                runs.append(results(b, use_graph))
+            out.append(runs)
+            stats = b.xls_batch_stats()
+    assert stats["captures"] == len(shapes) and stats["replays"] == 3 * len(shapes)
+    for eager, graph in zip(*out):
+        assert list(eager[2]) == list(graph[2])
+        for x, y in zip(eager[0] + eager[1] + eager[3], graph[0] + graph[1] + graph[3]):
+            assert np.array_equal(x, y)
