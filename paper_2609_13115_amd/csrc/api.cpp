@@ -687,6 +687,16 @@ size_t subdomain_ws_bytes(const xls_subdomain_s* s, bool shared_gemm_work) {
   return b;
 }
 
+void note_ws_addresses(xls_subdomain_s* s) {
+  const DenseWork& w = s->dw;
+  const std::vector<const void*> now = {
+      s->blk[0], s->blk[1], s->alpha, s->alpha64, s->partial, s->Mdev, s->Hsdev, s->Ydev, s->bwork, s->gwork,
+      w.R, w.Rinv, w.C0, w.C1, w.T, w.Vh, w.Z, w.vec, w.scal, w.flag, w.ivec, w.gemm_work};
+  if (now == s->ws_addr) return;
+  s->ws_addr = now;
+  ++s->ws_gen;
+}
+
 void subdomain_ws_alloc(xls_subdomain_s* s, double* shared_gwork, size_t shared_elems) {
   const size_t es = s->esize();
   const size_t bl = static_cast<size_t>(s->ld) * s->ns;
@@ -712,6 +722,7 @@ void subdomain_ws_alloc(xls_subdomain_s* s, double* shared_gwork, size_t shared_
     s->own_gwork = true;
   }
   dense_alloc(s->dw, s->ns, shared_gwork, shared_elems);
+  note_ws_addresses(s);
   s->resident = true;
 }
 
@@ -1225,7 +1236,7 @@ int xls_subdomain_tune(xls_subdomain_t s, int32_t prec, int32_t block, int32_t t
         dfree(s->partial);
         s->partial = np;
         s->partial_elems = need;
-        ++s->ws_gen;
+        note_ws_addresses(s);
       }
       s->cfg64 = c;
     } else {

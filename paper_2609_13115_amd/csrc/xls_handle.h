@@ -52,8 +52,10 @@ struct xls_subdomain_s {
   double* alpha64 = nullptr;  // [ns][nproj] FP64 (residuals of FP32 blocks)
   double* partial = nullptr;
   size_t partial_elems = 0;
-  // grows when a buffer of the working set moves: what was captured or tabled
-  // with the old addresses (a batch's graphs) is then no longer run
+  // addresses of the working set and a count of their changes: what was
+  // captured or tabled with old ones (a batch's graphs) is then no longer run.
+  // A set that comes back to the same addresses keeps its count.
+  std::vector<const void*> ws_addr;
   int64_t ws_gen = 0;
   // results of an iteration in one allocation, so that the host takes them in
   // one copy: eigenvalues, FP64 Rayleigh quotients of the block's columns
@@ -229,6 +231,8 @@ xls_subdomain_s* subdomain_create_tables(const xls_subdomain_desc_t* d);
 size_t subdomain_ws_bytes(const xls_subdomain_s* s, bool shared_gemm_work);
 void subdomain_ws_alloc(xls_subdomain_s* s, double* shared_gwork, size_t shared_elems);
 void subdomain_ws_free(xls_subdomain_s* s);
+// Advances ws_gen if a buffer of the working set has another address than at the last call.
+void note_ws_addresses(xls_subdomain_s* s);
 template <typename TS>
 void load_start_block(xls_subdomain_s* s, const double* x0);
 

@@ -45,3 +45,29 @@ def test_replay_after_retuning_the_fp64_sweep(prec):
         assert list(eager[2]) == list(graph[2])
         for x, y in zip(eager[0] + eager[1] + eager[3], graph[0] + graph[1] + graph[3]):
             assert np.array_equal(x, y)
+
+
+# Slot residency releases every working set at the end of a call and allocates
+# it anew in the next.  Other handles of the same sizes, made in between, take
+# the released addresses: the next call's sets lie elsewhere, and what the first
+# calls captured or tabled must not be run on them.
+@pytest.mark.parametrize("use_graph", [False, True])
+def test_slot_batch_whose_working_sets_moved(use_graph):
+    print(f"[case] slots moved graph={use_graph}", flush=True)
+    sds = boxes()
+    with xls.Batch(sds) as b:
+        ref = results(b, False)[:3]
+    others, start = [], []
+    with xls.Batch(sds, slots=0) as b:
+        for n in range(4):
+            ritz, resid, iters, _ = b.xls_batch_chefsi(PARAMS, use_graph=use_graph)
+            assert list(iters) == list(ref[2])
+            for x, y in zip(ritz + resid, ref[0] + ref[1]):
+                assert np.array_equal(x, y)
+            for s, X in zip(others, start):
+                assert np.array_equal(s.xls_subdomain_get_block(), X)
+            if n in (1, 2):
+                others += [xls.Subdomain(sd) for sd in sds]
+                start = [s.xls_subdomain_get_block() for s in others]
+    for s in others:
+        s.close()
