@@ -254,6 +254,16 @@ __device__ __forceinline__ Ent4<double> load_ent<double>(__amdgpu_buffer_rsrc_t 
 //   a pair, whose second value (the next row's first) is loaded but counts as
 //   the zero halo cell and is neither staged nor stored: those writes are single.
 constexpr int kRowPairs = 1, kXPairs = 2, kXHalf = 3;
+
+// Cells of a plane buffer in LDS: the rows of the band and its y halo, then the
+// spare cells that unused lanes write (two for x pairs: an even count keeps
+// every buffer aligned).  A band of an odd number of paired rows ends in half a
+// pair, whose absent row reads one row further down; that row is there too (its
+// content meets no stored value).
+__host__ __device__ constexpr int plane_cells(int ws, int ty, int pk) {
+  return ws * (ty + 2 * R + (pk == kRowPairs ? ty % 2 : 0)) + (pk >= kXPairs ? 2 : 1);
+}
+
 template <typename TS, typename TC, int MODE, int P, int NT, int WS, int NV, int HF, int HM, int PK>
 __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t logical, TC ca, TC cc, TC cb,
                                              unsigned char* smem_raw) {
@@ -267,8 +277,8 @@ __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t lo
   TC* lds = reinterpret_cast<TC*>(smem_raw);
   const int nx = A.nx, ny = A.ny, nz = A.nz;
   constexpr int W = WS;
-  const int dumpi = W * (A.ty + 2 * R);  // spare slots at the end of each plane buffer
-  const int plane = dumpi + (PAIR ? 2 : 1);  // even for pairs: aligned in every buffer
+  const int plane = plane_cells(W, A.ty, PK);
+  const int dumpi = plane - (PAIR ? 2 : 1);  // spare cells at the end of each plane buffer
   TC* alds = lds + 2 * NV * plane;     // the columns' projection coefficients
 
   // Logical order: z chunk, then column group, then y band.  The xcd remap
@@ -1027,10 +1037,9 @@ inline TileChoice choose_tiles(int nx, int ny, int nz, int elem, int nproj, int6
   tc.nyt = (ny + ty - 1) / ty;
   tc.ws = (nx + 2 * R <= 80) ? 80 : 128;
   auto smem_of = [&](int nv) {
-    const size_t plane = static_cast<size_t>(tc.ws) * (ty + 2 * R) + (tc.pk >= kXPairs ? 2 : 1);
-    return static_cast<size_t>(elem) * nv * (2 * plane + nproj);
+    return static_cast<size_t>(elem) * nv * (2 * static_cast<size_t>(plane_cells(tc.ws, ty, tc.pk)) + nproj);
   };
-  if (tc.pk >= kXPairs && smem_of(1) > 160 * 1024) tc.pk = 0;
+  if (tc.pk != 0 && smem_of(std::max(cfg.nv, 1)) > 160 * 1024) tc.pk = 0;
   if (cfg.nv > 0 || tc.pk >= kXPairs) {
     tc.nv = std::max(cfg.nv, 1);
   } else if (!fit) {
