@@ -84,3 +84,35 @@ def test_fp64_x_pairs_match_single_points(shape, ns, periodic, rows):
             out.append((s.xls_subdomain_get_block(), s.xls_hamiltonian_apply(X)))
     assert np.array_equal(out[0][0], out[1][0])
     assert np.array_equal(out[0][1], out[1][1])
+
+
+# Pairs of rows are taken where a row is whole 128-byte lines (nx 32, 64, 96) and
+# a lane holds two points: bands of odd and even height whose last one is odd,
+# even or a single row, periodic rows (the wrapped partner row, halo columns),
+# three and four halo cells a lane, both workgroup sizes and LDS row lengths, one
+# and two columns a tile, and the two steps that read a binary16 start
+@pytest.mark.parametrize("shape,block,periodic", [((32, 21, 9), 256, False), ((32, 32, 32), 256, True),
+                                                  ((64, 21, 9), 256, False), ((64, 23, 15), 512, False),
+                                                  ((64, 64, 64), 512, True), ((96, 33, 8), 512, False)])
+@pytest.mark.parametrize("nv", [1, 2])
+@pytest.mark.parametrize("half", [False, True])
+def test_paired_rows_match_one_row_a_lane(shape, block, periodic, nv, half):
+    import torch
+    sd = box(shape, 3, periodic)
+    X = np.random.default_rng(8).standard_normal((sd.nd, 3))
+    warm = torch.from_numpy(np.ascontiguousarray(X.T)).half().cuda()
+    bands = [ty for ty in range(2, 17) if 1 < shape[0] * ty / block <= 2 and (ty + 1) // 2 * shape[0] <= block]
+    assert any(ty % 2 for ty in bands) and any(ty % 2 == 0 for ty in bands)
+    ref = None
+    for ty in [1] + bands:
+        print(f"[case] paired rows {shape} block={block} periodic={periodic} nv={nv} half={half} ty={ty}", flush=True)
+        with xls.Subdomain(sd, filter_prec=xls.XLS_PREC_FP32) as s:
+            s.xls_subdomain_tune(xls.XLS_PREC_FP32, block, ty, 0, nv)
+            if half:
+                s.xls_subdomain_use_half(warm)
+            else:
+                s.xls_subdomain_set_block(X)
+            s.xls_subdomain_filter(3, -3.0, 4.0, 45.0)
+            got = s.xls_subdomain_get_block()
+        ref = got if ref is None else ref
+        assert np.array_equal(got, ref)
