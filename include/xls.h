@@ -292,11 +292,15 @@ int xls_split_bf16(const float* a, uint16_t* hi, uint16_t* lo, int64_t n);
  * (XLS_PREC_FP64 or XLS_PREC_FP32): block threads (256 or 512; 0: 256
  * when its per-thread halo budget covers the tile, else 512), ty rows
  * per tile (0: about 2 points per thread), tz planes per
- * z-chunk (0: the whole box), nv vectors per tile (1 or 2; 0: choose).  A
+ * z-chunk (0: the whole box), nv vectors per tile (1 or 2; 0: choose).  All
+ * four 0 give back the shape that a new handle has: rows, vectors and a cut of
+ * the z range chosen by the size of each launch, so that small ones fill the
+ * chip.  A
  * tile of 2 vectors reads the operator tables (V, projector entries) once
  * for both; residual sweeps always take 1.  The shape changes scheduling
  * only, never the arithmetic of a grid point.  Errors: INVALID_ARG when the
- * tile does not fit (LDS, registers, halo budget) or nv is not 0, 1 or 2. */
+ * tile does not fit (LDS, registers, halo budget), a size is negative or nv is
+ * not 0, 1 or 2. */
 int xls_subdomain_tune(xls_subdomain_t s, int32_t prec, int32_t block, int32_t ty, int32_t tz, int32_t nv);
 
 /* Launch plan of the handle's projection and rotation GEMMs (Sec. V-B.3:

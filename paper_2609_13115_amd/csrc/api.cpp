@@ -1220,11 +1220,13 @@ int xls_subdomain_tune(xls_subdomain_t s, int32_t prec, int32_t block, int32_t t
     if (!s) fail(XLS_ERR_INVALID_ARG, "NULL handle");
     if (prec != XLS_PREC_FP64 && prec != XLS_PREC_FP32) fail(XLS_ERR_INVALID_ARG, "prec must be FP64 or FP32");
     if (tz < 0) fail(XLS_ERR_INVALID_ARG, "stencil tile sizes must be >= 0");
-    StencilLaunch c;
-    c.block = block;
-    c.ty = ty;
-    c.tz = tz;
-    c.nv = nv;
+    StencilLaunch c;  // all four 0: as a handle starts
+    if (block != 0 || ty != 0 || tz != 0 || nv != 0) {
+      c.block = block;
+      c.ty = ty;
+      c.tz = tz;
+      c.nv = nv;
+    }
     stencil_validate(s->n[0], s->n[1], s->n[2], s->bc == XLS_BC_PERIODIC, prec == XLS_PREC_FP64 ? 8 : 4,
                      s->nproj(), c);
     if (prec == XLS_PREC_FP64) {

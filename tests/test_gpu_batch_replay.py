@@ -71,3 +71,18 @@ def test_slot_batch_whose_working_sets_moved(use_graph):
                 start = [s.xls_subdomain_get_block() for s in others]
     for s in others:
         s.close()
+
+
+# Four zeros give a tuned handle the shape back that it started with: the graph
+# captured before the first tune serves it again.
+def test_tune_with_zeros_restores_the_first_shape():
+    with xls.Batch(boxes(), filter_prec=xls.XLS_PREC_FP32) as b:
+        captures = []
+        for shape in (None, (0, 0, 0, 0), (256, 2, 4, 1), (0, 0, 0, 0)):
+            print(f"[case] tune {shape}", flush=True)
+            for i in range(len(PARAMS)):
+                if shape:
+                    b.xls_batch_subdomain(i).xls_subdomain_tune(xls.XLS_PREC_FP32, *shape)
+            results(b, True)
+            captures.append(b.xls_batch_stats()["captures"])
+    assert captures == [1, 1, 2, 2]
