@@ -478,20 +478,23 @@ int xls_subdomain_features(xls_subdomain_t s, double* f);
  *   edges[b+1]), the last bin closed on the right.  nbins = 0 skips it.
  * xls_batch_subdomain: borrowed handle of subdomain i (for the per-handle
  *   hooks); owned by the batch, never destroyed by the caller.
- * xls_batch_tune: times the fused filter kernel of one subdomain per shape
- *   class (precision, n[0], n[1] and n[2] rounded up to 8, boundary, atom
- *   count rounded up to 64; a member whose extents do not admit its class's
- *   shape keeps its own) over block {256, 512} x
- *   rows-per-tile {auto, 1, 2, 4, 8, 16} x vectors per tile {1, 2}, and the
+ * xls_batch_tune: times a grouped filter step per shape class (precision,
+ *   n[0], n[1] and n[2] rounded up to 8, boundary, atom count rounded up to 64;
+ *   one member in as many copies as hold the batch's points; a member whose
+ *   extents do not admit its class's shape keeps its own) under the untuned
+ *   shape and over block {256, 512} x
+ *   rows-per-tile {auto, 1, 2, 4, 8, 16} x vectors per tile {1, 2} on whole
+ *   boxes, of which one has to be 2 % faster to be taken, and the
  *   projection and rotation GEMMs of one subdomain per (precision, N_d
  *   rounded up to 32768, ns rounded up to 32) class over split scale {default, 1/2, 2, 4} x tile kind (FP32 GEMMs for
  *   FP32 batches), and applies the fastest to each class
  *   (xls_subdomain_tune, xls_subdomain_tune_gemm).  cache_path (may be
- *   NULL): JSON object "shape key": [block, ty, nv] and "gemm_... key":
+ *   NULL): JSON object "shape key": [block, ty, nv] (ty 0 with nv 1: the
+ *   untuned shape, whatever block says) and "gemm_... key":
  *   [split_scale, tile_tn, tile_nn]; known keys are taken from it without
  *   timing, new results are written back.
  *   tuned (may be NULL) = classes timed; best_ms (may be NULL) = sum over timed
- *   classes of the winning per-launch time.
+ *   classes of the winning filter step's time per subdomain.
  * xls_batch_stats: out[0] iterations of the last xls_batch_chefsi, out[1]
  *   graphs captured, out[2] graph replays, out[3] device time of those
  *   iterations (ms, events on the batch stream), out[4] the last one's,

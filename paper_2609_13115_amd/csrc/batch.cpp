@@ -616,6 +616,10 @@ void batch_chefsi(xls_batch_s* b, const xls_chefsi_params_t* P, int use_graph) {
 
 // --- autotuner -------------------------------------------------------------
 
+// End of every cache key, counted up when the kernels or candidates behind an
+// entry change: what a file holds from before is timed again.
+constexpr const char* kCacheTag = "_v2";
+
 // Shape classes: the filter kernel's tile depends on the exact row length
 // (n_x: halo budget, points per lane) and the boundary; n_y, n_z and the
 // atom count (LDS for the projection coefficients) only through their size,
@@ -623,12 +627,16 @@ void batch_chefsi(xls_batch_s* b, const xls_chefsi_params_t* P, int use_graph) {
 std::string shape_key(xls_subdomain_s* s) {
   std::ostringstream o;
   o << (s->prec == XLS_PREC_FP32 ? "f32" : "f64") << "_nx" << s->n[0] << "_ny" << (s->n[1] + 7) / 8 * 8 << "_nz"
-    << (s->n[2] + 7) / 8 * 8 << (s->bc == XLS_BC_PERIODIC ? "_p" : "_d") << "_na" << (s->n_atoms + 63) / 64 * 64;
+    << (s->n[2] + 7) / 8 * 8 << (s->bc == XLS_BC_PERIODIC ? "_p" : "_d") << "_na" << (s->n_atoms + 63) / 64 * 64
+    << kCacheTag;
   return o.str();
 }
 
-// tile shape of a class: block threads, rows per tile, vectors per tile
+// Tile shape of a class: block threads, rows per tile, vectors per tile on
+// whole boxes.  Rows 0 with one vector stand for the untuned shape, which
+// suits itself to each launch.
 using Shape = std::array<int, 3>;
+bool untuned_shape(const Shape& c) { return c[1] == 0 && c[2] == 1; }
 
 std::map<std::string, Shape> read_cache(const char* path) {
   std::map<std::string, Shape> m;
@@ -661,27 +669,51 @@ void write_cache(const char* path, const std::map<std::string, Shape>& m) {
   f << "}\n";
 }
 
-// Average fused-filter kernel time (ms) of subdomain s under launch shape cfg;
-// reads the current block and overwrites the spare one.
+// Average time (ms) per subdomain of a grouped filter step under launch shape
+// cfg, as the batch runs it: subdomain i stands for the rest of the batch, in as
+// many copies as hold its points (up to kTunePoints or kTuneCopies, where the
+// chip has been full for long), because the best shape of a lone small box, small tiles that
+// spread over the chip, is a slow one in a full launch.  A step of degree 1
+// reads the current block and writes the spare one; the copies write the same
+// values.
+constexpr int64_t kTunePoints = int64_t(1) << 27, kTuneCopies = 1024;
 template <typename TS>
-double time_filter(xls_subdomain_s* s, const StencilLaunch& cfg, hipEvent_t e0, hipEvent_t e1) {
-  const auto& op = op_of<TS>(s);
-  TS* y = B<TS>(s, s->cur);
-  TS* o = B<TS>(s, 1 - s->cur);
-  TS* al = static_cast<TS*>(s->alpha);
-  auto once = [&]() {
-    launch_stencil<TS, TS>(kFilter, op, y, s->ld, s->ns, al, o, o, 0.1, 0.0, 0.01, nullptr, nullptr, nullptr,
-                           s->st, cfg);
-  };
-  once();
-  XLS_HIP(hipEventRecord(e0, s->st));
+double time_filter(xls_batch_s* b, int i, const StencilLaunch& cfg, hipEvent_t e0, hipEvent_t e1) {
+  xls_subdomain_s* s = b->subs[i];
+  int64_t points = 0;
+  for (const auto* t : b->subs) points += t->nd * t->ns;
+  const int64_t own = s->nd * s->ns;
+  const int copies =
+      static_cast<int>(std::min(kTuneCopies, std::max<int64_t>(1, std::min(points, kTunePoints) / own)));
+  FilterGroupOp<TS> o{};
+  o.op = &op_of<TS>(s);
+  o.buf[0] = B<TS>(s, 0);
+  o.buf[1] = B<TS>(s, 1);
+  o.cur0 = s->cur;
+  o.ld = s->ld;
+  o.ncols = s->ns;
+  o.alpha = static_cast<TS*>(s->alpha);
+  o.coef = b->coef[i];
+  o.degree = 1;
+  o.cfg = cfg;
+  FilterGroup<TS>* g = filter_group_build<TS>(std::vector<FilterGroupOp<TS>>(copies, o));
   constexpr int reps = 3;
-  for (int r = 0; r < reps; ++r) once();
-  XLS_HIP(hipEventRecord(e1, s->st));
-  XLS_HIP(hipEventSynchronize(e1));
   float ms = 0.0f;
-  XLS_HIP(hipEventElapsedTime(&ms, e0, e1));
-  return ms / reps;
+  try {
+    launch_filter_coef(nullptr, s->ns, -1.0, 0.0, 1.0, 1, b->coef[i], b->flags + i, s->st);
+    filter_group_step<TS>(g, 0, s->st);
+    XLS_HIP(hipEventRecord(e0, s->st));
+    for (int r = 0; r < reps; ++r) filter_group_step<TS>(g, 0, s->st);
+    XLS_HIP(hipEventRecord(e1, s->st));
+    XLS_HIP(hipEventSynchronize(e1));
+    XLS_HIP(hipEventElapsedTime(&ms, e0, e1));
+  } catch (...) {
+    (void)hipStreamSynchronize(s->st);
+    filter_group_free(g);
+    throw;
+  }
+  filter_group_free(g);
+  return static_cast<double>(ms) / reps / copies;
 }
 
 // GEMM classes: N_d bucketed to 32768 rows (the split-K count follows it),
@@ -689,7 +721,7 @@ double time_filter(xls_subdomain_s* s, const StencilLaunch& cfg, hipEvent_t e0, 
 std::string gemm_key(xls_subdomain_s* s) {
   std::ostringstream o;
   o << "gemm_" << (s->prec == XLS_PREC_FP32 ? "f32" : "f64") << "_nd" << (s->nd + 32767) / 32768 * 32768 << "_ns"
-    << (s->ns + 31) / 32 * 32;
+    << (s->ns + 31) / 32 * 32 << kCacheTag;
   return o.str();
 }
 
@@ -800,7 +832,8 @@ int tune_batch(xls_batch_s* b, const char* cache_path, double* best_ms_out) {
   XLS_HIP(hipEventCreate(&e1));
   int tuned = 0;
   try {
-    for (auto* s : b->subs) {
+    for (int i = 0; i < b->n; ++i) {
+      xls_subdomain_s* s = b->subs[i];
       const std::string key = shape_key(s);
       if (chosen.count(key)) continue;
       auto hit = cache.find(key);
@@ -815,27 +848,39 @@ int tune_batch(xls_batch_s* b, const char* cache_path, double* best_ms_out) {
         subdomain_ws_alloc(s, b->pool_gwork[p], b->pool_gwork_elems);
         load_start_block<TS>(s, nullptr);
       }
-      double best = 1e30;
-      Shape arg{256, 0, 1};
-      for (int nv : {1, 2})
-      for (int block : {256, 512})
-        for (int ty : {0, 1, 2, 4, 8, 16}) {
-          StencilLaunch cfg = cfg_of<TS>(s);
-          cfg.block = block;
-          cfg.ty = ty;
-          cfg.tz = 0;  // as xls_subdomain_tune applies it below
-          cfg.nv = nv;
-          try {
-            stencil_validate(s->n[0], s->n[1], s->n[2], s->bc == XLS_BC_PERIODIC, sizeof(TS), s->nproj(), cfg);
-          } catch (const Error&) {
-            continue;
-          }
-          const double ms = time_filter<TS>(s, cfg, e0, e1);
-          if (ms < best) {
-            best = ms;
-            arg = {block, ty, nv};
-          }
+      auto fits = [&](const StencilLaunch& cfg) {
+        try {
+          stencil_validate(s->n[0], s->n[1], s->n[2], s->bc == XLS_BC_PERIODIC, sizeof(TS), s->nproj(), cfg);
+        } catch (const Error&) {
+          return false;
         }
+        return true;
+      };
+      // the untuned shape, and whole-box tiles where they are faster by more
+      // than such timings differ
+      constexpr double kGain = 0.98;
+      double best = time_filter<TS>(b, i, StencilLaunch{}, e0, e1), bar = kGain * best;
+      StencilLaunch narrow{};
+      narrow.block = 256;
+      narrow.tz = 0;
+      narrow.nv = 1;
+      Shape arg{fits(narrow) ? 256 : 512, 0, 1};
+      for (int nv : {1, 2})
+        for (int block : {256, 512})
+          for (int ty : {0, 1, 2, 4, 8, 16}) {
+            const Shape c{block, ty, nv};
+            StencilLaunch cfg;
+            cfg.block = block;
+            cfg.ty = ty;
+            cfg.tz = 0;  // as xls_subdomain_tune applies it below
+            cfg.nv = nv;
+            if (untuned_shape(c) || !fits(cfg)) continue;
+            const double ms = time_filter<TS>(b, i, cfg, e0, e1);
+            if (ms < bar) {
+              best = bar = ms;
+              arg = c;
+            }
+          }
       if (temp) subdomain_ws_free(s);
       chosen[key] = arg;
       best_ms[key] = best;
@@ -849,8 +894,11 @@ int tune_batch(xls_batch_s* b, const char* cache_path, double* best_ms_out) {
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   for (auto* s : b->subs) {  // a member whose extents do not admit its class's shape keeps its own
-    const auto& c = chosen[shape_key(s)];
-    (void)xls_subdomain_tune(s, s->prec, c[0], c[1], 0, c[2]);
+    const Shape& c = chosen[shape_key(s)];
+    if (untuned_shape(c))
+      (void)xls_subdomain_tune(s, s->prec, 0, 0, 0, 0);
+    else
+      (void)xls_subdomain_tune(s, s->prec, c[0], c[1], 0, c[2]);
   }
   // projection / rotation GEMM plans per (precision, N_d, ns) class
   tuned += tune_gemms<TS>(b, cache, chosen);

@@ -204,9 +204,9 @@ def tune_keys(sd, prec: int):
     pr = "f32" if prec == XLS_PREC_FP32 else "f64"
     up = lambda v, q: (v + q - 1) // q * q  # noqa: E731
     shape = (f"{pr}_nx{n[0]}_ny{up(n[1], 8)}_nz{up(n[2], 8)}_{'p' if int(sd.bc) == XLS_BC_PERIODIC else 'd'}"
-             f"_na{up(len(sd.atoms), 64)}")
+             f"_na{up(len(sd.atoms), 64)}_v2")
     nd = n[0] * n[1] * n[2]
-    return shape, f"gemm_{pr}_nd{up(nd, 32768)}_ns{up(int(sd.ns), 32)}"
+    return shape, f"gemm_{pr}_nd{up(nd, 32768)}_ns{up(int(sd.ns), 32)}_v2"
 
 
 def chefsi_params(degree: int, max_iter: int, bounds_mode: int = XLS_BOUNDS_LANCZOS, lam_lo: float = 0.0,
