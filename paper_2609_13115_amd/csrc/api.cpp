@@ -233,7 +233,8 @@ void lanczos_run(xls_subdomain_s* s, int k) {
   TS* w = V + ld * (k + 1);
   double* al = s->vsmall;         // [k]
   double* be = s->vsmall + 64;    // [k]
-  double* nrm = s->vsmall + 192;
+  double* nrm = s->vsmall + 192;  // and the results
+  double* top = s->vsmall + 200;
   double* part = s->vsmall + 256;  // [256]
   const int nblocks = 256;
   // v_1 = v0 / ||v0||
@@ -248,9 +249,14 @@ void lanczos_run(xls_subdomain_s* s, int k) {
   launch_norm_partial<TS>(w, s->nd, part, nblocks, s->st);
   launch_lanczos_scale<TS>(V, w, part, nblocks, nrm, s->nd, s->st);
   TS* alph = static_cast<TS*>(s->alpha);
-  // every step is launched; the ends of the spectrum are taken from the steps
-  // before the first that meets an invariant Krylov space
-  for (int j = 0; j < k; ++j) {
+  // The host launches ahead of the device and never waits; the ends of the
+  // spectrum are taken from the steps up to the first that meets an invariant
+  // Krylov space.  A step that finds one tells the host through pinned memory,
+  // which launches no more (an eigenvector as start: 2 or 3 steps of 20).
+  if (!s->lz_done) XLS_HIP(hipHostMalloc(reinterpret_cast<void**>(&s->lz_done), sizeof(int32_t), hipHostMallocDefault));
+  __atomic_store_n(s->lz_done, 0, __ATOMIC_RELAXED);
+  int steps = 0;
+  for (int j = 0; j < k && __atomic_load_n(s->lz_done, __ATOMIC_RELAXED) == 0; ++j) {
     TS* vj = V + j * ld;
     apply_H<TS>(s, vj, w, 1, alph);
     // u = w - alpha v - beta v_prev waits in the place of the next vector; full
@@ -260,14 +266,17 @@ void lanczos_run(xls_subdomain_s* s, int k) {
     launch_lanczos_dots<TS>(w, vj, j > 0 ? vj - ld : nullptr, part, nblocks, al + j, j > 0 ? be + j - 1 : nullptr, V,
                             ld, j + 1, s->nd, u, s->gwork, rb, s->st);
     launch_lanczos_reorth<TS>(u, V, ld, s->gwork, rb, j + 1, s->nd, w, part, nblocks, s->st);
-    launch_lanczos_scale<TS>(u, w, part, nblocks, be + j, s->nd, s->st);
+    launch_lanczos_scale<TS>(u, w, part, nblocks, be + j, s->nd, s->st, al + j, j > 0 ? be + j - 1 : nullptr, top,
+                             s->lz_done);
+    ++steps;
   }
-  launch_tridiag_extremes(al, be, k, nrm, s->st);
-  double ext[3];
+  launch_tridiag_extremes(al, be, steps, nrm, s->st);
+  double ext[4];
   XLS_HIP(hipMemcpyAsync(ext, nrm, sizeof(ext), hipMemcpyDeviceToHost, s->st));
   XLS_HIP(hipStreamSynchronize(s->st));
   s->lz_lo = ext[0];
   s->lz_up = ext[1] + ext[2];
+  s->happly -= steps - static_cast<int>(ext[3]);  // launched past the end: not part of the run
   s->lz_k = k;
   s->have_lanczos = true;
 }

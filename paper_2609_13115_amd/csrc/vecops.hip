@@ -504,13 +504,35 @@ __global__ __launch_bounds__(256) void lanczos_reorth_kernel(const TS* __restric
   if (threadIdx.x == 0) npart[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// dst = src / norm, norm the square root of the sum of npart, written to *norm
+// A norm within this of the largest entry of the tridiagonal matrix so far ends
+// the recurrence: the Krylov space is invariant.
+constexpr double kInvariant = 1e-12;
+
+// dst = src / norm, norm the square root of the sum of npart, written to *norm.
+// With done (pinned host memory), step j's launch also keeps the largest entry in
+// *top (a NaN is passed over) and sets *done where the space is invariant: the
+// host, which launches ahead, then stops.
 template <typename TS>
 __global__ __launch_bounds__(256) void lanczos_scale_kernel(TS* __restrict__ dst, const TS* __restrict__ src,
                                                             const double* __restrict__ npart, int nper,
-                                                            double* __restrict__ norm, int64_t n) {
-  const double nrm = sqrt(wave_sum(npart, nper, threadIdx.x & 63));
+                                                            double* __restrict__ norm, int64_t n,
+                                                            const double* __restrict__ alpha_j,
+                                                            const double* __restrict__ beta_prev,
+                                                            double* __restrict__ top, int32_t* __restrict__ done) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  double t = 0.0;
+  if (i == 0 && done) {
+    t = fabs(*alpha_j);
+    if (beta_prev) t = fmax(t, fmax(*beta_prev, *top));
+  }
+  const double nrm = sqrt(wave_sum(npart, nper, threadIdx.x & 63));
+  if (i == 0 && done) {
+    *top = t;
+    if (nrm <= kInvariant * t) {
+      *done = 1;
+      __threadfence_system();
+    }
+  }
   if (i == 0) *norm = nrm;
   if (i < n) dst[i] = static_cast<TS>(static_cast<double>(src[i]) / nrm);
 }
@@ -529,11 +551,10 @@ __global__ void fill_i32_kernel(int32_t* __restrict__ p, int32_t v, int64_t n) {
 
 // Smallest and largest eigenvalue of the k x k symmetric tridiagonal T
 // (diagonal alpha, off-diagonal beta[0..k-2]) by Sturm counts, cut at the first
-// step whose beta is within 1e-12 of the largest entry so far (an invariant
-// Krylov space; what follows it is not used).  One wave per end: every round
+// step whose beta ends the recurrence (what follows it is not used).  One wave per end: every round
 // counts at 63 interior points of the interval, which shrinks it 64-fold, to
 // the last bits of FP64 (one lane halving it took 105 us for k = 20).  out[2]
-// is |beta| of the last step used.
+// is |beta| of the last step used, out[3] the number of steps used.
 __global__ __launch_bounds__(128) void tridiag_extremes_kernel(const double* __restrict__ alpha,
                                                                const double* __restrict__ beta, int k,
                                                                double* __restrict__ out) {
@@ -549,7 +570,7 @@ __global__ __launch_bounds__(128) void tridiag_extremes_kernel(const double* __r
     const double x = fabs(al[j]);
     if (sa < x) sa = x;
     if (sb < be[j]) sb = be[j];
-    if (be[j] <= 1e-12 * (sa < sb ? sb : sa)) {
+    if (be[j] <= kInvariant * (sa < sb ? sb : sa)) {
       k = j + 1;
       break;
     }
@@ -581,7 +602,10 @@ __global__ __launch_bounds__(128) void tridiag_extremes_kernel(const double* __r
     if (f > 0) lo = nlo;
   }
   if (lane == 0) out[which] = 0.5 * (lo + hi);
-  if (threadIdx.x == 0) out[2] = fabs(be[k - 1]);
+  if (threadIdx.x == 0) {
+    out[2] = fabs(be[k - 1]);
+    out[3] = k;
+  }
 }
 
 template <typename TS>
@@ -770,8 +794,9 @@ void launch_norm_partial(const TS* x, int64_t n, double* part, int nblocks, hipS
 
 template <typename TS>
 void launch_lanczos_scale(TS* dst, const TS* src, const double* part, int nblocks, double* norm, int64_t n,
-                          hipStream_t st) {
-  hipLaunchKernelGGL(lanczos_scale_kernel<TS>, dim3(nblk(n, 256)), dim3(256), 0, st, dst, src, part, nblocks, norm, n);
+                          hipStream_t st, const double* alpha_j, const double* beta_prev, double* top, int32_t* done) {
+  hipLaunchKernelGGL(lanczos_scale_kernel<TS>, dim3(nblk(n, 256)), dim3(256), 0, st, dst, src, part, nblocks, norm, n,
+                     alpha_j, beta_prev, top, done);
   XLS_LAUNCH_CHECK("lanczos_scale_kernel");
 }
 
@@ -809,7 +834,8 @@ void launch_block_to_double(const TS* src, int64_t lds_, double* dst, int64_t ld
   template void launch_lanczos_reorth<TS>(const TS*, const TS*, int64_t, const double*, int, int, int64_t, TS*, \
                                           double*, int, hipStream_t);                               \
   template void launch_norm_partial<TS>(const TS*, int64_t, double*, int, hipStream_t);             \
-  template void launch_lanczos_scale<TS>(TS*, const TS*, const double*, int, double*, int64_t, hipStream_t); \
+  template void launch_lanczos_scale<TS>(TS*, const TS*, const double*, int, double*, int64_t, hipStream_t, \
+                                         const double*, const double*, double*, int32_t*);          \
   template void launch_convert_block<TS>(const double*, int64_t, TS*, int64_t, int64_t, int,        \
                                          hipStream_t);                                              \
   template void launch_block_to_double<TS>(const TS*, int64_t, double*, int64_t, int64_t, int,      \

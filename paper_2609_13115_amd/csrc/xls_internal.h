@@ -295,12 +295,15 @@ void launch_lanczos_reorth(const TS* u, const TS* V, int64_t ldv, const double* 
                            TS* w, double* part, int nblocks, hipStream_t st);
 template <typename TS>
 void launch_norm_partial(const TS* x, int64_t n, double* part, int nblocks, hipStream_t st);
-// *norm = sqrt of the sum of part, dst = src / *norm
+// *norm = sqrt of the sum of part, dst = src / *norm.  In a step (done not null,
+// pinned host memory) *top grows to the largest entry so far (beta_prev null: it
+// starts) and *done = 1 if *norm ends the recurrence.
 template <typename TS>
 void launch_lanczos_scale(TS* dst, const TS* src, const double* part, int nblocks, double* norm, int64_t n,
-                          hipStream_t st);
+                          hipStream_t st, const double* alpha_j = nullptr, const double* beta_prev = nullptr,
+                          double* top = nullptr, int32_t* done = nullptr);
 void launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t st);
-// out = (smallest and largest eigenvalue, |beta| of the last step used)
+// out = (smallest and largest eigenvalue, |beta| of the last step used, steps used)
 void launch_tridiag_extremes(const double* alpha, const double* beta, int k, double* out,
                              hipStream_t st);
 

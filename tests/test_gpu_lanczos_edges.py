@@ -47,3 +47,23 @@ def test_few_columns_match_many(prec):
             s.xls_subdomain_set_block(X[:, :n])
             s.xls_subdomain_filter(3, -3.0, 4.0, 45.0)
             assert np.array_equal(s.xls_subdomain_get_block(), many[:, :n])
+
+
+# The counter holds the products of the run: those of the recurrence up to its
+# end, however many steps the host had launched by then, and per iteration the
+# filter's, one for the projection and one for the residual.  A second call uses
+# the kept bounds.
+@pytest.mark.parametrize("count", [2, 5])
+def test_an_early_end_counts_the_products_that_it_took(count):
+    print(f"[case] lanczos products count={count}", flush=True)
+    sd = box((6, 5, 7), 3, False)
+    H = hamiltonian.from_subdomain(sd).apply(np.eye(sd.nd))
+    lam, U = np.linalg.eigh(0.5 * (H + H.T))
+    pick = np.unique(np.linspace(0, sd.nd - 1, count).round().astype(int))
+    sd.lanczos_v0 = U[:, pick].sum(axis=1)
+    with xls.Subdomain(sd) as s:
+        s.xls_chefsi_step(6, 1, xls.XLS_BOUNDS_LANCZOS)
+        first = s.xls_subdomain_counters()["h_applies"]
+        s.xls_chefsi_step(6, 1, xls.XLS_BOUNDS_LANCZOS)
+        assert s.xls_subdomain_counters()["h_applies"] == 3 * (6 + 2)
+    assert first == count + 3 * (6 + 2)
