@@ -954,8 +954,10 @@ unsigned march(xls_poisson_s* P, int l, const float* x, float* out) {
   A.m = level_march<KIND>(A.g, A.gc, nb);
   if (l == 0)
     hipLaunchKernelGGL((march_kernel<KIND, true>), dim3(nb), dim3(256), 0, P->s, A);
-  else
+  else if constexpr (KIND != kLast)  // the finest level's only
     hipLaunchKernelGGL((march_kernel<KIND, false>), dim3(nb), dim3(256), 0, P->s, A);
+  else
+    fail(XLS_ERR_INVALID_ARG, "the last sweep is the finest level's");
   check("march_kernel");
   return nb;
 }
