@@ -1,11 +1,13 @@
 // Hamiltonian application and the fused Chebyshev filter step (Sec. V-B.2).
-// Kernel templates; instantiated by stencil_f64.hip, stencil_f32.hip and
-// stencil_mix.hip (compiled in parallel).
+// Kernel templates; instantiated by stencil_f64.hip, stencil_f32.hip,
+// stencil_mix.hip (FP64 sweeps of FP32 blocks), stencil_f64_warm.hip and
+// stencil_f32_warm.hip (binary16 starts and grouped launches), compiled in
+// parallel.
 //
 // H y = -1/2 Lap y + V y + V_nl y with the 12th-order (n0 = 6) FD Laplacian:
 // 36 neighbour terms (+-1..6 along x, y, z) plus the centre.  One workgroup
-// owns NV columns (vectors; two by default), a band of ty full-width x-rows
-// and a z-chunk.  It streams along z: the 13 values of its points' z-column
+// owns NV columns (vectors; one or two by the size of the launch), a band of ty
+// full-width x-rows and a z-chunk.  It streams along z: the 13 values of its points' z-column
 // live in a register queue, the current xy plane (with a 6-point halo) is
 // staged in a double-buffered LDS tile, so each input plane is read from HBM
 // once per workgroup.  The nonlocal term is a gather over the reverse CSR of the point
@@ -283,7 +285,7 @@ __device__ __forceinline__ void stencil_tile(const HArgs<TS, TC>& A, uint32_t lo
 
   // Logical order: z chunk, then column group, then y band.  The xcd remap
   // hands each XCD a contiguous run of logical tiles, so when the grid is cut
-  // into z chunks (a tuning option; one chunk by default) an XCD sweeps one
+  // into z chunks (by the size of the launch, or a tuned length) an XCD sweeps one
   // chunk of many columns and its L2 holds only that chunk's V, reverse-CSR
   // words and projector payload; the bands of one column stay neighbours, so
   // their shared y-halo rows meet in the same L2.
@@ -1047,9 +1049,12 @@ inline TileChoice choose_tiles(int nx, int ny, int nz, int elem, int nproj, int6
   } else {
     // Two vectors also have to leave two workgroups per CU (FP64 past 68
     // points a row: 80^3 361 us with one vector, 514 with two), and in FP32
-    // they pay on rows of whole 32-byte sectors only (48 311 -> 295, 80 358 ->
-    // 330 us, but 46 352 -> 366, 50 332 -> 343, 60 338 -> 354, each 9e7 points).
-    const bool fits = smem_of(2) <= 80 * 1024 && (elem == 8 || nx % 8 == 0);
+    // they pay on rows of whole 32-byte sectors (48 311 -> 295, 80 358 -> 330
+    // us, but 46 352 -> 366, 50 332 -> 343, 60 338 -> 354, each 9e7 points) and
+    // on rows past 64 points, where a lane has a fourth halo cell either way (65
+    // 763 -> 733 us, 69 748 -> 690, 77 750 -> 718, 83 733 -> 692 for 1.5e8
+    // points; 60 677 -> 668, 53 699 -> 702).
+    const bool fits = smem_of(2) <= 80 * 1024 && (elem == 8 || nx % 8 == 0 || nx > 64);
     tc.nv = (fits && (cols + 1) / 2 * tc.nyt >= kTwoVecWgs) ? 2 : 1;
   }
   if (fit) {

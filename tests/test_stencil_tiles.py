@@ -54,10 +54,33 @@ int main() {
 """
 
 
-@pytest.mark.skipif(not os.path.exists(HIPCC) and shutil.which("hipcc") is None, reason="no hipcc")
-def test_tiles_stay_inside_their_plane_buffers(tmp_path):
-    src, exe = tmp_path / "sweep.hip", tmp_path / "sweep"
-    src.write_text(SWEEP)
+# Vectors per tile of FP32 launches on both sides of each condition of the rule:
+# rows of whole sectors or past 64 points, enough workgroups, and LDS for two
+# workgroups per CU
+RULE = r"""
+#include <cstdio>
+#include "stencil_impl.h"
+using namespace xls;
+using namespace xls::stencil_detail;
+void xls::fail(int code, const std::string& msg) { throw Error{code, msg}; }
+int main() {
+  const int shapes[][6] = {  // nx, ny, nz, columns, coefficients, vectors
+      {64, 64, 64, 480, 1600, 2}, {64, 64, 64, 300, 1600, 1}, {53, 61, 47, 900, 800, 1}, {60, 62, 62, 694, 800, 1},
+      {65, 67, 62, 445, 1000, 2}, {65, 67, 62, 200, 1000, 1}, {69, 68, 69, 443, 1000, 2}, {69, 68, 69, 200, 1000, 1},
+      {77, 78, 75, 700, 1600, 2}, {85, 85, 85, 500, 1600, 2}, {85, 85, 85, 500, 9000, 1}};
+  int bad = 0;
+  for (const auto& s : shapes) {
+    const TileChoice t = choose_tiles(s[0], s[1], s[2], 4, s[4], s[3], 0, StencilLaunch{});
+    if (t.nv != s[5]) ++bad, std::printf("%d %d %d x %d: %d vectors, not %d\n", s[0], s[1], s[2], s[3], t.nv, s[5]);
+  }
+  return bad != 0;
+}
+"""
+
+
+def run_program(tmp_path, source):
+    src, exe = tmp_path / "prog.hip", tmp_path / "prog"
+    src.write_text(source)
     csrc = os.path.join(ROOT, "paper_2609_13115_amd", "csrc")
     hipcc = HIPCC if os.path.exists(HIPCC) else shutil.which("hipcc")
     subprocess.run([hipcc, "--offload-host-only", "-O1", "-std=c++17", "-Wno-unused-result", "-I", csrc,
@@ -65,3 +88,16 @@ def test_tiles_stay_inside_their_plane_buffers(tmp_path):
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     print(r.stdout)
     assert r.returncode == 0, r.stdout
+
+
+needs_hipcc = pytest.mark.skipif(not os.path.exists(HIPCC) and shutil.which("hipcc") is None, reason="no hipcc")
+
+
+@needs_hipcc
+def test_tiles_stay_inside_their_plane_buffers(tmp_path):
+    run_program(tmp_path, SWEEP)
+
+
+@needs_hipcc
+def test_vectors_per_tile_of_fp32_launches(tmp_path):
+    run_program(tmp_path, RULE)
