@@ -5,20 +5,27 @@
 //
 //   M = R^T R          blocked right-looking Cholesky, 32-column panels; a
 //                      pivot at or below n*eps*M_kk reports NOT_SPD
-//   Rinv = R^-1        one workgroup per column, back-substitution in LDS
+//   Rinv = R^-1        back-substitution, one or two columns in a wavefront's
+//                      registers (n <= 1280), else one per workgroup in LDS
 //   C = Rinv^T H Rinv  MFMA GEMMs, symmetrised
-//   C = Q T Q^T        Householder tridiagonalisation, one launch per column:
-//                      every workgroup rebuilds the next Householder vector
-//                      from the previous step's product (deferred rank-2
-//                      update), then owns four trailing columns, applies the
-//                      pending update to them and forms their part of C v
+//   C = Q T Q^T        Householder tridiagonalisation, one launch per column
+//                      down to the last 192, which one workgroup does in
+//                      registers: every launch rebuilds the next Householder
+//                      vector from the previous step's product (deferred
+//                      rank-2 update), then each wavefront owns a trailing
+//                      column, applies the pending update to it and forms its
+//                      part of C v
 //   T = S L S^T        split at negligible off-diagonals; eigenvalues by
 //                      Sturm-count multisection (one wavefront per eigenvalue);
 //                      eigenvectors by inverse iteration with partial
-//                      pivoting (one wavefront per vector), modified
-//                      Gram-Schmidt inside clusters of close eigenvalues
-//   Y = Rinv Q S       reflectors applied in reverse order (LDS-resident
-//                      column blocks), then an MFMA GEMM
+//                      pivoting (one wavefront per vector, all at once), then
+//                      modified Gram-Schmidt inside clusters of close
+//                      eigenvalues, one more solve from that basis and the
+//                      final Gram-Schmidt
+//   Y = Rinv Q S       blocks of reflectors in compact WY form applied in
+//                      reverse order (columns in LDS to n = 900, in registers
+//                      to 2432; one reflector at a time below 32 and past
+//                      that), then an MFMA GEMM
 // Every launch count depends on n only, never on the data.
 // The paper's tridiagonal stage is implicit QL with the rotation sequence
 // computed serially and applied across eigenvector rows in parallel; on a GPU
@@ -1690,11 +1697,12 @@ int dense_geneig(DenseWork& w, const double* Hs, const double* M, double* Y, hip
   hipLaunchKernelGGL(tri_cluster_kernel, dim3(1), dim3(256), 0, st, raw, bs, w.scal, n, cstart, ncl, w.flag);
   const size_t inv_smem = 7 * static_cast<size_t>(n) * sizeof(double) + ((static_cast<size_t>(n) + 7) & ~size_t{7});
   set_smem(reinterpret_cast<const void*>(tri_solve_kernel), inv_smem);
-  // two solves from the start vectors, then, for clusters, an orthogonal
-  // basis, one more solve from it and the final basis
+  // two solves from the start vectors, then, for clusters (more than one state),
+  // an orthogonal basis, one more solve from it and the final basis
   for (int round = 0; round < 2; ++round) {
     hipLaunchKernelGGL(tri_solve_kernel, dim3(n), dim3(64), inv_smem, st, d, ez, bs, be, raw, cstart, ncl, w.scal, n,
                        round == 0 ? 1 : 0, round == 0 ? kInvIters - 1 : 1, w.Z, w.flag);
+    if (n == 1) break;
     hipLaunchKernelGGL(tri_ortho_kernel, dim3(n), dim3(kOrthoThreads), 0, st, bs, be, cstart, ncl, n, w.Z, w.flag);
   }
   hipLaunchKernelGGL(tri_rank_kernel, dim3(nblk(n, 256)), dim3(256), static_cast<size_t>(n) * sizeof(double), st,
