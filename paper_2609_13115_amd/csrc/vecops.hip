@@ -259,55 +259,60 @@ __global__ void pdos_hist_kernel(const double* __restrict__ P, const double* __r
 // 16-byte aligned (nd a multiple of 8 and an aligned buffer; the block's
 // columns always are), and otherwise kHalfVec values one workgroup apart, so
 // that enough bytes are in flight either way: FP32 96^3 x 1200 down 2107 -> 1095 us and up
-// 2351 -> 1101 us (5.8 TB/s) against one value a lane.
+// 2351 -> 1101 us (5.8 TB/s) against one value a lane.  FP64 takes the second
+// form on the way up: eight consecutive values a lane are stores 64 bytes apart
+// (40 x 40 x 41 x 110 35.0 -> 25.8 us, 64 x 64 x 65 x 300 219 -> 146; one value
+// a lane 28.3 and 214).  Blocks of up to kHalfSmall values take one value a lane
+// (V = 1): there the workgroups count.
 constexpr int kHalfVec = 8;
-template <typename TS, bool ALIGNED>
+constexpr int64_t kHalfSmall = int64_t(1) << 20;
+template <typename TS, bool ALIGNED, int V>
 __global__ __launch_bounds__(256) void block_to_half_kernel(const TS* __restrict__ src, int64_t ld, int64_t nd,
                                                             uint16_t* __restrict__ dst) {
-  typedef uint16_t h8 __attribute__((ext_vector_type(kHalfVec)));
-  typedef TS s8 __attribute__((ext_vector_type(kHalfVec)));
+  typedef uint16_t h8 __attribute__((ext_vector_type(V)));
+  typedef TS s8 __attribute__((ext_vector_type(V)));
   src += static_cast<int64_t>(blockIdx.y) * ld;
   dst += static_cast<int64_t>(blockIdx.y) * nd;
   if constexpr (ALIGNED) {
-    const int64_t r = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) * kHalfVec;
+    const int64_t r = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) * V;
     if (r >= nd) return;
     const s8 v = *reinterpret_cast<const s8*>(src + r);
     h8 h;
 #pragma unroll
-    for (int e = 0; e < kHalfVec; ++e) h[e] = __builtin_bit_cast(uint16_t, static_cast<_Float16>(v[e]));
+    for (int e = 0; e < V; ++e) h[e] = __builtin_bit_cast(uint16_t, static_cast<_Float16>(v[e]));
     *reinterpret_cast<h8*>(dst + r) = h;
   } else {
-    const int64_t r0 = static_cast<int64_t>(blockIdx.x) * 256 * kHalfVec + threadIdx.x;
-    TS v[kHalfVec];
+    const int64_t r0 = static_cast<int64_t>(blockIdx.x) * 256 * V + threadIdx.x;
+    TS v[V];
 #pragma unroll
-    for (int e = 0; e < kHalfVec; ++e) v[e] = src[min(r0 + e * 256, nd - 1)];
+    for (int e = 0; e < V; ++e) v[e] = src[min(r0 + e * 256, nd - 1)];
 #pragma unroll
-    for (int e = 0; e < kHalfVec; ++e)
+    for (int e = 0; e < V; ++e)
       if (r0 + e * 256 < nd) dst[r0 + e * 256] = __builtin_bit_cast(uint16_t, static_cast<_Float16>(v[e]));
   }
 }
-template <typename TS, bool ALIGNED>
+template <typename TS, bool ALIGNED, int V>
 __global__ __launch_bounds__(256) void half_to_block_kernel(const uint16_t* __restrict__ src, int64_t ld, int64_t nd,
                                                             TS* __restrict__ dst) {
-  typedef uint16_t h8 __attribute__((ext_vector_type(kHalfVec)));
-  typedef TS s8 __attribute__((ext_vector_type(kHalfVec)));
+  typedef uint16_t h8 __attribute__((ext_vector_type(V)));
+  typedef TS s8 __attribute__((ext_vector_type(V)));
   src += static_cast<int64_t>(blockIdx.y) * nd;
   dst += static_cast<int64_t>(blockIdx.y) * ld;
   if constexpr (ALIGNED) {
-    const int64_t r = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) * kHalfVec;
+    const int64_t r = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) * V;
     if (r >= nd) return;
     const h8 h = *reinterpret_cast<const h8*>(src + r);
     s8 v;
 #pragma unroll
-    for (int e = 0; e < kHalfVec; ++e) v[e] = static_cast<TS>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(h[e])));
+    for (int e = 0; e < V; ++e) v[e] = static_cast<TS>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(h[e])));
     *reinterpret_cast<s8*>(dst + r) = v;
   } else {
-    const int64_t r0 = static_cast<int64_t>(blockIdx.x) * 256 * kHalfVec + threadIdx.x;
-    uint16_t h[kHalfVec];
+    const int64_t r0 = static_cast<int64_t>(blockIdx.x) * 256 * V + threadIdx.x;
+    uint16_t h[V];
 #pragma unroll
-    for (int e = 0; e < kHalfVec; ++e) h[e] = src[min(r0 + e * 256, nd - 1)];
+    for (int e = 0; e < V; ++e) h[e] = src[min(r0 + e * 256, nd - 1)];
 #pragma unroll
-    for (int e = 0; e < kHalfVec; ++e)
+    for (int e = 0; e < V; ++e)
       if (r0 + e * 256 < nd) dst[r0 + e * 256] = static_cast<TS>(__builtin_bit_cast(_Float16, h[e]));
   }
 }
@@ -664,19 +669,25 @@ template <typename TS>
 void launch_block_half(const TS* blk, int64_t ld, int64_t nd, int ncols, uint16_t* half, int to_half,
                        hipStream_t st) {
   if (nd <= 0 || ncols <= 0) return;
-  const dim3 grid(nblk(nd, 256 * kHalfVec), static_cast<unsigned>(ncols));
   const auto a16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
   // vectors of TS values need no more than 16-byte alignment each
   const bool al = nd % kHalfVec == 0 && ld % kHalfVec == 0 && a16(half) && a16(blk);
+  const bool small = nd * ncols <= kHalfSmall;
   TS* out = const_cast<TS*>(blk);
-  if (to_half && al)
-    hipLaunchKernelGGL((block_to_half_kernel<TS, true>), grid, dim3(256), 0, st, blk, ld, nd, half);
-  else if (to_half)
-    hipLaunchKernelGGL((block_to_half_kernel<TS, false>), grid, dim3(256), 0, st, blk, ld, nd, half);
+  const auto go = [&](auto down, auto up, int v) {
+    const dim3 grid(nblk(nd, 256 * v), static_cast<unsigned>(ncols));
+    if (to_half)
+      hipLaunchKernelGGL(down, grid, dim3(256), 0, st, blk, ld, nd, half);
+    else
+      hipLaunchKernelGGL(up, grid, dim3(256), 0, st, half, ld, nd, out);
+  };
+  constexpr int V = kHalfVec;
+  if (small)
+    go(block_to_half_kernel<TS, false, 1>, half_to_block_kernel<TS, false, 1>, 1);
   else if (al)
-    hipLaunchKernelGGL((half_to_block_kernel<TS, true>), grid, dim3(256), 0, st, half, ld, nd, out);
+    go(block_to_half_kernel<TS, true, V>, half_to_block_kernel<TS, sizeof(TS) == 4, V>, V);
   else
-    hipLaunchKernelGGL((half_to_block_kernel<TS, false>), grid, dim3(256), 0, st, half, ld, nd, out);
+    go(block_to_half_kernel<TS, false, V>, half_to_block_kernel<TS, false, V>, V);
   XLS_LAUNCH_CHECK("block_half");
 }
 template void launch_block_half<float>(const float*, int64_t, int64_t, int, uint16_t*, int, hipStream_t);

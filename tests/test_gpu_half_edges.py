@@ -35,3 +35,25 @@ def test_half_buffers(shape, shift, prec):
         assert np.all(got[:shift] == 3.0) and np.all(got[shift + n:] == 3.0)
         s.xls_subdomain_load_half(buf)
         assert np.array_equal(s.xls_subdomain_get_block(), want.astype(np.float64))
+
+
+# blocks past the size from which a lane takes several values: whole vectors, odd
+# point counts, an unaligned buffer
+@pytest.mark.parametrize("shape,ns,shift", [((32, 32, 40), 30, 0), ((31, 33, 35), 33, 0), ((32, 32, 40), 30, 1)])
+@pytest.mark.parametrize("prec", [xls.XLS_PREC_FP64, xls.XLS_PREC_FP32])
+def test_half_buffers_of_large_blocks(shape, ns, shift, prec):
+    print(f"[case] large half buffers {shape} ns={ns} shift={shift} prec={prec}", flush=True)
+    sd = box(shape, ns, False)
+    X = np.random.default_rng(5).standard_normal((sd.nd, ns)).astype(np.float32).astype(np.float64)
+    n = sd.nd * ns
+    store = torch.full((n + 16,), 3.0, dtype=torch.float16, device="cuda")
+    buf = store[shift:shift + n]
+    want = X.astype(np.float32).astype(np.float16)
+    with xls.Subdomain(sd, filter_prec=prec) as s:
+        s.xls_subdomain_set_block(X)
+        s.xls_subdomain_store_half(buf)
+        got = store.cpu().numpy()
+        assert np.array_equal(got[shift:shift + n].reshape(ns, sd.nd).T.view(np.uint16), want.view(np.uint16))
+        assert np.all(got[:shift] == 3.0) and np.all(got[shift + n:] == 3.0)
+        s.xls_subdomain_load_half(buf)
+        assert np.array_equal(s.xls_subdomain_get_block(), want.astype(np.float64))
