@@ -1132,9 +1132,8 @@ int planned_splits(int def, const GemmPlan& plan) {
 // as are resident at once (2 per CU at edge 128, 3 at edge 96: its smaller
 // accumulator tile leaves room for a third), so that symmetric products
 // (fewer tiles) get more splits; >= 16 K slabs each.  The FP32 form counts
-// splits for the edge that issues 10 % less padded and redundant area (128 if
-// neither does), whichever edge then runs: its sums are as sensitive to their
-// order as to anything else, and so keep it.
+// splits for tn_area_edge, whichever edge then runs: its sums are as sensitive to
+// their order as to anything else, and so keep it.
 struct TnCut {
   int ntile, splits;
   int64_t kchunk;
@@ -1143,12 +1142,14 @@ int tn_tiles(int M, int N, int sym, int T) {
   const int tm = (M + T - 1) / T, tn = (N + T - 1) / T;
   return sym ? tm * (tm + 1) / 2 : tm * tn;
 }
+// the edge that issues 10 % less padded and redundant area, 128 if neither does
+int tn_area_edge(int M, int N, int sym) {
+  return 10 * int64_t{96 * 96} * tn_tiles(M, N, sym, 96) < 9 * int64_t{128 * 128} * tn_tiles(M, N, sym, 128) ? 96 : 128;
+}
 TnCut tn_cut(int M, int N, int64_t K, int sym, int T, bool f32, int bk, size_t work_elems, const GemmPlan& plan) {
   TnCut c;
   c.ntile = tn_tiles(M, N, sym, T);
-  int ts = T;
-  if (f32 && plan.tile_tn == 0)
-    ts = 10 * int64_t{96 * 96} * tn_tiles(M, N, sym, 96) < 9 * int64_t{128 * 128} * tn_tiles(M, N, sym, 128) ? 96 : 128;
+  const int ts = f32 && plan.tile_tn == 0 ? tn_area_edge(M, N, sym) : T;
   const int resident = (ts == 96) ? 3 : 2;
   int splits = planned_splits(std::max(1, resident * device_cus() / tn_tiles(M, N, sym, ts)), plan);
   splits = static_cast<int>(std::min<int64_t>(splits, std::max<int64_t>(1, K / (16 * bk))));
@@ -1166,11 +1167,17 @@ TnCut tn_cut(int M, int N, int64_t K, int sym, int T, bool f32, int bk, size_t w
 // cover its barriers, and the smaller tile about a twentieth for its LDS reads.  Measured ratios 96 / 128 follow it: 480 of FP64 0.85
 // (0.89 by the rule), 300 of FP32 0.86 (0.89), 1200 of FP32 1.01 (1.00), 1152
 // of FP32 1.12 (1.08), 200 of FP64 1.07 (1.07), 120 of FP64 0.73 (0.59).
-int tn_tile_edge(int M, int N, int64_t K, int sym, bool f32, int bk, size_t work_elems, const GemmPlan& plan) {
+// Split BF16 takes the edge by area: only entries of diagonal tiles of H_s are
+// averaged with their transposes, its two triangles differ by more than the
+// others', and the smaller tile leaves its H_s up to 1 % further off (order 100,
+// K = 35,904: 9.94e-7 against 9.85e-7) for at most 8 us.
+template <int MF>
+int tn_tile_edge(int M, int N, int64_t K, int sym, int bk, size_t work_elems, const GemmPlan& plan) {
   if (plan.tile_tn == 2) return 128;
   if (plan.tile_tn == 3) return 96;
+  if (MF == MF_BF) return tn_area_edge(M, N, sym);
   const auto cost = [&](int T) {
-    const TnCut c = tn_cut(M, N, K, sym, T, f32, bk, work_elems, plan);
+    const TnCut c = tn_cut(M, N, K, sym, T, MF == MF_F32, bk, work_elems, plan);
     const int64_t nb = static_cast<int64_t>(c.ntile) * c.splits, cus = device_cus();
     return static_cast<double>(T) * T * c.kchunk * ((nb + cus - 1) / cus) * (nb <= cus ? 1.1 : 1.0) *
            (T == 96 ? 1.05 : 1.0);
@@ -1203,7 +1210,7 @@ void tn_dispatch(const TIN* A, int64_t lda, const TIN* B, int64_t ldb, int M, in
     // products of FP32 blocks: 4 loads per 16-wide k slab and row)
     constexpr bool k96 = (96 * (BigLds<MF>::BK / VEC)) % 256 == 0;
     if constexpr (k96) {
-      if (tn_tile_edge(M, N, K, sym, MF == MF_F32, BigLds<MF>::BK, work_elems, plan) == 96) {
+      if (tn_tile_edge<MF>(M, N, K, sym, BigLds<MF>::BK, work_elems, plan) == 96) {
         tn_big_launch<TIN, MF, 96>(A, lda, B, ldb, M, N, K, C, ldc, sym, symmetrize, work, work_elems, st, plan);
         return;
       }

@@ -41,3 +41,23 @@ def test_large_tile_products(shape, ns, prec, gprec):
         out = s.xls_subdomain_get_block()
     assert rel_err(M, X.T @ X) <= 16 * np.sqrt(sd.nd) * eps_in
     assert rel_err(out, X @ Q) <= 16 * np.sqrt(ns) * eps_in + 4 * eps_out
+
+
+# Split-BF16 products take the edge that issues the less area, whatever leaves
+# the compute units less: 128 for orders that fill a tile or two of it, 96 for
+# those that it pads less by a tenth.  H_s is averaged with its transpose inside
+# diagonal tiles only, so its bits name the edge (an order inside one tile of either
+# is averaged whole).
+@pytest.mark.parametrize("ns,edge", [(100, 2), (128, 2), (200, 2), (90, 3), (140, 3)])
+def test_split_bf16_projection_edge_by_area(ns, edge):
+    print(f"[case] split-BF16 edge ns={ns}", flush=True)
+    sd = box((33, 32, 34), ns, False)
+    X = np.random.default_rng(9).standard_normal((sd.nd, ns))
+    got = []
+    for plan in (0, edge, 5 - edge):
+        with xls.Subdomain(sd, filter_prec=xls.XLS_PREC_FP32) as s:
+            s.xls_subdomain_set_block(X)
+            s.xls_subdomain_tune_gemm(0, plan, 0)
+            got.append(s.xls_subdomain_project(xls.XLS_PREC_BF16X3))
+    assert np.array_equal(got[0][1], got[1][1]) and np.array_equal(got[0][0], got[1][0])
+    assert ns <= 96 or not np.array_equal(got[0][1], got[2][1])
