@@ -1065,7 +1065,8 @@ inline TileChoice choose_tiles(int nx, int ny, int nz, int elem, int nproj, int6
       // its planes and about four more for its start: the z range is cut where
       // that shortens the rounds (64^3 x 480 7.5 rounds of 64 planes 781 us, 15
       // of 32 765; 48^3 x 200 142 and 146; 53 x 61 x 47 x 229 279 and 267;
-      // 32 x 30 x 34 x 60 four cuts 20 us, two 23).
+      // 32 x 30 x 34 x 60 four cuts 20 us, two 23: launches back to back; between
+      // the projections of a filter the 64^3 one takes 3 to 6 % longer).
       const int64_t slots = 256 * (tc.block == 256 ? 2 : 1);
       int64_t best = INT64_MAX;
       for (int64_t c = 1; c == 1 || c <= nz / 4; ++c) {
@@ -1076,7 +1077,12 @@ inline TileChoice choose_tiles(int nx, int ny, int nz, int elem, int nproj, int6
         }
       }
     } else if (tc.nv == 2)
-      nzt = nz >= 56 ? 2 : 1;  // a shorter last round: 64^3 x 480 -2 % in both precisions, 80^3 x 702 equal
+      // a shorter last round: FP32, 1.5e8 points, us whole and halved: 53 688, 702;
+      // 57 746, 760; 60 666, 668; 63 705, 682; 65 733, 748; 66 734, 721; 69 688,
+      // 690; 75 748, 730; 79 745, 727; 84 684, 664.  With more rounds the last one
+      // matters less than the planes read twice (2.7e8 points: 65 1298, 1298; 69
+      // 1243, 1230; 78 1234, 1251; 79 1273, 1293; 83 1191, 1201).
+      nzt = nz >= 56 && wgs < 3 * kTileSlots ? 2 : 1;
     else
       nzt = std::max(std::min<int64_t>((3 * kTileSlots + wgs - 1) / wgs, nz / 20),
                      std::min<int64_t>(kTileSlots / wgs, nz / 2));

@@ -56,7 +56,8 @@ int main() {
 
 # Vectors per tile of FP32 launches on both sides of each condition of the rule:
 # rows of whole sectors or past 64 points, enough workgroups, and LDS for two
-# workgroups per CU
+# workgroups per CU; two-vector tiles halve the z range until a launch has three
+# thousand of them
 RULE = r"""
 #include <cstdio>
 #include "stencil_impl.h"
@@ -64,14 +65,15 @@ using namespace xls;
 using namespace xls::stencil_detail;
 void xls::fail(int code, const std::string& msg) { throw Error{code, msg}; }
 int main() {
-  const int shapes[][6] = {  // nx, ny, nz, columns, coefficients, vectors
-      {64, 64, 64, 480, 1600, 2}, {64, 64, 64, 300, 1600, 1}, {53, 61, 47, 900, 800, 1}, {60, 62, 62, 694, 800, 1},
-      {65, 67, 62, 445, 1000, 2}, {65, 67, 62, 200, 1000, 1}, {69, 68, 69, 443, 1000, 2}, {69, 68, 69, 200, 1000, 1},
-      {77, 78, 75, 700, 1600, 2}, {85, 85, 85, 500, 1600, 2}, {85, 85, 85, 500, 9000, 1}};
+  const int shapes[][7] = {  // nx, ny, nz, columns, coefficients, vectors, z chunks of two-vector tiles
+      {64, 64, 64, 480, 1600, 2, 2}, {64, 64, 64, 300, 1600, 1, 0}, {53, 61, 47, 900, 800, 1, 0}, {60, 62, 62, 694, 800, 1, 0},
+      {65, 67, 62, 445, 1000, 2, 2}, {65, 67, 62, 200, 1000, 1, 0}, {69, 68, 69, 443, 1000, 2, 2}, {69, 68, 69, 200, 1000, 1, 0},
+      {77, 78, 75, 500, 1600, 2, 1}, {77, 78, 75, 700, 1600, 2, 1}, {85, 85, 85, 400, 1600, 2, 2}, {85, 85, 85, 500, 9000, 1, 0},
+      {64, 64, 64, 1000, 1600, 2, 1}, {48, 48, 48, 1200, 1600, 2, 1}};
   int bad = 0;
   for (const auto& s : shapes) {
     const TileChoice t = choose_tiles(s[0], s[1], s[2], 4, s[4], s[3], 0, StencilLaunch{});
-    if (t.nv != s[5]) ++bad, std::printf("%d %d %d x %d: %d vectors, not %d\n", s[0], s[1], s[2], s[3], t.nv, s[5]);
+    if (t.nv != s[5] || (s[6] && t.nzt != s[6])) ++bad, std::printf("%d %d %d x %d: %d vectors, %d chunks\n", s[0], s[1], s[2], s[3], t.nv, t.nzt);
   }
   return bad != 0;
 }
