@@ -484,7 +484,7 @@ int xls_subdomain_features(xls_subdomain_t s, double* f);
  *   extents do not admit its class's shape keeps its own) under the untuned
  *   shape and over block {256, 512} x
  *   rows-per-tile {auto, 1, 2, 4, 8, 16} x vectors per tile {1, 2} on whole
- *   boxes, of which one has to be 2 % faster to be taken, and the
+ *   boxes, of which one has to be 1 % faster to be taken, and the
  *   projection and rotation GEMMs of one subdomain per (precision, N_d
  *   rounded up to 32768, ns rounded up to 32) class over split scale {default, 1/2, 2, 4} x tile kind (FP32 GEMMs for
  *   FP32 batches), and applies the fastest to each class

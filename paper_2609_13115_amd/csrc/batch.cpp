@@ -26,6 +26,7 @@
 #include <cstring>
 #include <fstream>
 #include <map>
+#include <memory>
 #include <sstream>
 #include <string>
 #include <vector>
@@ -669,52 +670,89 @@ void write_cache(const char* path, const std::map<std::string, Shape>& m) {
   f << "}\n";
 }
 
-// Average time (ms) per subdomain of a grouped filter step under launch shape
-// cfg, as the batch runs it: subdomain i stands for the rest of the batch, in as
-// many copies as hold its points (up to kTunePoints or kTuneCopies, where the
-// chip has been full for long), because the best shape of a lone small box, small tiles that
-// spread over the chip, is a slow one in a full launch.  A step of degree 1
-// reads the current block and writes the spare one; the copies write the same
-// values.
+// Times filter steps of one subdomain's shape as the batch runs them: the
+// subdomain stands for the rest of the batch, in as many copies as hold its
+// points (up to kTunePoints or kTuneCopies, where the chip has been full for
+// long), because the best shape of a lone small box, small tiles that spread over
+// the chip, is a slow one in a full launch.  The copies read the current block;
+// the first writes the handle's spare one and the others blocks of their own
+// (fewer copies where memory is short).
 constexpr int64_t kTunePoints = int64_t(1) << 27, kTuneCopies = 1024;
 template <typename TS>
-double time_filter(xls_batch_s* b, int i, const StencilLaunch& cfg, hipEvent_t e0, hipEvent_t e1) {
-  xls_subdomain_s* s = b->subs[i];
-  int64_t points = 0;
-  for (const auto* t : b->subs) points += t->nd * t->ns;
-  const int64_t own = s->nd * s->ns;
-  const int copies =
-      static_cast<int>(std::min(kTuneCopies, std::max<int64_t>(1, std::min(points, kTunePoints) / own)));
-  FilterGroupOp<TS> o{};
-  o.op = &op_of<TS>(s);
-  o.buf[0] = B<TS>(s, 0);
-  o.buf[1] = B<TS>(s, 1);
-  o.cur0 = s->cur;
-  o.ld = s->ld;
-  o.ncols = s->ns;
-  o.alpha = static_cast<TS*>(s->alpha);
-  o.coef = b->coef[i];
-  o.degree = 1;
-  o.cfg = cfg;
-  FilterGroup<TS>* g = filter_group_build<TS>(std::vector<FilterGroupOp<TS>>(copies, o));
-  constexpr int reps = 3;
-  float ms = 0.0f;
-  try {
-    launch_filter_coef(nullptr, s->ns, -1.0, 0.0, 1.0, 1, b->coef[i], b->flags + i, s->st);
-    filter_group_step<TS>(g, 0, s->st);
-    XLS_HIP(hipEventRecord(e0, s->st));
-    for (int r = 0; r < reps; ++r) filter_group_step<TS>(g, 0, s->st);
-    XLS_HIP(hipEventRecord(e1, s->st));
-    XLS_HIP(hipEventSynchronize(e1));
-    XLS_HIP(hipEventElapsedTime(&ms, e0, e1));
-  } catch (...) {
-    (void)hipStreamSynchronize(s->st);
-    filter_group_free(g);
-    throw;
+class FilterTimer {
+ public:
+  FilterTimer(xls_batch_s* b, int i, hipEvent_t e0, hipEvent_t e1) : s_(b->subs[i]), e0_(e0), e1_(e1) {
+    int64_t points = 0;
+    for (const auto* t : b->subs) points += t->nd * t->ns;
+    const int64_t own = s_->nd * s_->ns;
+    const int copies =
+        static_cast<int>(std::min(kTuneCopies, std::max<int64_t>(1, std::min(points, kTunePoints) / own)));
+    FilterGroupOp<TS> o{};
+    o.op = &op_of<TS>(s_);
+    o.buf[0] = B<TS>(s_, 0);
+    o.buf[1] = B<TS>(s_, 1);
+    o.cur0 = 1 - s_->cur;  // step 1, the first with a Y_{k-1}, reads the current block
+    o.ld = s_->ld;
+    o.ncols = s_->ns;
+    o.alpha = static_cast<TS*>(s_->alpha);
+    o.coef = b->coef[i];
+    o.degree = 2;
+    ops_.push_back(o);
+    const size_t nblk = static_cast<size_t>(s_->ld) * s_->ns, nal = static_cast<size_t>(s_->nproj()) * s_->ns;
+    try {
+      while (static_cast<int>(ops_.size()) < copies) {
+        own_.push_back(nullptr);
+        TS* m = static_cast<TS*>(own_.back() = dalloc<TS>(nblk + nal));
+        XLS_HIP(hipMemsetAsync(m, 0, nblk * sizeof(TS), s_->st));
+        o.buf[1 - s_->cur] = m;
+        o.alpha = m + nblk;
+        ops_.push_back(o);
+      }
+    } catch (const Error& e) {
+      if (e.code != XLS_ERR_OUT_OF_MEMORY) throw;
+    }
+    launch_filter_coef(nullptr, s_->ns, -1.0, 0.0, 1.0, 2, b->coef[i], b->flags + i, s_->st);
   }
-  filter_group_free(g);
-  return static_cast<double>(ms) / reps / copies;
-}
+  ~FilterTimer() {
+    (void)hipStreamSynchronize(s_->st);
+    for (void* m : own_) dfree(m);
+  }
+  FilterTimer(const FilterTimer&) = delete;
+  FilterTimer& operator=(const FilterTimer&) = delete;
+
+  // Average ms of a step per subdomain under launch shape cfg; of its first
+  // launch only where that is twice `best` or more.
+  double time(const StencilLaunch& cfg, double best) {
+    for (auto& o : ops_) o.cfg = cfg;
+    FilterGroup<TS>* g = filter_group_build<TS>(ops_);
+    auto run = [&](int reps) {
+      float ms = 0.0f;
+      XLS_HIP(hipEventRecord(e0_, s_->st));
+      for (int r = 0; r < reps; ++r) filter_group_step<TS>(g, 1, s_->st);
+      XLS_HIP(hipEventRecord(e1_, s_->st));
+      XLS_HIP(hipEventSynchronize(e1_));
+      XLS_HIP(hipEventElapsedTime(&ms, e0_, e1_));
+      return static_cast<double>(ms) / reps / static_cast<double>(ops_.size());
+    };
+    double ms = 0.0;
+    try {
+      ms = run(1);
+      if (ms < 2.0 * best) ms = run(3);
+    } catch (...) {
+      (void)hipStreamSynchronize(s_->st);
+      filter_group_free(g);
+      throw;
+    }
+    filter_group_free(g);
+    return ms;
+  }
+
+ private:
+  xls_subdomain_s* s_;
+  hipEvent_t e0_, e1_;
+  std::vector<FilterGroupOp<TS>> ops_;
+  std::vector<void*> own_;
+};
 
 // GEMM classes: N_d bucketed to 32768 rows (the split-K count follows it),
 // ns to 32 columns (the tile grid follows it).
@@ -858,8 +896,9 @@ int tune_batch(xls_batch_s* b, const char* cache_path, double* best_ms_out) {
       };
       // the untuned shape, and whole-box tiles where they are faster by more
       // than such timings differ
-      constexpr double kGain = 0.98;
-      double best = time_filter<TS>(b, i, StencilLaunch{}, e0, e1), bar = kGain * best;
+      constexpr double kGain = 0.99;
+      auto timer = std::make_unique<FilterTimer<TS>>(b, i, e0, e1);
+      double best = timer->time(StencilLaunch{}, HUGE_VAL), bar = kGain * best;
       StencilLaunch narrow{};
       narrow.block = 256;
       narrow.tz = 0;
@@ -875,12 +914,13 @@ int tune_batch(xls_batch_s* b, const char* cache_path, double* best_ms_out) {
             cfg.tz = 0;  // as xls_subdomain_tune applies it below
             cfg.nv = nv;
             if (untuned_shape(c) || !fits(cfg)) continue;
-            const double ms = time_filter<TS>(b, i, cfg, e0, e1);
+            const double ms = timer->time(cfg, best);
             if (ms < bar) {
               best = bar = ms;
               arg = c;
             }
           }
+      timer.reset();
       if (temp) subdomain_ws_free(s);
       chosen[key] = arg;
       best_ms[key] = best;
