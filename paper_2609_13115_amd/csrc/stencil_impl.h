@@ -1080,9 +1080,11 @@ inline TileChoice choose_tiles(int nx, int ny, int nz, int elem, int nproj, int6
       // a shorter last round: FP32, 1.5e8 points, us whole and halved: 53 688, 702;
       // 57 746, 760; 60 666, 668; 63 705, 682; 65 733, 748; 66 734, 721; 69 688,
       // 690; 75 748, 730; 79 745, 727; 84 684, 664.  With more rounds the last one
-      // matters less than the planes read twice (2.7e8 points: 65 1298, 1298; 69
-      // 1243, 1230; 78 1234, 1251; 79 1273, 1293; 83 1191, 1201).
-      nzt = nz >= 56 && wgs < 3 * kTileSlots ? 2 : 1;
+      // matters less than the planes read twice: 2.7e8 points (3,300 to 4,900
+      // workgroups) 65 1298, 1298; 69 1243, 1230; 78 1234, 1251; 80 1158, 1134; 83
+      // 1191, 1201; 32 boxes of 53 to 80 points together (60,000) 605, 630 ms an
+      // iteration.
+      nzt = nz >= 56 && wgs < 6 * kTileSlots ? 2 : 1;
     else
       nzt = std::max(std::min<int64_t>((3 * kTileSlots + wgs - 1) / wgs, nz / 20),
                      std::min<int64_t>(kTileSlots / wgs, nz / 2));
