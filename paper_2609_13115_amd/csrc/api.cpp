@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -219,6 +220,66 @@ double gated_max(const double* r, int gate) {
   return mx;
 }
 
+namespace {
+
+// A word of pinned host memory that kernels on a stream may set while the host
+// looks at it, lent for one call: a page of 64 words serves the process (making
+// one takes 80 us).  Without a free word get() is null.
+class PinnedWord {
+ public:
+  explicit PinnedWord(hipStream_t st) : st_(st) {
+    Pool& p = pool();
+    std::lock_guard<std::mutex> lock(p.mu);
+    if (!p.page) {
+      void* m = nullptr;
+      if (hipHostMalloc(&m, kWords * kStride * sizeof(int32_t), hipHostMallocPortable) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+      }
+      p.page = static_cast<int32_t*>(m);
+    }
+    for (int i = 0; i < kWords; ++i)
+      if (!p.lent[i]) {
+        p.lent[i] = true;
+        i_ = i;
+        __atomic_store_n(get(), 0, __ATOMIC_RELAXED);
+        return;
+      }
+  }
+  ~PinnedWord() {
+    if (i_ >= 0) (void)hipStreamSynchronize(st_);  // nothing in flight sets the word of its next user
+    give_back();
+  }
+  PinnedWord(const PinnedWord&) = delete;
+  PinnedWord& operator=(const PinnedWord&) = delete;
+  int32_t* get() const { return i_ < 0 ? nullptr : pool().page + i_ * kStride; }
+  // Once the stream has been waited for.
+  void give_back() {
+    if (i_ < 0) return;
+    Pool& p = pool();
+    std::lock_guard<std::mutex> lock(p.mu);
+    p.lent[i_] = false;
+    i_ = -1;
+  }
+  bool set() const { return i_ >= 0 && __atomic_load_n(get(), __ATOMIC_RELAXED) != 0; }
+
+ private:
+  static constexpr int kWords = 64, kStride = 16;
+  struct Pool {
+    std::mutex mu;
+    int32_t* page = nullptr;
+    bool lent[kWords] = {};
+  };
+  static Pool& pool() {
+    static Pool* p = new Pool();  // lives as long as the process: the runtime may be gone before a destructor
+    return *p;
+  }
+  hipStream_t st_;
+  int i_ = -1;
+};
+
+}  // namespace
+
 template <typename TS>
 void lanczos_run(xls_subdomain_s* s, int k) {
   k = lanczos_steps(s, k);
@@ -253,10 +314,9 @@ void lanczos_run(xls_subdomain_s* s, int k) {
   // spectrum are taken from the steps up to the first that meets an invariant
   // Krylov space.  A step that finds one tells the host through pinned memory,
   // which launches no more (an eigenvector as start: 2 or 3 steps of 20).
-  if (!s->lz_done) XLS_HIP(hipHostMalloc(reinterpret_cast<void**>(&s->lz_done), sizeof(int32_t), hipHostMallocDefault));
-  __atomic_store_n(s->lz_done, 0, __ATOMIC_RELAXED);
+  PinnedWord done(s->st);
   int steps = 0;
-  for (int j = 0; j < k && __atomic_load_n(s->lz_done, __ATOMIC_RELAXED) == 0; ++j) {
+  for (int j = 0; j < k && !done.set(); ++j) {
     TS* vj = V + j * ld;
     apply_H<TS>(s, vj, w, 1, alph);
     // u = w - alpha v - beta v_prev waits in the place of the next vector; full
@@ -267,13 +327,14 @@ void lanczos_run(xls_subdomain_s* s, int k) {
                             ld, j + 1, s->nd, u, s->gwork, rb, s->st);
     launch_lanczos_reorth<TS>(u, V, ld, s->gwork, rb, j + 1, s->nd, w, part, nblocks, s->st);
     launch_lanczos_scale<TS>(u, w, part, nblocks, be + j, s->nd, s->st, al + j, j > 0 ? be + j - 1 : nullptr, top,
-                             s->lz_done);
+                             done.get());
     ++steps;
   }
   launch_tridiag_extremes(al, be, steps, nrm, s->st);
   double ext[4];
   XLS_HIP(hipMemcpyAsync(ext, nrm, sizeof(ext), hipMemcpyDeviceToHost, s->st));
   XLS_HIP(hipStreamSynchronize(s->st));
+  done.give_back();
   s->lz_lo = ext[0];
   s->lz_up = ext[1] + ext[2];
   s->happly -= steps - static_cast<int>(ext[3]);  // launched past the end: not part of the run

@@ -103,7 +103,6 @@ struct xls_subdomain_s {
   std::vector<double> lanczos_v0;
   void* lz = nullptr;  // [nd * (kmax + 2)]
   int lz_cols = 0;
-  int32_t* lz_done = nullptr;  // pinned host memory: a step found the space invariant
   bool have_lanczos = false;
   double lz_lo = 0, lz_up = 0;
   int lz_k = 0;
@@ -131,7 +130,6 @@ struct xls_subdomain_s {
                   orb_P, orb_D, orb_edges, orb_core};
     for (void* p : ps) xls::dfree(p);
     if (own_gwork) xls::dfree(gwork);
-    if (lz_done) (void)hipHostFree(lz_done);
     for (auto e : fev) (void)hipEventDestroy(e);
     if (dexec) (void)hipGraphExecDestroy(dexec);
     if (dgraph) (void)hipGraphDestroy(dgraph);

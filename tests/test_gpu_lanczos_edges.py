@@ -67,3 +67,32 @@ def test_an_early_end_counts_the_products_that_it_took(count):
         s.xls_chefsi_step(6, 1, xls.XLS_BOUNDS_LANCZOS)
         assert s.xls_subdomain_counters()["h_applies"] == 3 * (6 + 2)
     assert first == count + 3 * (6 + 2)
+
+
+# Handles of several threads at once, some with a start vector that ends early:
+# each stops on its own end.
+def test_threads_end_on_their_own_steps():
+    import threading
+    sd = box((6, 5, 7), 3, False)
+    H = hamiltonian.from_subdomain(sd).apply(np.eye(sd.nd))
+    lam, U = np.linalg.eigh(0.5 * (H + H.T))
+    full = np.random.default_rng(12).standard_normal(sd.nd)
+    vectors = [U[:, 0] + U[:, -1], full, U[:, 3] + U[:, 9] + U[:, -1], full]
+    got = [[] for _ in vectors]
+
+    def work(i):
+        with xls.Subdomain(sd, lanczos_v0=vectors[i]) as s:
+            for _ in range(20):
+                got[i].append(s.xls_lanczos_bounds(20))
+
+    print("[case] lanczos threads", flush=True)
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(vectors))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert all(len(g) == 20 and len(set(g)) == 1 for g in got)
+    assert got[1][0] == got[3][0]
+    tol = 1e-10 * np.abs(lam).max()
+    for i, (a, b) in ((0, (0, -1)), (2, (3, -1))):
+        assert abs(got[i][0][0] - lam[a]) <= tol and abs(got[i][0][1] - lam[b]) <= tol
