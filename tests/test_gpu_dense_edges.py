@@ -55,3 +55,26 @@ def test_one_wide_cluster():
     """Every gap below the cluster threshold: all vectors in one group."""
     print("[case] dense edges one cluster", flush=True)
     check(300, np.linspace(0.5, 0.6, 300), 0.2, 6)
+
+
+# Spectra that fall to 1e-14 of the largest state: hundreds of eigenvalues equal
+# to rounding, whose vectors come out of inverse iteration nearly parallel.
+# Vectors of one cluster are orthogonal to rounding, those of two clusters to eps
+# over the gap between them, 1e-3 |T| at least; twice that here.
+@pytest.mark.parametrize("n", [300, 480])
+def test_states_equal_to_rounding_are_orthogonal(n):
+    worst = 0.0
+    for seed in range(8):
+        print(f"[case] dense edges geometric n={n} seed={seed}", flush=True)
+        rng = np.random.default_rng(seed)
+
+        def full(lam):
+            q, _ = np.linalg.qr(rng.standard_normal((n, n)))
+            a = (q * lam) @ q.T
+            return 0.5 * (a + a.T)
+
+        H, M = full(10.0 ** -np.linspace(0, 14, n)), full(np.linspace(0.5, 2, n))
+        lam, Y = xls.xls_dense_geneig(H, M)
+        worst = max(worst, np.max(np.abs(Y.T @ M @ Y - np.eye(n))))
+        assert np.linalg.norm(H @ Y - (M @ Y) * lam) <= 1e-12 * np.linalg.norm(Y)
+    assert worst <= 2 * 2.3e-16 / 1e-3
