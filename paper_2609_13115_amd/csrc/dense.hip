@@ -324,7 +324,10 @@ __global__ __launch_bounds__(256) void trinv_kernel(const double* __restrict__ R
 // a few dependent FP64 operations instead of two barriers and two LDS trips
 // (n = 480 215 -> 61 us, 1201 1005 -> 300).  The latency of R's columns bounds
 // it: U steps of loads in flight count for more than columns that share them
-// (480 with two columns and four steps 70 us, 1201 with four and two 388).
+// (480 with two columns and four steps 70 us, 1201 with four and two 388), until
+// the registers run out: past 512 two columns and four steps, us at 600, 768, 950
+// and 1201: 99, 143, 195, 302 (one column and four steps 87, 126, 184, 312; two
+// and two 95, 135, 186, 279).
 // The quotient is corrected once by its remainder.
 template <int I, typename F>
 __device__ __forceinline__ void count_down(F& f) {
